@@ -19,9 +19,12 @@
  *   "hash.cap"               JOIN_HASH_CAP                R entries per LDS table, 64..9728
  *                                                         (batches: at most 4608, the table of
  *                                                         their 512-thread workgroups)
- *   "hash.slice"             JOIN_HASH_SLICE              S rows per work unit, >= 1024
+ *   "hash.slice"             JOIN_HASH_SLICE              S rows per work unit, >= 1024 (unset: 4096 to
+ *                                                         32768 by the probe side's size)
  *   "hash.bits"              JOIN_HASH_BITS               single-join fan-out log2, -1 automatic
  *   "hash.single_max_chunks" JOIN_HASH_SINGLE_MAX_CHUNKS  R up to this many tables: no partitioning
+ *                                                         (unset: 16, unless the probe rows would
+ *                                                         be probed too many times over)
  *   "theta.ts"               JOIN_THETA_TS                S rows per theta tile, 0 automatic
  *   "theta.waves"            JOIN_THETA_WAVES             waves a theta grid aims for, 0 automatic
  *   "theta.stash"            JOIN_THETA_STASH             matches stashed per theta work unit

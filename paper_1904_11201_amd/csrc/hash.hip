@@ -2284,20 +2284,48 @@ static int join_grid(int num_cus, int cap, bool rids)
     return num_cus * per_cu;
 }
 
-HashPlan hash_plan(int64_t nR, int64_t nS, int num_cus, int prebuilt_bits, bool semi)
+// S rows per unit of one join.  A unit builds its table once whatever its slice, so long slices
+// are better as long as there are units for every CU: 32K rows from 8M probe rows on, and below
+// that about one unit per CU, at least 4K rows (150K x 1M: 114 us a join with 32K, 81 with 4K;
+// 1M x 4M: 127 with 32K, 107 with 16K, 148 with 4K).
+static int default_slice(int64_t nS, int num_cus)
+{
+    int s = 4096;
+    while (s < 32768 && (int64_t)s * num_cus < nS) s *= 2;
+    return s;
+}
+
+// Whether a join of up to single_max build rows is joined without partitioning.  The
+// unpartitioned path probes every S row once per R chunk, so it repeats (chunks - 1) * nS
+// probes; partitioning reads and writes both sides once more in three more launches (about 25 us)
+// and probes once.  Measured (us a join, unpartitioned / partitioned): 18K x 4M 91 / 131,
+// x 16M 214 / 223; 36K x 1M 69 / 84, x 4M 142 / 122; 73K x 256K 60 / 70, x 1M 89 / 81;
+// 147K x 256K 69 / 70, x 1M 139 / 81, x 16M 1292 / 195.  The line lies at about 6M repeats.
+constexpr int64_t kSingleRepeats = (int64_t)6 << 20;
+// Fewer partitions than this make the histogram's and the scatter's LDS atomics collide
+// (18K x 16M: 270 us with 4 partitions, 223 with 16).
+constexpr int kMinBits = 5;
+
+HashPlan hash_plan(int64_t nR, int64_t nS, int num_cus, int prebuilt_bits, bool semi, bool keep_single)
 {
     HashPlan pl{};
     pl.nR = nR;
     pl.nS = nS;
     const int cap = env_cap();
     pl.cap = cap;
-    pl.slice = (int)tune_get(TUNE_HASH_SLICE, 32768);
+    pl.slice = (int)tune_get(TUNE_HASH_SLICE, default_slice(nS, num_cus));
     if (pl.slice < 1024) pl.slice = 1024;
-    const int64_t single_max = tune_get(TUNE_HASH_SINGLE_MAX, 16) * cap;
+    const int64_t single_knob = tune_get(TUNE_HASH_SINGLE_MAX, -1);
+    const int64_t single_max = (single_knob >= 0 ? single_knob : 16) * cap;
     pl.prebuilt = prebuilt_bits >= 0;
     pl.ordered = ordered_knob();
     const int forced_bits = pl.prebuilt ? prebuilt_bits : (int)tune_get(TUNE_HASH_BITS, -1);
-    pl.single = !pl.prebuilt && (forced_bits == 0 || (forced_bits < 0 && nR <= single_max));
+    // a join under single_max chunks set by the caller, or asked to stay unpartitioned
+    // (keep_single), is not moved by the rule above
+    const bool repeats_ok = single_knob >= 0 || keep_single ||
+                            (ceil_div(nR, cap) - 1) * nS <= kSingleRepeats;
+    pl.single = !pl.prebuilt &&
+                (forced_bits == 0 || (forced_bits < 0 && nR <= single_max && repeats_ok));
     if (semi && !pl.single) {
         // The semi-join's write pass visits about the matching probe rows only, so its units pay
         // their fixed costs (table build, per-unit loads) for few rows: S slices up to one unit
@@ -2325,7 +2353,7 @@ HashPlan hash_plan(int64_t nR, int64_t nS, int num_cus, int prebuilt_bits, bool 
         pl.Umax = (nR > 0 && nS > 0) ? nrc * nss : 0;
     } else {
         int bits = forced_bits;
-        if (bits < 0) bits = default_bits(nR, cap) < 1 ? 1 : default_bits(nR, cap);
+        if (bits < 0) bits = default_bits(nR, cap) < kMinBits ? kMinBits : default_bits(nR, cap);
         if (bits > kMaxBits) bits = kMaxBits;
         pl.bits = bits;
         pl.P = 1 << bits;

@@ -71,7 +71,10 @@ struct HashPlan {
 // prebuilt_bits >= 0: R is a resident build partitioned with that fan-out (no single path, no
 // R arrays in the workspace).
 // semi: record the semi-join in the count pass (ignored by the unpartitioned path).
-HashPlan hash_plan(int64_t nR, int64_t nS, int num_cus, int prebuilt_bits = -1, bool semi = false);
+// keep_single: leave a small build unpartitioned however many probe rows it meets (the
+// unpartitioned path's workspace does not grow with the inputs).
+HashPlan hash_plan(int64_t nR, int64_t nS, int num_cus, int prebuilt_bits = -1, bool semi = false,
+                   bool keep_single = false);
 
 // A build relation already partitioned (resident build): its partition sizes, starts, tuples.
 struct RView {

@@ -85,7 +85,10 @@ int join_hash_noalloc(const join_rel_t* R, const join_rel_t* S, int32_t* pairs, 
     if ((e = hipGetDevice(&dev)) != hipSuccess ||
         (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
         return hip_fail(e, "join_hash_noalloc: device attributes");
-    const HashPlan pl = hash_plan(R->n, S->n, cus > 0 ? cus : 256);
+    HashPlan pl = hash_plan(R->n, S->n, cus > 0 ? cus : 256);
+    // a small build against many probe rows would be partitioned; when its partitioned tuples do
+    // not fit the array, it is joined unpartitioned, in under 100 KB
+    if (pl.bytes > kScratchBytes) pl = hash_plan(R->n, S->n, cus > 0 ? cus : 256, -1, false, true);
     if (pl.bytes > kScratchBytes) {
         set_error("join_hash_noalloc: this join needs %zu bytes of scratch, above the %zu bytes of "
                   "the static array; use join_hash with a workspace", pl.bytes, kScratchBytes);
