@@ -131,7 +131,8 @@ int check_args(int kind, const join_rel_t* R, const join_rel_t* S, const join_pr
 
 RegionPlan plan_region(int64_t nR, int64_t nS, const join_pred_t* p)
 {
-    return region_plan(nR, nS, p ? p->op_a : JOIN_OP_NONE, theta_stash_k());
+    return region_plan(nR, nS, p ? p->op_a : JOIN_OP_NONE, p ? p->op_c : JOIN_OP_NONE, num_cus(),
+                       theta_stash_k());
 }
 
 // Signature of the plan a call of this kind makes for these sizes under the current knobs
@@ -318,7 +319,7 @@ DebugView debug_view(int kind, int64_t nR, int64_t nS, const join_pred_t* p)
         v = DebugView{pl.off_dbg, pl.off_dbg, pl.off_counts, pl.U, pl.U};
     } else if (kind == JOIN_KIND_THETA_REGION) {
         const RegionPlan pl = plan_region(nR, nS, p);
-        v = DebugView{pl.off_dbg, pl.off_dbg, pl.off_counts, pl.Umax, pl.nOff};
+        v = DebugView{pl.off_dbg, pl.off_dbg, pl.off_counts, pl.U, pl.U};
     }
     return v;
 }

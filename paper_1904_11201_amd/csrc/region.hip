@@ -1,722 +1,1118 @@
 // region.hip -- theta join with region pruning on gfx950 (the paper's improved theta join).
 //
-// Section 4.2 cuts the |T| x |S| matrix into square regions of join-key ranges, with the same
-// range boundaries on both axes (k quantiles, figure "classb"), and classifies each region from
-// its ranges alone (figures "greena"/"greenb"/"greenc"): in a green region every pair satisfies
-// the condition, in a white region none does, and only the red regions need pair-by-pair
-// evaluation on the GPU (Algorithm 3: red = the diagonal, sent to GPU_theta_join; green =
-// cross join).  Here:
-//   1. range:      min and max of column a over R and S;
-//   2. fine bins:  2^14 power-of-two bins over [min, max], histogram of each side;
-//   3. buckets:    B buckets (quantiles of the union) made of whole bins, so both sides share
-//                  the same boundaries; each bucket knows its value range [lo_b, hi_b];
-//   4. partition:  R and S are scattered by bucket (columns a, c, rid);
-//   5. classify:   for each R bucket i and S bucket j, the pair of value ranges decides white,
-//                  green or red for op_a; a condition on column c turns green into red;
-//   6. red:        the red S buckets of R bucket i are contiguous: their rows become units
-//                  (512 R rows x <= 8 S tiles) of the tiled nested-loop kernels;
-//   7. green:      counted as |R_i| * |S rows| with no evaluation, written as a cross product.
-// The result is exactly the nested-loop result: every pair is either in a red unit (evaluated),
-// in a green span (holds by the range argument) or in a white span (cannot hold).
+// Section 4.2 cuts the |T| x |S| matrix into regions of join-key ranges, with the same range
+// boundaries on both axes (quantiles, figure "classb"), and classifies each region from its
+// ranges alone (figures "greena"/"greenb"/"greenc"): in a green region every pair satisfies the
+// condition, in a white region none does, and only red regions need pair-by-pair evaluation
+// (Algorithm 3).  Here the regions shrink to single R rows: with both sides sorted by column a,
+// the S rows that satisfy op_a with one R row are one interval of S (two for !=), found by binary
+// search.  Inside it every row is green for op_a, outside it white, and nothing is left red: a
+// condition on column c is the only thing evaluated pair by pair, and only inside the interval.
+//
+//   1. setup:    value bins over a sample of both sides (gathered by one launch, binned by the
+//                next), buckets (quantiles of the sample) made of whole bins, so both sides share
+//                boundaries and bucket ids rise with the value;
+//   2. sizes:    rows of each bucket; the last workgroup turns them into starts;
+//   3. scatter:  rows (a, [c,] rid) into their buckets, tile by tile through LDS;
+//   4. sort:     each bucket sorted by a in LDS, written as columns: both sides are sorted;
+//   5. count:    each R row's interval and its matches; the last workgroup scans the counts;
+//   6. write:    the pairs of each wave from the offset the count pass gave it.
+// Sides that fit one workgroup's LDS skip 1 to 3.
+//
+// What bounds it: launches and dependent memory round trips up to 1M rows a side (every pass
+// moves 8 to 32 MB, 2 to 8 us at the copy rate, and takes 4 to 29), from 4M on the LDS work of
+// the sort and the partition's traffic.  Count pass of a band of w = 8 at 4M x 4M: sample and
+// setup 19 us, sizes 24, scatter 58, sort 79, intervals and counts 55.  The former design put
+// every R row of a bucket against every S row of its red span, in 26 launches: 1M x 1M with a
+// condition on c 414 us of kernels, now 110; the count at 4M x 4M 1200, now 239.
 #include "region.hpp"
 #include "debug.hpp"
 
 #include "prof.hpp"
-#include "scan.hpp"
-#include "theta.hpp"
 
 namespace jl {
 
 namespace {
 
-constexpr int kBinBits = 14;
-constexpr int kBins = 1 << kBinBits;
-constexpr int kBlk = 256;
-constexpr int kTile = 2048;        // tuples staged per scatter step
-constexpr int kRBlockRows = 512;   // R rows per unit (one wave, 8 rows per lane)
-#ifndef JL_REGION_TILE
-#define JL_REGION_TILE 128
-#endif
-constexpr int kTileRows = JL_REGION_TILE;     // S rows per unit, at least
-constexpr int kMaxTiles = 8;       // S tiles per R block, at most (the tile grows beyond)
-constexpr int kCrossWaves = 4;
-constexpr int kSortCap = 2048;     // S rows of a bucket split in LDS for band trimming, at most
-constexpr int kSortBlk = 256;
-
-enum : int { kWhite = 0, kGreen = 1, kRed = 2 };
+constexpr int kBlk = 1024;        // threads of the partition and sort kernels
+constexpr int kPer = 4;           // rows per thread
+constexpr int kCap = kBlk * kPer; // rows of a scatter tile, and of one LDS sort
+constexpr int kSortBlk = 512;     // threads of a sort: four workgroups share a CU
+constexpr int kSortPer = kCap / kSortBlk;
+constexpr int kMeanRows = 2048;   // a bucket's mean size, at most (while B < kMaxBuckets)
+constexpr int kMaxBits = 13;      // 2^13 buckets: 64 KB of LDS state beside the scatter's tile
+constexpr int kMinBinBits = 10;   // at least one bin per thread of the setup workgroup
+constexpr int kMaxBinBits = 14;   // 64 KB of LDS counters
+constexpr int kSubBits = 12;      // value bins of one LDS sort: about one row each
+constexpr int kSub = 1 << kSubBits;
+constexpr uint32_t kRankBin = 64; // rows of a bin ranked one against the other, at most
+constexpr int kJoinBlk = 256;     // threads of the count and write kernels
+constexpr int kJoinWaves = kJoinBlk / kWave;
+constexpr int64_t kMaxBlocks = 4096;  // R blocks of the count pass
+// Intervals up to this length are walked lane by lane: neighbouring rows' intervals start close
+// together, so each step's loads are nearly consecutive.  Longer ones are walked by the whole
+// wave, one S row (condition on c) or one R row (none) at a time.
+constexpr uint32_t kSerial = 32;
 
 struct Hdr {
     uint64_t total;
-    uint32_t U;     // red units
-    uint32_t pad;
-    int32_t lo, hi; // range of column a over R and S
-    uint32_t shift; // bin = (uint32)(a - lo) >> shift
-    uint32_t pad2;
+    int32_t lo;      // smallest sampled value
+    uint32_t shift;  // bin = (a - lo) >> shift, clamped to the outer bins
+    uint32_t nbins;
 };
 
-struct BucketInfo {
-    uint32_t rStart, nR;      // R rows of the bucket (bucketed order)
-    uint32_t red0, red1;      // S rows evaluated pair by pair
-    uint32_t gl0, gl1;        // S rows of the green span left of the red span
-    uint32_t gr0, gr1;        // S rows of the green span right of it
-    uint32_t tiles, ts;       // S tiles per R block and their length
-    uint32_t pad0, pad1;
+// Words of the cleared area: sizes of R's and S's buckets, arrivals at S's buckets of more than
+// kCap rows, then these counters.
+constexpr int kCntExtra = 0;  // entries of the extra chunk list
+constexpr int kCntHist = 32;  // workgroups that finished the bucket sizes (an arrival set each)
+constexpr int kArrivals = 32; // counters of an arrival set, and the words between two of them
+constexpr int kCntCount = kCntHist + (kArrivals + 1) * 32;  // workgroups that finished counting
+constexpr int kCounters = kCntCount + (kArrivals + 1) * 32;
+
+struct Cols {
+    const int32_t *a, *c, *rid;
+    int64_t n;
 };
 
 __device__ __forceinline__ uint32_t bin_of(int32_t a, const Hdr& h)
 {
-    return (uint32_t)((uint32_t)a - (uint32_t)h.lo) >> h.shift;
+    const uint32_t d = a < h.lo ? 0u : (uint32_t)a - (uint32_t)h.lo;
+    return min(d >> h.shift, h.nbins - 1);
 }
 
-// ---------------------------------------------------------------------------- range + bins --
-__global__ void init_k(Hdr* h, uint32_t* hist2)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) {
-        h->lo = INT32_MAX;
-        h->hi = INT32_MIN;
-    }
-    if (i < 2 * kBins) hist2[i] = 0;
-}
-
-__global__ __launch_bounds__(kBlk) void range_k(const int32_t* __restrict__ Ra, int64_t nR,
-                                                const int32_t* __restrict__ Sa, int64_t nS,
-                                                Hdr* h)
-{
-    int32_t lo = INT32_MAX, hi = INT32_MIN;
-    const int64_t n = nR + nS;
-    for (int64_t i = (int64_t)blockIdx.x * kBlk + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlk) {
-        const int32_t a = i < nR ? Ra[i] : Sa[i - nR];
-        lo = a < lo ? a : lo;
-        hi = a > hi ? a : hi;
-    }
-    __shared__ int32_t slo, shi;
-    if (threadIdx.x == 0) {
-        slo = INT32_MAX;
-        shi = INT32_MIN;
-    }
-    __syncthreads();
-    atomicMin(&slo, lo);
-    atomicMax(&shi, hi);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        atomicMin(&h->lo, slo);
-        atomicMax(&h->hi, shi);
-    }
-}
-
-__global__ void shift_k(Hdr* h)
-{
-    const uint32_t span = (uint32_t)h->hi - (uint32_t)h->lo;  // hi >= lo
-    const int len = span ? 32 - __builtin_clz(span) : 0;
-    h->shift = len > kBinBits ? (uint32_t)(len - kBinBits) : 0u;
-}
-
-__global__ __launch_bounds__(kBlk) void finehist_k(const int32_t* __restrict__ a, int64_t n,
-                                                   const Hdr* __restrict__ h,
-                                                   uint32_t* __restrict__ hist)
-{
-    __shared__ uint32_t lh[kBins];
-    for (int i = threadIdx.x; i < kBins; i += kBlk) lh[i] = 0;
-    __syncthreads();
-    const Hdr hh = *h;
-    for (int64_t i = (int64_t)blockIdx.x * kBlk + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlk)
-        atomicAdd(&lh[bin_of(a[i], hh)], 1u);
-    __syncthreads();
-    for (int i = threadIdx.x; i < kBins; i += kBlk)
-        if (lh[i]) atomicAdd(&hist[i], lh[i]);
-}
-
-// Bucket of every bin: buckets of about (|R| + |S|) / B tuples made of whole bins, so the
-// bucket ids are non-decreasing in the value; and each bucket's value range.
-__global__ __launch_bounds__(1024) void buckets_k(const uint32_t* __restrict__ hR,
-                                                  const uint32_t* __restrict__ hS, const Hdr* h,
-                                                  int B, uint64_t N, uint16_t* __restrict__ lut,
-                                                  int64_t* __restrict__ vlo,
-                                                  int64_t* __restrict__ vhi)
-{
-    constexpr int PER = kBins / 1024;
-    __shared__ uint32_t wsum[1024 / kWave + 1];
-    __shared__ uint32_t first[4096], last[4096];
-    const int t = threadIdx.x;
-    for (int b = t; b < B; b += 1024) {
-        first[b] = kBins;
-        last[b] = 0;
-    }
-    uint32_t c[PER], s = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        c[k] = hR[t * PER + k] + hS[t * PER + k];
-        s += c[k];
-    }
-    uint32_t tot;
-    uint64_t run = block_excl_scan<1024>(s, wsum, &tot);
-    uint16_t id[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        uint64_t b = run * (uint64_t)B / (N ? N : 1);
-        id[k] = (uint16_t)(b < (uint64_t)B ? b : (uint64_t)(B - 1));
-        lut[t * PER + k] = id[k];
-        run += c[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        atomicMin(&first[id[k]], (uint32_t)(t * PER + k));
-        atomicMax(&last[id[k]], (uint32_t)(t * PER + k));
-    }
-    __syncthreads();
-    const Hdr hh = *h;
-    for (int b = t; b < B; b += 1024) {
-        if (first[b] == (uint32_t)kBins) {  // no bin maps here: an empty bucket
-            vlo[b] = 1;
-            vhi[b] = 0;
-        } else {
-            int64_t lo = (int64_t)hh.lo + ((int64_t)first[b] << hh.shift);
-            int64_t hi = (int64_t)hh.lo + (((int64_t)last[b] + 1) << hh.shift) - 1;
-            vlo[b] = lo;
-            vhi[b] = hi < (int64_t)hh.hi ? hi : (int64_t)hh.hi;
-        }
-    }
-}
-
-// ------------------------------------------------------------------------ bucket partition --
-__global__ __launch_bounds__(kBlk) void bhist_k(const int32_t* __restrict__ a, int64_t n,
-                                                int64_t chunk, const Hdr* __restrict__ h,
-                                                const uint16_t* __restrict__ lut, int B,
-                                                uint32_t* __restrict__ hist, int64_t nCh)
-{
-    extern __shared__ uint32_t lh[];
-    for (int i = threadIdx.x; i < B; i += kBlk) lh[i] = 0;
-    __syncthreads();
-    const Hdr hh = *h;
-    const int64_t beg = (int64_t)blockIdx.x * chunk;
-    const int64_t end = beg + chunk < n ? beg + chunk : n;
-    for (int64_t i = beg + threadIdx.x; i < end; i += kBlk) atomicAdd(&lh[lut[bin_of(a[i], hh)]], 1u);
-    __syncthreads();
-    for (int b = threadIdx.x; b < B; b += kBlk) hist[(int64_t)b * nCh + blockIdx.x] = lh[b];
-}
-
-// LDS: cursor[B] | tstart[B + 1] | sa[T] | sc[T] | sr[T] | sp[T] (uint16)
-template <bool HAS_C, bool HAS_RID>
-__global__ __launch_bounds__(kBlk) void bscatter_k(const int32_t* __restrict__ a,
-                                                   const int32_t* __restrict__ c,
-                                                   const int32_t* __restrict__ rid, int64_t n,
-                                                   int64_t chunk, const Hdr* __restrict__ h,
-                                                   const uint16_t* __restrict__ lut, int B,
-                                                   const uint32_t* __restrict__ off, int64_t nCh,
-                                                   int32_t* __restrict__ oa, int32_t* __restrict__ oc,
-                                                   int32_t* __restrict__ orid)
-{
-    extern __shared__ uint32_t lds[];
-    __shared__ uint32_t wsum[kBlk / kWave + 1];
-    constexpr int IT = kTile / kBlk;
-    uint32_t* cursor = lds;
-    uint32_t* tstart = lds + B;
-    int32_t* sa = reinterpret_cast<int32_t*>(tstart + B + 1);
-    int32_t* sc = sa + kTile;
-    int32_t* sr = sc + kTile;
-    uint16_t* sp = reinterpret_cast<uint16_t*>(sr + kTile);
-    const int tid = threadIdx.x;
-    const Hdr hh = *h;
-    for (int b = tid; b < B; b += kBlk) {
-        cursor[b] = off[(int64_t)b * nCh + blockIdx.x];
-        tstart[b] = 0;
-    }
-    __syncthreads();
-    const int64_t beg = (int64_t)blockIdx.x * chunk;
-    const int64_t end = beg + chunk < n ? beg + chunk : n;
-    const int seg = (B + kBlk - 1) / kBlk;
-    for (int64_t t0 = beg; t0 < end; t0 += kTile) {
-        const int tn = (int)(end - t0 < kTile ? end - t0 : kTile);
-        int32_t va[IT], vc[IT], vr[IT];
-        uint32_t p[IT], rank[IT];
-#pragma unroll
-        for (int q = 0; q < IT; ++q) {
-            const int e = q * kBlk + tid;
-            const bool ok = e < tn;
-            va[q] = ok ? a[t0 + e] : 0;
-            vc[q] = (HAS_C && ok) ? c[t0 + e] : 0;
-            vr[q] = ok ? (HAS_RID ? rid[t0 + e] : (int32_t)(t0 + e)) : 0;
-        }
-#pragma unroll
-        for (int q = 0; q < IT; ++q) {
-            const int e = q * kBlk + tid;
-            p[q] = e < tn ? lut[bin_of(va[q], hh)] : 0u;
-            rank[q] = e < tn ? atomicAdd(&tstart[p[q]], 1u) : 0u;
-        }
-        __syncthreads();
-        {
-            uint32_t s = 0;
-            for (int i = 0; i < seg; ++i) {
-                const int b = tid * seg + i;
-                s += b < B ? tstart[b] : 0u;
-            }
-            uint32_t tot;
-            uint32_t run = block_excl_scan<kBlk>(s, wsum, &tot);
-            for (int i = 0; i < seg; ++i) {
-                const int b = tid * seg + i;
-                if (b < B) {
-                    const uint32_t x = tstart[b];
-                    tstart[b] = run;
-                    run += x;
-                }
-            }
-            if (tid == 0) tstart[B] = (uint32_t)tn;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < IT; ++q) {
-            const int e = q * kBlk + tid;
-            if (e < tn) {
-                const uint32_t pos = tstart[p[q]] + rank[q];
-                sa[pos] = va[q];
-                if (HAS_C) sc[pos] = vc[q];
-                sr[pos] = vr[q];
-                sp[pos] = (uint16_t)p[q];
-            }
-        }
-        __syncthreads();
-        for (int e = tid; e < tn; e += kBlk) {
-            const uint32_t b = sp[e];
-            const uint32_t gidx = cursor[b] + ((uint32_t)e - tstart[b]);
-            oa[gidx] = sa[e];
-            if (HAS_C) oc[gidx] = sc[e];
-            orid[gidx] = sr[e];
-        }
-        __syncthreads();
-        for (int b = tid; b < B; b += kBlk) cursor[b] += tstart[b + 1] - tstart[b];
-        __syncthreads();
-        for (int b = tid; b < B; b += kBlk) tstart[b] = 0;
-        __syncthreads();
-    }
-}
-
-// --------------------------------------------------------------------------- classification --
-// Class of the region (R values in [rlo, rhi]) x (S values in [slo, shi]) for R.a op S.a.
-__device__ __forceinline__ int region_class(int op, int64_t w, int64_t rlo, int64_t rhi,
-                                            int64_t slo, int64_t shi)
-{
-    switch (op) {
-    case JOIN_OP_EQ:
-        if (rhi < slo || shi < rlo) return kWhite;
-        return (rlo == rhi && slo == shi) ? kGreen : kRed;
-    case JOIN_OP_NE:
-        if (rhi < slo || shi < rlo) return kGreen;
-        return (rlo == rhi && slo == shi) ? kWhite : kRed;
-    case JOIN_OP_LT:
-        if (rhi < slo) return kGreen;
-        if (rlo >= shi) return kWhite;
-        return kRed;
-    case JOIN_OP_LE:
-        if (rhi <= slo) return kGreen;
-        if (rlo > shi) return kWhite;
-        return kRed;
-    case JOIN_OP_GT:
-        if (rlo > shi) return kGreen;
-        if (rhi <= slo) return kWhite;
-        return kRed;
-    case JOIN_OP_GE:
-        if (rlo >= shi) return kGreen;
-        if (rhi < slo) return kWhite;
-        return kRed;
-    case JOIN_OP_BAND: {
-        int64_t dmin = slo - rhi > rlo - shi ? slo - rhi : rlo - shi;
-        if (dmin < 0) dmin = 0;
-        const int64_t dmax = shi - rlo > rhi - slo ? shi - rlo : rhi - slo;
-        if (dmin > w) return kWhite;
-        if (dmax <= w) return kGreen;
-        return kRed;
-    }
-    default: return kRed;
-    }
-}
-
-__device__ __forceinline__ int wave_min_i(int v)
+__device__ __forceinline__ int32_t wave_min_i(int32_t v)
 {
     for (int o = kWave / 2; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
     return v;
 }
 
-__device__ __forceinline__ int wave_max_i(int v)
+__device__ __forceinline__ int32_t wave_max_i(int32_t v)
 {
     for (int o = kWave / 2; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
     return v;
 }
 
-// Band joins: the S rows of every bucket of at most kSortCap rows are split three ways by a:
-// low (a < vlo + w), middle, high (a > vhi - w), each keeping its c and rid, and the two split
-// points are recorded.  An R bucket's band reaches into a neighbouring S bucket only through that
-// bucket's near edge: a left neighbour contributes only its high rows, a right neighbour only
-// its low rows, so classify_k trims the red span to them.  A bucket that is not split (larger
-// than kSortCap, or narrower than 2w, where the parts would overlap) records split points that
-// trim nothing.  One workgroup per bucket, the rows staged in LDS, kSplitRows per thread.
-constexpr int kSplitRows = kSortCap / kSortBlk;
-
-__global__ __launch_bounds__(kSortBlk) void bsplit_k(const uint32_t* __restrict__ offS, int64_t nChS,
-                                                     uint32_t nS, int B, const int64_t* __restrict__ vlo,
-                                                     const int64_t* __restrict__ vhi, int64_t w,
-                                                     int32_t* __restrict__ Sa, int32_t* __restrict__ Sc,
-                                                     int32_t* __restrict__ Sr, uint32_t* __restrict__ split)
+// Smallest and largest value of a BLOCK-thread workgroup; red: 2 * BLOCK / 64 words of LDS.
+template <int BLOCK>
+__device__ __forceinline__ void block_range(int32_t& lo, int32_t& hi, int32_t* red)
 {
-    __shared__ int32_t ta[kSortCap], tc[kSortCap], tr[kSortCap];
-    __shared__ uint32_t tmp[kSortBlk / kWave + 1];
-    const int b = blockIdx.x;
-    const int tid = threadIdx.x;
-    const uint32_t s0 = offS[(int64_t)b * nChS];
-    const uint32_t s1 = b + 1 < B ? offS[(int64_t)(b + 1) * nChS] : nS;
-    const uint32_t n = s1 - s0;
-    const int64_t lo = vlo[b], hi = vhi[b];
-    if (n == 0 || n > (uint32_t)kSortCap || hi - lo < 2 * w) {  // uniform
-        if (tid == 0) {
-            split[2 * b] = s1;      // low rows end: the whole bucket
-            split[2 * b + 1] = s0;  // high rows start: the whole bucket
-        }
-        return;
-    }
-    for (uint32_t i = tid; i < n; i += kSortBlk) {
-        ta[i] = Sa[s0 + i];
-        if (Sc) tc[i] = Sc[s0 + i];
-        tr[i] = Sr[s0 + i];
+    constexpr int W = BLOCK / kWave;
+    lo = wave_min_i(lo);
+    hi = wave_max_i(hi);
+    if (lane_id() == 0) {
+        red[threadIdx.x / kWave] = lo;
+        red[W + threadIdx.x / kWave] = hi;
     }
     __syncthreads();
-    // thread t holds rows [t * kSplitRows, ...): category 0 low, 1 middle, 2 high
-    const uint32_t r0 = (uint32_t)tid * kSplitRows;
-    uint32_t cl = 0, cm = 0;
-    uint8_t cat[kSplitRows];
-#pragma unroll
-    for (int k = 0; k < kSplitRows; ++k) {
-        const uint32_t i = r0 + k;
-        const int64_t a = i < n ? (int64_t)ta[i] : 0;
-        cat[k] = a < lo + w ? 0 : (a > hi - w ? 2 : 1);
-        if (i < n) {
-            cl += cat[k] == 0;
-            cm += cat[k] == 1;
-        }
+    for (int w = 0; w < W; ++w) {
+        lo = min(lo, red[w]);
+        hi = max(hi, red[W + w]);
     }
-    uint32_t L, M;
-    const uint32_t pl = block_excl_scan<kSortBlk>(cl, tmp, &L);
-    const uint32_t pm = block_excl_scan<kSortBlk>(cm, tmp, &M);
-    uint32_t ql = pl, qm = L + pm, qh = L + M + ((r0 < n ? r0 : n) - pl - pm);
+    __syncthreads();
+}
+
+// Waits for every memory access of the wave, and keeps the compiler from moving any across.
+__device__ __forceinline__ void drain()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+}
+
+// Whether this is the last of `total` workgroups to arrive (one thread calls it, workgroup id <
+// total).  Atomics on one address take about 10 ns each, 41 us for 4096 workgroups, so the
+// workgroups arrive at 32 counters on lines of their own, and the last at each at one more.
+__device__ __forceinline__ bool arrive_last(uint32_t* set, uint32_t id, uint32_t total)
+{
+    const uint32_t k = id % kArrivals;
+    const uint32_t expect = (total - k + kArrivals - 1) / kArrivals;
+    if (atomicAdd(&set[(k + 1) * 32], 1u) != expect - 1) return false;
+    return atomicAdd(set, 1u) == min(total, (uint32_t)kArrivals) - 1;
+}
+
+// Bits to shift a value span so that it falls below 2^bits.
+__device__ __forceinline__ uint32_t span_shift(uint32_t span, int bits)
+{
+    const int len = span ? 32 - __builtin_clz(span) : 0;
+    return len > bits ? (uint32_t)(len - bits) : 0u;
+}
+
+// ----------------------------------------------------------------------------------- setup --
+// Evenly spaced rows of R, then of S, as one array, and the counters cleared.  Many workgroups,
+// so that the scattered reads overlap (one workgroup took 64 us for 16K rows a side).
+__global__ __launch_bounds__(kBlk) void sample_k(Cols R, Cols S, uint32_t sR, uint32_t sS,
+                                                 int32_t* __restrict__ sample, uint32_t* __restrict__ zero,
+                                                 uint32_t zeroWords)
+{
+    const uint32_t i = blockIdx.x * kBlk + threadIdx.x;
+    if (i < sR) sample[i] = R.a[i * (R.n / sR)];
+    else if (i < sR + sS) sample[i] = S.a[(i - sR) * (S.n / sS)];
+    for (uint32_t z = i; z < zeroWords; z += gridDim.x * kBlk) zero[z] = 0;
+}
+
+// One workgroup: bins over the sampled range, buckets of about equal sample counts.  Rows outside
+// the sampled range fall into the outer bins, so an outlier does not stretch the bins.  A
+// bucket's size follows its sample count, 16 rows or more, so that it stays under kCap (twice the
+// mean or more) for all but a few buckets; those are sorted in several chunks.
+__global__ __launch_bounds__(kBlk) void setup_k(const int32_t* __restrict__ sample, uint32_t m, int binBits,
+                                                int bits, Hdr* __restrict__ h, uint16_t* __restrict__ lut)
+{
+    extern __shared__ uint32_t bins[];
+    __shared__ int32_t red[2 * kBlk / kWave];
+    __shared__ uint32_t wsum[kBlk / kWave + 1];
+    const int tid = threadIdx.x;
+    const int nb = 1 << binBits;
+    for (int i = tid; i < nb; i += kBlk) bins[i] = 0;
+    constexpr int kBatch = 16;  // loads of a thread in flight together
+    auto each = [&](auto f) {
+        for (uint32_t i0 = 0; i0 < m; i0 += kBlk * kBatch) {
+            int32_t a[kBatch];
 #pragma unroll
-    for (int k = 0; k < kSplitRows; ++k) {
-        const uint32_t i = r0 + k;
-        if (i < n) {
-            const uint32_t d = cat[k] == 0 ? ql++ : (cat[k] == 1 ? qm++ : qh++);
-            Sa[s0 + d] = ta[i];
-            if (Sc) Sc[s0 + d] = tc[i];
-            Sr[s0 + d] = tr[i];
+            for (int k = 0; k < kBatch; ++k) a[k] = sample[min(i0 + k * kBlk + tid, m - 1)];
+#pragma unroll
+            for (int k = 0; k < kBatch; ++k)
+                if (i0 + k * kBlk + tid < m) f(a[k]);
         }
-    }
-    if (tid == 0) {
-        split[2 * b] = s0 + L;
-        split[2 * b + 1] = s0 + L + M;
+    };
+    int32_t lo = INT32_MAX, hi = INT32_MIN;
+    each([&](int32_t a) {
+        lo = min(lo, a);
+        hi = max(hi, a);
+    });
+    block_range<kBlk>(lo, hi, red);
+    const Hdr hh{0, lo, span_shift((uint32_t)hi - (uint32_t)lo, binBits), (uint32_t)nb};
+    if (tid == 0) *h = hh;
+    each([&](int32_t a) { atomicAdd(&bins[bin_of(a, hh)], 1u); });
+    __syncthreads();
+    const int per = nb / kBlk;
+    uint32_t s = 0, tot;
+    for (int k = 0; k < per; ++k) s += bins[tid * per + k];
+    uint32_t run = block_excl_scan<kBlk>(s, wsum, &tot);
+    for (int k = 0; k < per; ++k) {
+        const uint32_t c = bins[tid * per + k];
+        const uint32_t b = (run << bits) / tot;  // run <= tot <= 2^16, bits <= 13
+        lut[tid * per + k] = (uint16_t)min(b, (1u << bits) - 1);
+        run += c;
     }
 }
 
-// One wave per R bucket: red span, adjacent green spans, units and green pair counts.  The S
-// buckets are classified by the wave's lanes together; every span end is a wave-wide min or max.
-__global__ __launch_bounds__(kWave) void classify_k(const uint32_t* __restrict__ offR, int64_t nChR,
-                                                    const uint32_t* __restrict__ offS, int64_t nChS,
-                                                    uint32_t nR, uint32_t nS,
-                                                    const int64_t* __restrict__ vlo,
-                                                    const int64_t* __restrict__ vhi, int B, int op,
-                                                    int64_t w, int has_c, const uint32_t* __restrict__ split,
-                                                    BucketInfo* __restrict__ info,
-                                                    uint32_t* __restrict__ units,
-                                                    uint64_t* __restrict__ green)
+// --------------------------------------------------------------------------- bucket sizes --
+// Exclusive starts of a side's B buckets (base[0..B], cur: the scatter's cursors), and an entry
+// of the extra chunk list for every chunk of kCap rows of a bucket past its first one.
+__device__ void bucket_starts(const uint32_t* tot, uint32_t* base, uint32_t* cur, int B, uint32_t side,
+                              uint2* extra, uint32_t* nextra, uint32_t* wsum)
 {
-    const int i = blockIdx.x;
-    const int lane = threadIdx.x;
-    if (i >= B) {
-        if (lane == 0) units[B] = 0;
+    uint32_t carry = 0;
+    for (int b0 = 0; b0 < B; b0 += kBlk) {
+        const int b = b0 + (int)threadIdx.x;
+        const uint32_t n = b < B ? tot[b] : 0u;
+        uint32_t sum;
+        const uint32_t at = carry + block_excl_scan<kBlk>(n, wsum, &sum);
+        if (b < B) {
+            base[b] = at;
+            cur[b] = at;
+            if (n > (uint32_t)kCap) {
+                const uint32_t k = (n - 1) / kCap;
+                const uint32_t x = atomicAdd(nextra, k);
+                for (uint32_t j = 0; j < k; ++j) extra[x + j] = make_uint2(side << 31 | (uint32_t)b, j + 1);
+            }
+        }
+        carry += sum;
+    }
+    if (threadIdx.x == 0) base[B] = carry;
+}
+
+struct Sides {
+    Cols X[2];           // R, S
+    uint32_t split;      // workgroups of R (S's follow)
+    int64_t chunk;       // rows per workgroup
+    const Hdr* h;
+    const uint16_t* lut;
+    int B;
+    uint32_t* zero;      // [2B] sizes, [B] arrivals, counters
+    uint32_t *base, *cur;  // [2][B + 1], [2][B]
+    uint2* extra;
+    uint16_t* id[2];     // each row's bucket
+    void* part[2];       // bucketed rows: int4 (a, c, rid, 0) with a condition on c, else int2 (a, rid)
+    int32_t *oa[2], *oc[2], *orid[2];  // sorted columns
+};
+
+// The bucket of every row is kept (16 bits a row) for the scatter.  The table of bins goes through
+// LDS: a gather from the caches serves one line per clock and lane.
+// LDS: cnt[B] | lut[nbins] (16 bits)
+__global__ __launch_bounds__(kBlk) void sizes_k(Sides s)
+{
+    extern __shared__ uint32_t cnt[];
+    uint16_t* lut = reinterpret_cast<uint16_t*>(cnt + s.B);
+    __shared__ uint32_t wsum[kBlk / kWave + 1];
+    __shared__ uint32_t last;
+    const int side = blockIdx.x >= s.split;
+    const int64_t beg = (int64_t)(blockIdx.x - (side ? s.split : 0)) * s.chunk;
+    const Cols X = s.X[side];
+    const int64_t end = beg + s.chunk < X.n ? beg + s.chunk : X.n;
+    for (int b = threadIdx.x; b < s.B; b += kBlk) cnt[b] = 0;
+    const Hdr h = *s.h;
+    for (uint32_t k = threadIdx.x; k < h.nbins / 2; k += kBlk)
+        reinterpret_cast<uint32_t*>(lut)[k] = reinterpret_cast<const uint32_t*>(s.lut)[k];
+    __syncthreads();
+    for (int64_t i0 = beg; i0 < end; i0 += kCap) {
+        int32_t a[kPer];
+        uint16_t b[kPer];
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int64_t i = i0 + q * kBlk + threadIdx.x;
+            a[q] = X.a[i < end ? i : beg];
+        }
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) b[q] = lut[bin_of(a[q], h)];
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int64_t i = i0 + q * kBlk + threadIdx.x;
+            if (i < end) {
+                s.id[side][i] = b[q];
+                atomicAdd(&cnt[b[q]], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    uint32_t* tot = s.zero + side * s.B;
+    for (int b = threadIdx.x; b < s.B; b += kBlk)
+        if (cnt[b]) atomicAdd(&tot[b], cnt[b]);
+    // Device-scope atomics act on memory beyond the XCD's L2, so a wave's additions are in place
+    // once it has waited for them; a release fence would also write back the whole L2 (16 waves
+    // of 512 workgroups doing that took 50 of the kernel's 70 us at 1M rows a side).
+    drain();
+    __syncthreads();
+    uint32_t* counters = s.zero + 3 * s.B;
+    if (threadIdx.x == 0) last = arrive_last(counters + kCntHist, blockIdx.x, gridDim.x);
+    __syncthreads();
+    if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    for (int x = 0; x < 2; ++x)
+        bucket_starts(s.zero + x * s.B, s.base + x * (s.B + 1), s.cur + x * s.B, s.B, (uint32_t)x, s.extra,
+                      &counters[kCntExtra], wsum);
+}
+
+// --------------------------------------------------------------------------------- scatter --
+// One tile of kCap rows: counted by bucket, given a place in every bucket by one atomic per
+// bucket and tile, sorted by bucket in LDS and written in runs.  Rows of one bucket travel as one
+// 16-byte (8-byte) record, so a run of two rows still fills a 32-byte sector.
+// LDS: cnt[B] | dlt[B] | a[kCap] | rid[kCap] | [c[kCap]] | bucket[kCap] (16 bits)
+template <bool HAS_C>
+__global__ __launch_bounds__(kBlk) void scatter_rows_k(Sides s)
+{
+    extern __shared__ __align__(16) uint32_t lds[];
+    __shared__ uint32_t wsum[kBlk / kWave + 1];
+    uint32_t* cnt = lds;
+    uint32_t* dlt = cnt + s.B;
+    int32_t* ta = reinterpret_cast<int32_t*>(dlt + s.B);
+    int32_t* tr = ta + kCap;
+    int32_t* tc = tr + kCap;
+    uint16_t* tb = reinterpret_cast<uint16_t*>(HAS_C ? tc + kCap : tc);
+    const int tid = threadIdx.x;
+    const int side = blockIdx.x >= s.split;
+    const Cols X = s.X[side];
+    const int64_t beg = (int64_t)(blockIdx.x - (side ? s.split : 0)) * kCap;
+    const int n = (int)(X.n - beg < kCap ? X.n - beg : kCap);
+    for (int b = tid; b < s.B; b += kBlk) cnt[b] = 0;
+    int32_t a[kPer], c[kPer], r[kPer];
+    uint32_t b[kPer], rank[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int e = q * kBlk + tid;
+        const int64_t i = beg + (e < n ? e : 0);
+        a[q] = X.a[i];
+        if (HAS_C) c[q] = X.c[i];
+        r[q] = X.rid ? X.rid[i] : (int32_t)i;
+        b[q] = s.id[side][i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+        if (q * kBlk + tid < n) rank[q] = atomicAdd(&cnt[b[q]], 1u);
+    __syncthreads();
+    uint32_t* cur = s.cur + side * s.B;
+    uint32_t carry = 0;
+    for (int b0 = 0; b0 < s.B; b0 += kBlk) {
+        const int k = b0 + tid;
+        const uint32_t m = k < s.B ? cnt[k] : 0u;
+        const uint32_t g = m ? atomicAdd(&cur[k], m) : 0u;
+        uint32_t sum;
+        const uint32_t at = carry + block_excl_scan<kBlk>(m, wsum, &sum);
+        if (k < s.B) {
+            cnt[k] = at;
+            dlt[k] = g - at;
+        }
+        carry += sum;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+        if (q * kBlk + tid < n) {
+            const uint32_t p = cnt[b[q]] + rank[q];
+            ta[p] = a[q];
+            tr[p] = r[q];
+            if (HAS_C) tc[p] = c[q];
+            tb[p] = (uint16_t)b[q];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int p = q * kBlk + tid;
+        if (p < n) {
+            const uint32_t at = dlt[tb[p]] + (uint32_t)p;
+            if (HAS_C) static_cast<int4*>(s.part[side])[at] = make_int4(ta[p], tc[p], tr[p], 0);
+            else static_cast<int2*>(s.part[side])[at] = make_int2(ta[p], tr[p]);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------ sort --
+struct Row {
+    int32_t a, c, r;
+};
+
+template <bool HAS_C>
+__device__ __forceinline__ Row part_row(const void* part, uint32_t i)
+{
+    if (HAS_C) {
+        const int4 v = static_cast<const int4*>(part)[i];
+        return Row{v.x, v.y, v.z};
+    }
+    const int2 v = static_cast<const int2*>(part)[i];
+    return Row{v.x, 0, v.y};
+}
+
+// A bucket of more than kCap rows, its chunks of kCap rows sorted: merged pairwise by one
+// workgroup, back and forth between the sorted columns and the bucketed rows (which nothing
+// reads any more).  Each thread makes kSortPer consecutive rows of a merged run; where they start in
+// its two halves is the usual binary search along the diagonal.
+template <bool HAS_C>
+__device__ void merge_chunks(const Sides& s, int side, uint32_t b0, uint32_t n)
+{
+    int32_t *oa = s.oa[side], *oc = s.oc[side], *orr = s.orid[side];
+    void* part = s.part[side];
+    // one value in every chunk (a value frequent enough to fill its own bucket): nothing to merge
+    __shared__ uint32_t mixed;
+    if (threadIdx.x == 0) mixed = 0;
+    __syncthreads();
+    for (uint64_t i = (uint64_t)threadIdx.x * kCap; i < n; i += (uint64_t)kSortBlk * kCap)
+        if (oa[b0 + i] != oa[b0] || oa[b0 + min(i + kCap, (uint64_t)n) - 1] != oa[b0]) mixed = 1;
+    __syncthreads();
+    if (!mixed) return;
+    bool cols = true;  // the rows are in the columns
+    auto key = [&](uint32_t i) { return cols ? oa[b0 + i] : part_row<HAS_C>(part, b0 + i).a; };
+    auto row = [&](uint32_t i) {
+        if (cols) return Row{oa[b0 + i], HAS_C ? oc[b0 + i] : 0, orr[b0 + i]};
+        return part_row<HAS_C>(part, b0 + i);
+    };
+    auto put = [&](uint32_t i, const Row& v) {
+        if (cols) {
+            if (HAS_C) static_cast<int4*>(part)[b0 + i] = make_int4(v.a, v.c, v.r, 0);
+            else static_cast<int2*>(part)[b0 + i] = make_int2(v.a, v.r);
+        } else {
+            oa[b0 + i] = v.a;
+            if (HAS_C) oc[b0 + i] = v.c;
+            orr[b0 + i] = v.r;
+        }
+    };
+    for (uint64_t w = kCap; w < n || !cols; w *= 2) {  // at the end the rows are in the columns
+        for (uint64_t o = (uint64_t)threadIdx.x * kSortPer; o < n; o += (uint64_t)kSortBlk * kSortPer) {
+            const uint32_t x0 = (uint32_t)(o / (2 * w) * (2 * w));  // run [x0, y0) with [y0, y1)
+            const uint32_t y0 = (uint32_t)(x0 + w < n ? x0 + w : n);
+            const uint32_t y1 = (uint32_t)(x0 + 2 * w < n ? x0 + 2 * w : n);
+            const uint32_t d = (uint32_t)o - x0;
+            uint32_t lo = d > y1 - y0 ? d - (y1 - y0) : 0u, hi = min(d, y0 - x0);
+            while (lo < hi) {  // rows of the first half among the run's first d
+                const uint32_t m = (lo + hi) / 2;
+                if (key(x0 + m) <= key(y0 + d - 1 - m)) lo = m + 1;
+                else hi = m;
+            }
+            uint32_t x = x0 + lo, y = y0 + d - lo;
+            for (int q = 0; q < kSortPer && o + q < y1; ++q) {
+                const bool first = y >= y1 || (x < y0 && key(x) <= key(y));
+                put((uint32_t)o + q, row(first ? x : y));
+                if (first) ++x;
+                else ++y;
+            }
+        }
+        cols = !cols;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+}
+
+// Ranks of a chunk's n rows by (a, position) from a bitonic network over LDS, 78 steps for kCap
+// rows whatever their values.  key: kCap words of 8 bytes.
+__device__ void bitonic_ranks(const Row (&v)[kSortPer], uint32_t n, uint64_t* key, uint32_t (&rank)[kSortPer])
+{
+    const uint32_t tid = threadIdx.x;
+    const uint32_t N = n <= 1 ? 1u : 1u << (32 - __builtin_clz(n - 1));
+#pragma unroll
+    for (int q = 0; q < kSortPer; ++q) {
+        const uint32_t e = (uint32_t)(q * kSortBlk) + tid;
+        if (e < N) key[e] = e < n ? (uint64_t)((uint32_t)v[q].a ^ 0x80000000u) << 32 | e : ~0ull;
+    }
+    for (uint32_t k = 2; k <= N; k *= 2)
+        for (uint32_t j = k / 2; j > 0; j /= 2) {
+            __syncthreads();
+            for (uint32_t i = tid; i < N / 2; i += kSortBlk) {
+                const uint32_t x = 2 * j * (i / j) + i % j, y = x + j;
+                const uint64_t kx = key[x], ky = key[y];
+                if ((kx > ky) == ((x & k) == 0)) {
+                    key[x] = ky;
+                    key[y] = kx;
+                }
+            }
+        }
+    __syncthreads();
+    uint32_t e[kSortPer];
+#pragma unroll
+    for (int q = 0; q < kSortPer; ++q) e[q] = q * kSortBlk + tid < n ? (uint32_t)key[q * kSortBlk + tid] : 0u;
+    __syncthreads();
+    uint32_t* at = reinterpret_cast<uint32_t*>(key);
+#pragma unroll
+    for (int q = 0; q < kSortPer; ++q)
+        if (q * kSortBlk + tid < n) at[e[q]] = (uint32_t)(q * kSortBlk) + tid;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSortPer; ++q)
+        if (q * kSortBlk + tid < n) rank[q] = at[q * kSortBlk + tid];
+    __syncthreads();
+}
+
+// One chunk of up to kCap rows of one bucket per workgroup, sorted by a: counted into kSub value
+// bins of the chunk's own range (about one row each), placed by bin, and each row of S ranked
+// against the rows of its bin (nothing to do when a bin holds one value; when some bin holds more
+// than kRankBin rows, a frequent value among others, the chunk goes through a bitonic network
+// instead, since ranking takes the square of that number).  R stays in the order
+// of the bins: its rows only have to lie near each other.  direct: the input columns, one
+// workgroup per side; else workgroup i < 2B takes bucket i's first chunk, the others the list of
+// further chunks.
+// LDS: bins[kSub + 1] | one column of kCap rows, which stages a, then rid and c, into sorted order
+template <bool HAS_C>
+__global__ __launch_bounds__(kSortBlk) void sort_k(Sides s, int direct)
+{
+    extern __shared__ __align__(16) uint32_t lds[];
+    __shared__ int32_t red[2 * kSortBlk / kWave];
+    __shared__ uint32_t wsum[kSortBlk / kWave + 1];
+    __shared__ uint32_t last, crowded;
+    if (threadIdx.x == 0) crowded = 0;
+    uint32_t* bin = lds;
+    int32_t* ta = reinterpret_cast<int32_t*>(bin + kSub + 1);
+    const int tid = threadIdx.x;
+    int side;
+    uint32_t b0, at, n, total;  // the bucket's first row, the chunk's first row and rows, the bucket's rows
+    int bucket = 0;
+    if (direct) {
+        side = blockIdx.x;
+        b0 = at = 0;
+        n = total = (uint32_t)s.X[side].n;
+        if (side == 0)
+            for (int i = tid; i < kCounters; i += kSortBlk) s.zero[3 * s.B + i] = 0;
+    } else {
+        uint32_t chunk = 0;
+        if (blockIdx.x < 2 * (uint32_t)s.B) {
+            side = blockIdx.x >= (uint32_t)s.B;
+            bucket = (int)blockIdx.x - side * s.B;
+        } else {
+            const uint32_t x = blockIdx.x - 2 * (uint32_t)s.B;
+            if (x >= s.zero[3 * s.B + kCntExtra]) return;
+            const uint2 e = s.extra[x];
+            side = (int)(e.x >> 31);
+            bucket = (int)(e.x & 0x7FFFFFFFu);
+            chunk = e.y;
+        }
+        const uint32_t* base = s.base + side * (s.B + 1);
+        b0 = base[bucket];
+        total = base[bucket + 1] - b0;
+        at = b0 + chunk * kCap;
+        n = min((uint32_t)kCap, total - chunk * kCap);
+        if (total == 0) return;
+    }
+    Row v[kSortPer];
+    uint32_t sub[kSortPer], rank[kSortPer];
+    int32_t lo = INT32_MAX, hi = INT32_MIN;
+#pragma unroll
+    for (int q = 0; q < kSortPer; ++q) {
+        const uint32_t e = (uint32_t)(q * kSortBlk + tid);
+        const uint32_t i = at + (e < n ? e : 0u);
+        if (direct) {
+            const Cols& X = s.X[side];
+            v[q] = Row{X.a[i], HAS_C ? X.c[i] : 0, X.rid ? X.rid[i] : (int32_t)i};
+        } else {
+            v[q] = part_row<HAS_C>(s.part[side], i);
+        }
+    }
+    for (int i = tid; i <= kSub; i += kSortBlk) bin[i] = 0;
+#pragma unroll
+    for (int q = 0; q < kSortPer; ++q) {
+        lo = min(lo, v[q].a);
+        hi = max(hi, v[q].a);
+    }
+    block_range<kSortBlk>(lo, hi, red);
+    const uint32_t sh = span_shift((uint32_t)hi - (uint32_t)lo, kSubBits);
+#pragma unroll
+    for (int q = 0; q < kSortPer; ++q) {
+        sub[q] = ((uint32_t)v[q].a - (uint32_t)lo) >> sh;
+        if ((uint32_t)(q * kSortBlk + tid) < n) rank[q] = atomicAdd(&bin[sub[q]], 1u);
+    }
+    __syncthreads();
+    {
+        constexpr int S = kSub / kSortBlk;
+        uint32_t x[S], sum = 0, tot;
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+            x[k] = bin[tid * S + k];
+            sum += x[k];
+            if (x[k] > kRankBin) crowded = 1;
+        }
+        uint32_t run = block_excl_scan<kSortBlk>(sum, wsum, &tot);
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+            bin[tid * S + k] = run;
+            run += x[k];
+        }
+        if (tid == 0) bin[kSub] = n;
+    }
+    __syncthreads();
+    const bool exact = sh && side == 1;  // uniform: a bin spans several values, and S needs them in order
+    if (exact && crowded) {
+        bitonic_ranks(v, n, reinterpret_cast<uint64_t*>(lds), rank);
+    } else {
+#pragma unroll
+        for (int q = 0; q < kSortPer; ++q)
+            if ((uint32_t)(q * kSortBlk + tid) < n) {
+                rank[q] += bin[sub[q]];
+                if (exact) ta[rank[q]] = v[q].a;
+            }
+        __syncthreads();
+        if (exact) {
+#pragma unroll
+            for (int q = 0; q < kSortPer; ++q)
+                if ((uint32_t)(q * kSortBlk + tid) < n) {
+                    const uint32_t p0 = bin[sub[q]], p1 = bin[sub[q] + 1], mine = rank[q];
+                    uint32_t less = 0;
+                    for (uint32_t p = p0; p < p1; ++p)
+                        less += ta[p] < v[q].a || (ta[p] == v[q].a && p < mine) ? 1u : 0u;
+                    rank[q] = p0 + less;
+                }
+            __syncthreads();
+        }
+    }
+    auto store = [&](auto col, int32_t* out) {
+#pragma unroll
+        for (int q = 0; q < kSortPer; ++q)
+            if ((uint32_t)(q * kSortBlk + tid) < n) ta[rank[q]] = col(v[q]);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kSortPer; ++q) {
+            const uint32_t p = (uint32_t)(q * kSortBlk + tid);
+            if (p < n) out[at + p] = ta[p];
+        }
+        __syncthreads();
+    };
+    store([](const Row& x) { return x.a; }, s.oa[side]);
+    store([](const Row& x) { return x.r; }, s.orid[side]);
+    if (HAS_C) store([](const Row& x) { return x.c; }, s.oc[side]);
+    if (total <= (uint32_t)kCap || side == 0) return;  // R's chunks stay as they are
+    // the last of the bucket's chunks to finish merges them
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (tid == 0)
+        last = atomicAdd(&s.zero[2 * s.B + bucket], 1u) == (total - 1) / kCap;
+    __syncthreads();
+    if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    merge_chunks<HAS_C>(s, side, b0, total);
+}
+
+// ------------------------------------------------------------------------- count and write --
+struct Join {
+    const int32_t *Ra, *Rc, *Rr, *Sa, *Sc, *Sr;  // sorted columns
+    uint32_t nR, nS;
+    int op_a;
+    int64_t w;
+    uint32_t rows;  // R rows per unit (a multiple of kJoinBlk)
+    uint32_t U;     // units
+    int Y;          // S tiles: unit u = R block u / Y, tile u % Y
+    int direct;     // S is one bucket
+    const Hdr* h;
+    const uint16_t* lut;
+    const uint32_t* baseS;
+    uint32_t *lo, *hi;   // each R row's interval
+    uint64_t* counts;    // [U] counts, then offsets
+    uint64_t* wave_off;  // [U][kJoinWaves] each wave's start inside its unit's range
+    uint32_t* done;
+    uint64_t* stamp_at;
+    uint64_t stamp;
+    uint64_t* dbg;
+};
+
+// The first position in sorted S whose value is >= x (UP: > x), x the same in the whole wave.
+// Buckets rise with the value, so it lies in x's bucket; there 64 probes at a time cut the range
+// by 64 (two dependent loads for 2048 rows, a binary search takes eleven).
+template <bool UP>
+__device__ __forceinline__ uint32_t wave_bound(const Join& g, const Hdr& h, int32_t x)
+{
+    uint32_t lo = 0, hi = g.nS;
+    if (!g.direct) {
+        const uint32_t b = uniform((uint32_t)g.lut[bin_of(x, h)]);
+        lo = uniform(g.baseS[b]);
+        hi = uniform(g.baseS[b + 1]);
+    }
+    while (lo < hi) {
+        const uint32_t step = (hi - lo + kWave - 1) / kWave;
+        const uint32_t at = lo + (lane_id() + 1) * step - 1;  // the last row of this lane's part
+        const int32_t v = g.Sa[at < hi ? at : hi - 1];
+        const uint32_t k = (uint32_t)__builtin_popcountll(ballot(at < hi && (UP ? v <= x : v < x)));
+        lo += k * step;
+        if (step == 1) return lo;
+        // the bound lies in part k, or behind the last whole part
+        hi = lo + step - 1 < hi ? lo + step - 1 : hi;
+    }
+    return lo;
+}
+
+constexpr uint32_t kWin = 512;  // S values a wave stages for the bounds of its 64 rows
+
+// The first position >= x (UP: > x) of sorted v[0, n), from `first` on.
+template <bool UP, typename P>
+__device__ __forceinline__ uint32_t lane_bound(P v, uint32_t first, uint32_t n, int32_t x)
+{
+    uint32_t lo = first, hi = first + n;
+    while (lo < hi) {
+        const uint32_t m = lo + (hi - lo) / 2;
+        const int32_t a = v[m];
+        if (UP ? a <= x : a < x) lo = m + 1;
+        else hi = m;
+    }
+    return lo;
+}
+
+// The S rows that satisfy op_a with this lane's value a: [lo, hi), or for != everything outside
+// it; by the whole wave.  The bounds of neighbouring rows lie close together: the rows of S
+// between the wave's smallest and largest one are staged in LDS (win, kWin values of the wave)
+// and searched there; too many of them are searched where they are.
+__device__ __forceinline__ void interval(const Join& g, const Hdr& h, int32_t a, bool valid, int32_t* win,
+                                         uint32_t& lo, uint32_t& hi)
+{
+    const int64_t w = g.w;  // 0 but for BAND
+    const int32_t x0 = (int32_t)max((int64_t)a - w, (int64_t)INT32_MIN);
+    const int32_t x1 = (int32_t)min((int64_t)a + w, (int64_t)INT32_MAX);
+    const uint32_t w0 = wave_bound<false>(g, h, uniform(wave_min_i(valid ? x0 : INT32_MAX)));
+    const uint32_t w1 = wave_bound<true>(g, h, uniform(wave_max_i(valid ? x1 : INT32_MIN)));
+    const uint32_t n = w1 > w0 ? w1 - w0 : 0u;
+    const bool need_lo = g.op_a != JOIN_OP_GT && g.op_a != JOIN_OP_GE;
+    const bool need_hi = g.op_a != JOIN_OP_LT && g.op_a != JOIN_OP_LE;
+    const bool up_lo = g.op_a == JOIN_OP_LT, up_hi = g.op_a != JOIN_OP_GT;
+    auto bounds = [&](auto v, uint32_t first) {
+        lo = 0;
+        hi = g.nS;
+        if (need_lo) lo = w0 - first + (up_lo ? lane_bound<true>(v, first, n, x0) : lane_bound<false>(v, first, n, x0));
+        if (need_hi) hi = w0 - first + (up_hi ? lane_bound<true>(v, first, n, x1) : lane_bound<false>(v, first, n, x1));
+    };
+    if (n <= kWin) {  // uniform
+        for (uint32_t k = lane_id(); k < n; k += kWave) win[k] = g.Sa[w0 + k];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        bounds((const int32_t*)win, 0u);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+        bounds(g.Sa, w0);
+    }
+}
+
+template <int OP>
+__device__ __forceinline__ bool holds_c(int32_t r, int32_t s)
+{
+    if constexpr (OP == JOIN_OP_EQ) return r == s;
+    if constexpr (OP == JOIN_OP_NE) return r != s;
+    if constexpr (OP == JOIN_OP_LT) return r < s;
+    if constexpr (OP == JOIN_OP_LE) return r <= s;
+    if constexpr (OP == JOIN_OP_GT) return r > s;
+    if constexpr (OP == JOIN_OP_GE) return r >= s;
+    return true;
+}
+
+__device__ __forceinline__ uint32_t wave_min_u(uint32_t v)
+{
+    for (int o = kWave / 2; o > 0; o >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, o));
+    return uniform(v);
+}
+
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t v)
+{
+    for (int o = kWave / 2; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o));
+    return uniform(v);
+}
+
+// Matches of this lane's R row among the S rows [l, h) (l == h: none), by the whole wave.  Long
+// intervals: the wave walks the union of its rows' intervals one S row at a time, the S value in
+// a scalar register; where every interval of the wave covers the S row nothing but c is compared.
+template <int OPC>
+__device__ __forceinline__ uint64_t count_in(const Join& g, int32_t xc, uint32_t l, uint32_t h)
+{
+    if constexpr (OPC == JOIN_OP_NONE) return h - l;
+    const uint32_t len = h - l;
+    const uint32_t longest = wave_max_u(len);
+    if (longest == 0) return 0;
+    uint32_t n = 0;  // an interval holds fewer than 2^32 rows
+    if (longest <= kSerial) {
+        constexpr uint32_t G = 4;
+        for (uint32_t i = 0; i < longest; i += G) {
+            int32_t sc[G];
+#pragma unroll
+            for (uint32_t k = 0; k < G; ++k) sc[k] = g.Sc[i + k < len ? l + i + k : 0u];
+#pragma unroll
+            for (uint32_t k = 0; k < G; ++k) n += i + k < len && holds_c<OPC>(xc, sc[k]) ? 1u : 0u;
+        }
+        return n;
+    }
+    const cptr<int32_t> Sc = as_const(g.Sc);
+    const uint32_t j0 = wave_min_u(len ? l : ~0u), j1 = wave_max_u(len ? h : 0u);
+    uint32_t i0 = wave_max_u(len ? l : 0u), i1 = wave_min_u(len ? h : ~0u);
+    if (i1 < i0) i0 = i1 = j1;  // no S row is in every interval
+    auto checked = [&](uint32_t a, uint32_t b) {
+        for (uint32_t j = a; j < b; ++j) n += j >= l && j < h && holds_c<OPC>(xc, Sc[j]) ? 1u : 0u;
+    };
+    checked(j0, i0);
+    constexpr uint32_t G = 8;
+    uint32_t j = i0, m = 0;
+    for (; j + G <= i1; j += G) {
+        int32_t sc[G];
+#pragma unroll
+        for (uint32_t k = 0; k < G; ++k) sc[k] = Sc[j + k];
+#pragma unroll
+        for (uint32_t k = 0; k < G; ++k) m += holds_c<OPC>(xc, sc[k]) ? 1u : 0u;
+    }
+    if (len) n += m;
+    checked(j, j1);
+    return n;
+}
+
+// The pairs of this lane's R row (row id rr) with the S rows [l, h) from slot `at` on; the wave's
+// pairs follow each other, and `at` moves past them.  part / parts: this workgroup's share of
+// long intervals without a condition on c.
+template <int OPC>
+__device__ __forceinline__ void write_in(const Join& g, int32_t xc, int32_t rr, uint32_t l, uint32_t h,
+                                         uint64_t& at, int2* __restrict__ out, uint32_t part, uint32_t parts)
+{
+    const uint32_t len = h - l;
+    const uint32_t longest = wave_max_u(len);
+    if (longest == 0) return;
+    auto emit = [&](bool match, int32_t srid) {
+        const uint64_t m = ballot(match);
+        if (match) out[at + mask_rank(m)] = make_int2(rr, srid);
+        at += (uint64_t)__builtin_popcountll(m);
+    };
+    if (longest <= kSerial) {
+        if (OPC == JOIN_OP_NONE && part) {  // uniform: the first workgroup writes short intervals
+            at += wave_sum64(len);
+            return;
+        }
+        for (uint32_t i = 0; i < longest; ++i) {
+            const bool in = i < len;
+            const uint32_t j = in ? l + i : 0u;
+            emit(in && (OPC == JOIN_OP_NONE || holds_c<OPC>(xc, g.Sc[j])), g.Sr[j]);
+        }
         return;
     }
-    auto rs = [&](int b) { return b < B ? offR[(int64_t)b * nChR] : nR; };
-    auto ss = [&](int b) { return b < B ? offS[(int64_t)b * nChS] : nS; };
-    BucketInfo bi{};
-    bi.rStart = rs(i);
-    bi.nR = rs(i + 1) - bi.rStart;
-    const int64_t lo_i = vlo[i], hi_i = vhi[i];
-    auto cls = [&](int j) -> int {
-        if (ss(j + 1) == ss(j)) return -1;  // an empty S bucket: any class
-        int c = region_class(op, w, lo_i, hi_i, vlo[j], vhi[j]);
-        if (c == kGreen && has_c) c = kRed;  // a condition on c must still be checked
-        return c;
+    if constexpr (OPC == JOIN_OP_NONE) {
+        // row by row, each by the whole wave
+        for (int q = 0; q < kWave; ++q) {
+            const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)len, q);
+            const uint32_t s0 = (uint32_t)__builtin_amdgcn_readlane((int)l, q);
+            const int32_t r = __builtin_amdgcn_readlane(rr, q);
+            const uint32_t k1 = (uint32_t)((uint64_t)n * (part + 1) / parts);
+            for (uint32_t k = (uint32_t)((uint64_t)n * part / parts) + lane_id(); k < k1; k += kWave)
+                out[at + k] = make_int2(r, g.Sr[s0 + k]);
+            at += n;
+        }
+    } else {
+        const cptr<int32_t> Sc = as_const(g.Sc);
+        const cptr<int32_t> Sr = as_const(g.Sr);
+        const uint32_t j0 = wave_min_u(len ? l : ~0u), j1 = wave_max_u(len ? h : 0u);
+        for (uint32_t j = j0; j < j1; ++j) emit(j >= l && j < h && holds_c<OPC>(xc, Sc[j]), Sr[j]);
+    }
+}
+
+// Unit u: R rows [r0, r1) and S rows [t0, t1).
+__device__ __forceinline__ void unit_of(const Join& g, uint32_t u, uint32_t& r0, uint32_t& r1, uint32_t& t0,
+                                        uint32_t& t1)
+{
+    const uint32_t rb = u / (uint32_t)g.Y, y = u - rb * (uint32_t)g.Y;
+    r0 = rb * g.rows;
+    r1 = g.nR - r0 < g.rows ? g.nR : r0 + g.rows;
+    t0 = (uint32_t)((uint64_t)g.nS * y / (uint32_t)g.Y);
+    t1 = (uint32_t)((uint64_t)g.nS * (y + 1) / (uint32_t)g.Y);
+}
+
+// Both intervals of a row inside the tile [t0, t1): f(first, last + 1).  != has the rows before
+// and after its equal run, every other operator one interval.
+template <typename F>
+__device__ __forceinline__ void each_interval(const Join& g, uint32_t lo, uint32_t hi, uint32_t t0,
+                                              uint32_t t1, bool valid, F f)
+{
+    auto clip = [&](uint32_t a, uint32_t b) {
+        const uint32_t l = max(a, t0), h = min(b, t1);
+        const bool some = valid && l < h;
+        f(some ? l : 0u, some ? h : 0u);
     };
-    int jr0 = B, jr1 = 0, jg0 = B, jg1 = 0;
-    if (bi.nR > 0) {
-        for (int j = lane; j < B; j += kWave) {
-            const int c = cls(j);
-            if (c == kRed) {
-                jr0 = min(jr0, j);
-                jr1 = max(jr1, j + 1);
-            } else if (c == kGreen) {
-                jg0 = min(jg0, j);
-                jg1 = max(jg1, j + 1);
-            }
-        }
-        jr0 = wave_min_i(jr0);
-        jr1 = wave_max_i(jr1);
-        jg0 = wave_min_i(jg0);
-        jg1 = wave_max_i(jg1);
-    }
-    // Spans of S buckets: red [jr0, jr1), green [gl, jr0) and [jr1, gr); every bucket outside
-    // them is white or empty.  Empty buckets may join any span.
-    if (jr0 >= jr1) jr0 = jr1 = 0;
-    int gl = jr0, gr = jr1;
-    if (jg0 < jg1) {
-        if (jr0 == jr1) {
-            int white = 0;  // no red region: the greens must form one run without whites
-            for (int j = jg0 + lane; j < jg1; j += kWave) white |= cls(j) == kWhite;
-            if (!wave_max_i(white)) {
-                jr0 = jr1 = gl = jg0;
-                gr = jg1;
-            } else {
-                jr0 = gl = jg0;
-                jr1 = gr = jg1;
-            }
-        } else {
-            // greens reach from the red span to the nearest white on each side (no red lies
-            // outside [jr0, jr1))
-            int lw = -1, fw = B;
-            for (int j = lane; j < jr0; j += kWave)
-                if (cls(j) == kWhite) lw = max(lw, j);
-            for (int j = jr1 + lane; j < B; j += kWave)
-                if (cls(j) == kWhite) fw = min(fw, j);
-            gl = wave_max_i(lw) + 1;
-            gr = wave_min_i(fw);
-            if (jg0 < gl || jg1 > gr) {  // greens cut off by whites: evaluate them as red
-                jr0 = gl = (jg0 < jr0 ? jg0 : jr0);
-                jr1 = gr = (jg1 > jr1 ? jg1 : jr1);
-            }
-        }
-    }
-    if (lane != 0) return;
-    bi.red0 = ss(jr0);
-    bi.red1 = jr1 > jr0 ? ss(jr1) : bi.red0;
-    if (split && jr1 > jr0) {
-        // band: a left neighbour of the R bucket contributes only its high rows, a right one only
-        // its low rows (bsplit_k); not next to a green span, which must stay adjacent
-        if (gl == jr0 && jr0 < i) bi.red0 = split[2 * jr0 + 1];
-        if (gr == jr1 && jr1 - 1 > i) bi.red1 = split[2 * (jr1 - 1)];
-        if (bi.red1 < bi.red0) bi.red1 = bi.red0;
-    }
-    bi.gl0 = ss(gl);
-    bi.gl1 = jr0 > gl ? ss(jr0) : bi.gl0;
-    bi.gr0 = ss(jr1);
-    bi.gr1 = gr > jr1 ? ss(gr) : bi.gr0;
-    const uint32_t span = bi.red1 - bi.red0;
-    uint32_t tiles = 0, ts = 0;
-    if (span > 0 && bi.nR > 0) {
-        tiles = (span + kTileRows - 1) / kTileRows;
-        if (tiles > (uint32_t)kMaxTiles) tiles = kMaxTiles;
-        ts = (span + tiles - 1) / tiles;
-    }
-    bi.tiles = tiles;
-    bi.ts = ts;
-    info[i] = bi;
-    const uint32_t blocks = (bi.nR + kRBlockRows - 1) / kRBlockRows;
-    units[i] = blocks * tiles;
-    green[2 * i] = (uint64_t)bi.nR * (bi.gl1 - bi.gl0);
-    green[2 * i + 1] = (uint64_t)bi.nR * (bi.gr1 - bi.gr0);
-}
-
-__global__ void expand_k(const BucketInfo* __restrict__ info, const uint32_t* __restrict__ ustart,
-                         int B, int64_t Umax, uint4* __restrict__ out)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B) return;
-    const BucketInfo bi = info[i];
-    const uint32_t u0 = ustart[i], u1 = ustart[i + 1];
-    for (uint32_t u = u0; u < u1 && (int64_t)u < Umax; ++u) {
-        const uint32_t k = u - u0;
-        const uint32_t b = k / bi.tiles, t = k - b * bi.tiles;
-        const uint32_t r0 = bi.rStart + b * kRBlockRows;
-        const uint32_t rEnd = r0 + kRBlockRows < bi.rStart + bi.nR ? r0 + kRBlockRows : bi.rStart + bi.nR;
-        const uint32_t s0 = bi.red0 + t * bi.ts;
-        const uint32_t s1 = s0 + bi.ts < bi.red1 ? s0 + bi.ts : bi.red1;
-        out[u] = make_uint4(r0, rEnd, s0, s1);
+    if (g.op_a == JOIN_OP_NE) {
+        clip(0, lo);
+        clip(hi, g.nS);
+    } else {
+        clip(lo, hi);
     }
 }
 
-__global__ void fill_u64_k(uint64_t* p, int64_t n, uint64_t v)
+// Count pass, and by the last workgroup to finish the exclusive scan of the units' counts, the
+// total of which goes to *total and to the host's pinned word.
+template <int OPC>
+__global__ __launch_bounds__(kJoinBlk) void region_count_k(Join g, uint64_t* __restrict__ total, uint64_t* pub)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
+    __shared__ uint64_t wsum[kJoinWaves];
+    __shared__ int32_t win[kJoinWaves][kWin];
+    __shared__ uint32_t last;
+    const int wv = uniform((int32_t)(threadIdx.x / kWave));
+    const uint32_t u = blockIdx.x;
+    if (u == 0 && threadIdx.x == 0) *g.stamp_at = g.stamp;  // for the write pass
+    uint32_t r0, r1, t0, t1;
+    unit_of(g, u, r0, r1, t0, t1);
+    Hdr h{};
+    if (!g.direct) h = *g.h;
+    uint64_t n = 0;
+    for (uint32_t i0 = r0; i0 < r1; i0 += kJoinBlk) {
+        const uint32_t i = i0 + threadIdx.x;
+        const bool valid = i < r1;
+        uint32_t lo = 0, hi = 0;
+        interval(g, h, g.Ra[valid ? i : r1 - 1], valid, win[wv], lo, hi);
+        if (valid && t0 == 0) {
+            g.lo[i] = lo;
+            g.hi[i] = hi;
+        }
+        const int32_t xc = OPC != JOIN_OP_NONE && valid ? g.Rc[i] : 0;
+        each_interval(g, lo, hi, t0, t1, valid,
+                      [&](uint32_t a, uint32_t b) { n += count_in<OPC>(g, xc, a, b); });
+    }
+    const uint64_t wt = wave_sum64(n);
+    if (lane_id() == 0) wsum[wv] = wt;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t run = 0;
+        for (int w = 0; w < kJoinWaves; ++w) {
+            g.wave_off[(uint64_t)u * kJoinWaves + w] = run;
+            run += wsum[w];
+        }
+        // an atomic store reaches memory by itself: no fence that writes back the L2 per workgroup
+        __hip_atomic_store(&g.counts[u], run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        drain();
+        last = arrive_last(g.done, u, g.U);
+    }
+    __syncthreads();
+    if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    uint64_t carry = 0;
+    for (uint32_t b0 = 0; b0 < g.U; b0 += kJoinBlk * 8) {
+        uint64_t v[8], s = 0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t i = b0 + threadIdx.x * 8 + k;
+            v[k] = i < g.U ? g.counts[i] : 0;
+            s += v[k];
+        }
+        const uint64_t inc = wave_incl_scan64(s);
+        if (lane_id() == kWave - 1) wsum[wv] = inc;
+        __syncthreads();
+        uint64_t run = carry + inc - s;
+        for (int w = 0; w < kJoinWaves; ++w) {
+            run += w < wv ? wsum[w] : 0;
+            carry += wsum[w];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t i = b0 + threadIdx.x * 8 + k;
+            if (i < g.U) g.counts[i] = run;
+            run += v[k];
+        }
+    }
+    if (threadIdx.x == 0) {
+        *total = carry;
+        if (pub) publish_total(pub, carry);
+    }
 }
 
-// Green spans: item k = (R row r, side) writes |span| pairs (rid_R[r], rid_S[s]) at
-// green offset + (r - rStart) * |span| + (s - span start); one wave per item.
-__global__ __launch_bounds__(kCrossWaves * kWave) void cross_k(
-    const BucketInfo* __restrict__ info, int B, uint32_t nR, const int32_t* __restrict__ rrid,
-    const int32_t* __restrict__ srid, const uint64_t* __restrict__ goff,
-    const uint64_t* __restrict__ total, int2* __restrict__ out, uint64_t cap,
-    const uint64_t* __restrict__ stamp_at, uint64_t stamp)
+template <int OPC>
+__global__ __launch_bounds__(kJoinBlk) void region_write_k(Join g, const uint64_t* __restrict__ total,
+                                                           int2* __restrict__ out, uint64_t cap, uint32_t parts)
 {
-    (void)nR;
-    if (*total > cap || *stamp_at != stamp) return;  // see theta_write_k
-    const int lane = (int)lane_id();
-    const int wv = uniform((int32_t)(threadIdx.x >> 6));
-    // one workgroup per (R bucket, side) item; its waves take the bucket's rows in turn, and a
-    // row's pairs with the green span are written by the wave's lanes, consecutive in S
-    for (int64_t item = blockIdx.x; item < 2 * (int64_t)B; item += gridDim.x) {
-        const int i = (int)(item >> 1);
-        const int side = (int)(item & 1);
-        const BucketInfo bi = info[i];
-        const uint32_t g0 = side ? bi.gr0 : bi.gl0, g1 = side ? bi.gr1 : bi.gl1;
-        if (g1 <= g0 || bi.nR == 0) continue;
-        const uint64_t len = g1 - g0;
-        const uint64_t base0 = goff[2 * i + side];
-        for (uint32_t r = (uint32_t)wv; r < bi.nR; r += kCrossWaves) {
-            const int32_t rr = rrid[bi.rStart + r];
-            const uint64_t base = base0 + (uint64_t)r * len;
-            for (uint64_t s2 = lane; s2 < len; s2 += kWave)
-                if (base + s2 < cap) out[base + s2] = make_int2(rr, srid[g0 + s2]);
-        }
+    // an output too small for the exact count, or a plan other than the count pass's, receives
+    // nothing
+    if (*total > cap || *g.stamp_at != g.stamp) return;
+    const int wv = uniform((int32_t)(threadIdx.x / kWave));
+    const uint32_t u = blockIdx.x / parts, part = blockIdx.x - u * parts;
+    uint32_t r0, r1, t0, t1;
+    unit_of(g, u, r0, r1, t0, t1);
+    uint64_t at = uniform(g.counts[u] + g.wave_off[(uint64_t)u * kJoinWaves + wv]);
+#if JL_DEBUG
+    const uint64_t at0 = at;
+#endif
+    for (uint32_t i0 = r0; i0 < r1; i0 += kJoinBlk) {
+        const uint32_t i = i0 + threadIdx.x;
+        const bool valid = i < r1;
+        const uint32_t lo = valid ? g.lo[i] : 0u, hi = valid ? g.hi[i] : 0u;
+        const int32_t xc = OPC != JOIN_OP_NONE && valid ? g.Rc[i] : 0;
+        const int32_t rr = valid ? g.Rr[i] : 0;
+        each_interval(g, lo, hi, t0, t1, valid,
+                      [&](uint32_t a, uint32_t b) { write_in<OPC>(g, xc, rr, a, b, at, out, part, parts); });
+    }
+#if JL_DEBUG
+    if (g.dbg && part == 0 && lane_id() == 0 && at > at0)
+        atomicAdd(reinterpret_cast<unsigned long long*>(&g.dbg[u]), (unsigned long long)(at - at0));
+#endif
+}
+
+using CountFn = void (*)(Join, uint64_t*, uint64_t*);
+using WriteFn = void (*)(Join, const uint64_t*, int2*, uint64_t, uint32_t);
+
+CountFn count_fn(int opc)
+{
+    switch (opc) {
+    case JOIN_OP_NONE: return region_count_k<JOIN_OP_NONE>;
+    case JOIN_OP_EQ: return region_count_k<JOIN_OP_EQ>;
+    case JOIN_OP_NE: return region_count_k<JOIN_OP_NE>;
+    case JOIN_OP_LT: return region_count_k<JOIN_OP_LT>;
+    case JOIN_OP_LE: return region_count_k<JOIN_OP_LE>;
+    case JOIN_OP_GT: return region_count_k<JOIN_OP_GT>;
+    case JOIN_OP_GE: return region_count_k<JOIN_OP_GE>;
+    default: return nullptr;
+    }
+}
+
+WriteFn write_fn(int opc)
+{
+    switch (opc) {
+    case JOIN_OP_NONE: return region_write_k<JOIN_OP_NONE>;
+    case JOIN_OP_EQ: return region_write_k<JOIN_OP_EQ>;
+    case JOIN_OP_NE: return region_write_k<JOIN_OP_NE>;
+    case JOIN_OP_LT: return region_write_k<JOIN_OP_LT>;
+    case JOIN_OP_LE: return region_write_k<JOIN_OP_LE>;
+    case JOIN_OP_GT: return region_write_k<JOIN_OP_GT>;
+    case JOIN_OP_GE: return region_write_k<JOIN_OP_GE>;
+    default: return nullptr;
     }
 }
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
-int64_t chunk_for(int64_t n)
-{
-    int64_t c = ceil_div(n, 512);
-    c = ceil_div(c, kTile) * kTile;
-    return c < kTile ? kTile : c;
-}
+size_t scatter_lds(int B, bool has_c) { return (size_t)B * 8 + (size_t)kCap * (has_c ? 14 : 10); }
 
-size_t bscatter_lds(int B) { return (size_t)(2 * B + 1) * 4 + (size_t)kTile * 14; }
+constexpr size_t kSortLds = (size_t)(kSub + 1) * 4 + (size_t)kCap * 4;
 
 }  // namespace
 
-RegionPlan region_plan(int64_t nR, int64_t nS, int op_a, int64_t stash_k)
+RegionPlan region_plan(int64_t nR, int64_t nS, int op_a, int op_c, int num_cus, int64_t knob)
 {
     RegionPlan pl{};
-    int bits = 1;
-    const int64_t n = nR + nS;
-    while (bits < 12 && (n >> bits) > 1024) ++bits;
-    pl.bits = bits;
-    pl.B = 1 << bits;
-    pl.chR = chunk_for(nR);
-    pl.chS = chunk_for(nS);
-    pl.nChR = nR > 0 ? ceil_div(nR, pl.chR) : 0;
-    pl.nChS = nS > 0 ? ceil_div(nS, pl.chS) : 0;
-    pl.Umax = (int64_t)kMaxTiles * (ceil_div(nR, kRBlockRows) + pl.B);
-    const bool sel = op_a == JOIN_OP_BAND || op_a == JOIN_OP_EQ || op_a == JOIN_OP_NONE;
-#ifndef JL_REGION_STASH_MULT
-#define JL_REGION_STASH_MULT 2
-#endif
-    pl.K = sel && stash_k > 0 ? stash_k * JL_REGION_STASH_MULT : 0;
-    pl.nOff = pl.Umax + 2 * (int64_t)pl.B;
+    const int64_t n = nR > nS ? nR : nS;
+    const bool has_c = op_a == JOIN_OP_NONE || op_c != JOIN_OP_NONE;
+    pl.direct = n <= kCap;
+    while (!pl.direct && pl.bits < kMaxBits && (n >> pl.bits) > kMeanRows) ++pl.bits;
+    pl.B = 1 << pl.bits;
+    pl.binBits = pl.bits + 4 < kMinBinBits ? kMinBinBits : (pl.bits + 4 > kMaxBinBits ? kMaxBinBits : pl.bits + 4);
+    pl.samples = (int64_t)8 * pl.B < 4096 ? 4096 : ((int64_t)8 * pl.B > 32768 ? 32768 : (int64_t)8 * pl.B);
+    pl.rows = ceil_div(ceil_div(nR > 0 ? nR : 1, kMaxBlocks), kJoinBlk) * kJoinBlk;
+    const int64_t blocks = nR > 0 && nS > 0 ? ceil_div(nR, pl.rows) : 0;
+    // A condition on c inside intervals of a large share of S is the one thing that costs more
+    // than the sort: it is cut into S tiles until there are waves for every SIMD.
+    const bool wide = op_a != JOIN_OP_EQ && op_a != JOIN_OP_BAND;
+    pl.Y = 1;
+    if (has_c && wide)
+        while (pl.Y < 64 && blocks * pl.Y < (int64_t)num_cus * 8 && nS / (2 * pl.Y) >= 256) pl.Y *= 2;
+    pl.U = blocks * pl.Y;
     size_t off = 256;
     auto take = [&](size_t bytes) {
         const size_t o = off;
         off = align_up(off + bytes);
         return o;
     };
-    pl.off_hist2 = take((size_t)2 * kBins * 4);
-    pl.off_lut = take((size_t)kBins * 2);
-    pl.off_vlo = take((size_t)pl.B * 8);
-    pl.off_vhi = take((size_t)pl.B * 8);
-    pl.off_hR = take((size_t)pl.B * pl.nChR * 4);
-    pl.off_hS = take((size_t)pl.B * pl.nChS * 4);
+    pl.zero_words = (size_t)3 * pl.B + kCounters;
+    pl.off_zero = take(pl.zero_words * 4);
+    pl.off_base = take((size_t)2 * (pl.B + 1) * 4);
+    pl.off_cur = take((size_t)2 * pl.B * 4);
+    pl.off_extra = take(pl.direct ? 0 : (size_t)(nR / kCap + nS / kCap + 2) * 8);
+    pl.off_lut = take(pl.direct ? 0 : ((size_t)2 << pl.binBits));
+    pl.off_sample = take(pl.direct ? 0 : (size_t)pl.samples * 8);
+    pl.off_id = take(pl.direct ? 0 : (size_t)(nR + nS) * 2);
+    const size_t rec = pl.direct ? 0 : (has_c ? 16 : 8);
+    pl.off_pR = take((size_t)nR * rec);
+    pl.off_pS = take((size_t)nS * rec);
     pl.off_Ra = take((size_t)nR * 4);
-    pl.off_Rc = take((size_t)nR * 4);
     pl.off_Rr = take((size_t)nR * 4);
+    pl.off_Rc = take(has_c ? (size_t)nR * 4 : 0);
     pl.off_Sa = take((size_t)nS * 4);
-    pl.off_Sc = take((size_t)nS * 4);
     pl.off_Sr = take((size_t)nS * 4);
-    pl.off_info = take((size_t)pl.B * sizeof(BucketInfo));
-    pl.off_split = take((size_t)pl.B * 8);
-    pl.off_units = take((size_t)(pl.B + 1) * 4);
-    pl.off_table = take((size_t)pl.Umax * sizeof(uint4));
-    pl.off_counts = take((size_t)pl.nOff * 8);
-    pl.off_stash = take((size_t)pl.Umax * pl.K * 8);
-    size_t temp = scan_temp_elems<uint64_t>(pl.nOff) * 8;
-    const size_t t1 = scan_temp_elems<uint32_t>((int64_t)pl.B * pl.nChR) * 4;
-    const size_t t2 = scan_temp_elems<uint32_t>((int64_t)pl.B * pl.nChS) * 4;
-    const size_t t3 = scan_temp_elems<uint32_t>(pl.B + 1) * 4;
-    temp = temp > t1 ? temp : t1;
-    temp = temp > t2 ? temp : t2;
-    temp = temp > t3 ? temp : t3;
-    pl.off_temp = take(temp + 8);
-    pl.off_dbg = take(JL_DEBUG ? (size_t)(pl.Umax > 0 ? pl.Umax : 1) * 8 : 0);  // last (checking build)
+    pl.off_Sc = take(has_c ? (size_t)nS * 4 : 0);
+    pl.off_lo = take((size_t)nR * 4);
+    pl.off_hi = take((size_t)nR * 4);
+    pl.off_counts = take((size_t)(pl.U > 0 ? pl.U : 1) * 8);
+    pl.off_wave = take((size_t)(pl.U > 0 ? pl.U : 1) * kJoinWaves * 8);
+    pl.off_dbg = take(JL_DEBUG ? (size_t)(pl.U > 0 ? pl.U : 1) * 8 : 0);  // last (checking build)
     pl.bytes = off;
-    pl.stamp = plan_stamp({JOIN_KIND_THETA_REGION, nR, nS, op_a, pl.bits, pl.B, pl.chR, pl.chS, pl.Umax,
-                           pl.K, pl.nOff, (int64_t)pl.bytes});
+    pl.stamp = plan_stamp({JOIN_KIND_THETA_REGION, nR, nS, op_a, op_c, pl.direct, pl.bits, pl.rows, pl.U, pl.Y,
+                           knob, (int64_t)pl.bytes});
     return pl;
 }
 
-static bool g_region_attr = false;
-
 static hipError_t region_attrs()
 {
-    if (g_region_attr) return hipSuccess;
-    const int big = 160 * 1024 - 4096;
-    hipError_t e;
-    e = hipFuncSetAttribute((const void*)bscatter_k<true, true>, hipFuncAttributeMaxDynamicSharedMemorySize, big);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)bscatter_k<true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, big);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)bscatter_k<false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, big);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)bscatter_k<false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, big);
-    if (e != hipSuccess) return e;
-    g_region_attr = true;
+    static bool done = false;
+    if (done) return hipSuccess;
+    for (const void* f : {(const void*)setup_k, (const void*)sizes_k, (const void*)scatter_rows_k<true>,
+                          (const void*)scatter_rows_k<false>, (const void*)sort_k<true>, (const void*)sort_k<false>}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
+        if (e != hipSuccess) return e;
+    }
+    done = true;
     return hipSuccess;
 }
 
-static ThetaUnitArgs unit_args(const RegionPlan& pl, char* ws)
+static Join join_of(const RegionPlan& pl, const join_rel_t& R, const join_rel_t& S, const join_pred_t& p, char* ws)
 {
-    ThetaUnitArgs a{};
-    a.Ra = reinterpret_cast<const int32_t*>(ws + pl.off_Ra);
-    a.Rc = reinterpret_cast<const int32_t*>(ws + pl.off_Rc);
-    a.Rrid = reinterpret_cast<const int32_t*>(ws + pl.off_Rr);
-    a.Sa = reinterpret_cast<const int32_t*>(ws + pl.off_Sa);
-    a.Sc = reinterpret_cast<const int32_t*>(ws + pl.off_Sc);
-    a.Srid = reinterpret_cast<const int32_t*>(ws + pl.off_Sr);
-    a.units = reinterpret_cast<const uint4*>(ws + pl.off_table);
-    a.Uptr = reinterpret_cast<const uint32_t*>(ws + 8);
-    a.Umax = pl.Umax;
-    a.stash = pl.K > 0 ? reinterpret_cast<int2*>(ws + pl.off_stash) : nullptr;
-    a.K = pl.K;
-    a.nOff = pl.nOff;
-    a.stamp_at = reinterpret_cast<uint64_t*>(ws + kStampOffset);
-    a.stamp = pl.stamp;
-    a.dbg = JL_DEBUG ? reinterpret_cast<uint64_t*>(ws + pl.off_dbg) : nullptr;
-    return a;
-}
-
-static hipError_t part_side(const RegionPlan& pl, const join_rel_t& X, bool has_c, int64_t ch,
-                            int64_t nCh, size_t off_h, size_t off_a, size_t off_c, size_t off_r,
-                            char* ws, hipStream_t st, const char* name)
-{
-    const Hdr* h = reinterpret_cast<const Hdr*>(ws);
-    const uint16_t* lut = reinterpret_cast<const uint16_t*>(ws + pl.off_lut);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(ws + off_h);
-    {
-        prof::Scope ps(st, name);
-        bhist_k<<<(unsigned)nCh, kBlk, (size_t)pl.B * 4, st>>>(X.key, X.n, ch, h, lut, pl.B, hist, nCh);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = exclusive_scan<uint32_t>(hist, hist, (int64_t)pl.B * nCh, nullptr,
-                                 reinterpret_cast<uint32_t*>(ws + pl.off_temp), st);
-    if (e != hipSuccess) return e;
-    int32_t* oa = reinterpret_cast<int32_t*>(ws + off_a);
-    int32_t* oc = reinterpret_cast<int32_t*>(ws + off_c);
-    int32_t* orr = reinterpret_cast<int32_t*>(ws + off_r);
-    const size_t lds = bscatter_lds(pl.B);
-    prof::Scope ps(st, name);
-    if (has_c) {
-        if (X.rid) bscatter_k<true, true><<<(unsigned)nCh, kBlk, lds, st>>>(X.key, X.key2, X.rid, X.n, ch, h, lut, pl.B, hist, nCh, oa, oc, orr);
-        else bscatter_k<true, false><<<(unsigned)nCh, kBlk, lds, st>>>(X.key, X.key2, X.rid, X.n, ch, h, lut, pl.B, hist, nCh, oa, oc, orr);
-    } else {
-        if (X.rid) bscatter_k<false, true><<<(unsigned)nCh, kBlk, lds, st>>>(X.key, X.key2, X.rid, X.n, ch, h, lut, pl.B, hist, nCh, oa, oc, orr);
-        else bscatter_k<false, false><<<(unsigned)nCh, kBlk, lds, st>>>(X.key, X.key2, X.rid, X.n, ch, h, lut, pl.B, hist, nCh, oa, oc, orr);
-    }
-    return hipGetLastError();
+    auto i32 = [&](size_t o) { return reinterpret_cast<const int32_t*>(ws + o); };
+    Join g{};
+    g.Ra = i32(pl.off_Ra);
+    g.Rc = i32(pl.off_Rc);
+    g.Rr = i32(pl.off_Rr);
+    g.Sa = i32(pl.off_Sa);
+    g.Sc = i32(pl.off_Sc);
+    g.Sr = i32(pl.off_Sr);
+    g.nR = (uint32_t)R.n;
+    g.nS = (uint32_t)S.n;
+    g.op_a = p.op_a;
+    g.w = p.op_a == JOIN_OP_BAND ? (int64_t)p.w : 0;
+    g.rows = (uint32_t)pl.rows;
+    g.U = (uint32_t)pl.U;
+    g.Y = pl.Y;
+    g.direct = pl.direct;
+    g.h = reinterpret_cast<const Hdr*>(ws);
+    g.lut = reinterpret_cast<const uint16_t*>(ws + pl.off_lut);
+    g.baseS = reinterpret_cast<const uint32_t*>(ws + pl.off_base) + pl.B + 1;
+    g.lo = reinterpret_cast<uint32_t*>(ws + pl.off_lo);
+    g.hi = reinterpret_cast<uint32_t*>(ws + pl.off_hi);
+    g.counts = reinterpret_cast<uint64_t*>(ws + pl.off_counts);
+    g.wave_off = reinterpret_cast<uint64_t*>(ws + pl.off_wave);
+    g.done = reinterpret_cast<uint32_t*>(ws + pl.off_zero) + 3 * pl.B + kCntCount;
+    g.stamp_at = reinterpret_cast<uint64_t*>(ws + kStampOffset);
+    g.stamp = pl.stamp;
+    g.dbg = JL_DEBUG ? reinterpret_cast<uint64_t*>(ws + pl.off_dbg) : nullptr;
+    return g;
 }
 
 hipError_t region_count(const RegionPlan& pl, const join_rel_t& R, const join_rel_t& S,
@@ -724,91 +1120,85 @@ hipError_t region_count(const RegionPlan& pl, const join_rel_t& R, const join_re
 {
     hipError_t e = region_attrs();
     if (e != hipSuccess) return e;
-    Hdr* h = reinterpret_cast<Hdr*>(ws);
-    uint32_t* hist2 = reinterpret_cast<uint32_t*>(ws + pl.off_hist2);
     const bool has_c = p.op_c != JOIN_OP_NONE;
-    {
-        prof::Scope ps(st, "region.bucket");
-        init_k<<<(unsigned)ceil_div(2 * kBins, 256), 256, 0, st>>>(h, hist2);
-        range_k<<<512, kBlk, 0, st>>>(R.key, R.n, S.key, S.n, h);
-        shift_k<<<1, 1, 0, st>>>(h);
-        finehist_k<<<256, kBlk, 0, st>>>(R.key, R.n, h, hist2);
-        finehist_k<<<256, kBlk, 0, st>>>(S.key, S.n, h, hist2 + kBins);
-        buckets_k<<<1, 1024, 0, st>>>(hist2, hist2 + kBins, h, pl.B, (uint64_t)(R.n + S.n),
-                                      reinterpret_cast<uint16_t*>(ws + pl.off_lut),
-                                      reinterpret_cast<int64_t*>(ws + pl.off_vlo),
-                                      reinterpret_cast<int64_t*>(ws + pl.off_vhi));
-    }
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = part_side(pl, R, has_c, pl.chR, pl.nChR, pl.off_hR, pl.off_Ra, pl.off_Rc, pl.off_Rr, ws, st, "region.partition.R");
-    if (e != hipSuccess) return e;
-    e = part_side(pl, S, has_c, pl.chS, pl.nChS, pl.off_hS, pl.off_Sa, pl.off_Sc, pl.off_Sr, ws, st, "region.partition.S");
-    if (e != hipSuccess) return e;
-    uint32_t* split = p.op_a == JOIN_OP_BAND ? reinterpret_cast<uint32_t*>(ws + pl.off_split) : nullptr;
-    if (split) {
-        prof::Scope ps(st, "region.split");
-        bsplit_k<<<(unsigned)pl.B, kSortBlk, 0, st>>>(
-            reinterpret_cast<const uint32_t*>(ws + pl.off_hS), pl.nChS, (uint32_t)S.n, pl.B,
-            reinterpret_cast<const int64_t*>(ws + pl.off_vlo), reinterpret_cast<const int64_t*>(ws + pl.off_vhi),
-            (int64_t)p.w, reinterpret_cast<int32_t*>(ws + pl.off_Sa),
-            has_c ? reinterpret_cast<int32_t*>(ws + pl.off_Sc) : nullptr,
-            reinterpret_cast<int32_t*>(ws + pl.off_Sr), split);
+    auto i32 = [&](size_t o) { return reinterpret_cast<int32_t*>(ws + o); };
+    Sides s{};
+    s.X[0] = Cols{R.key, has_c ? R.key2 : nullptr, R.rid, R.n};
+    s.X[1] = Cols{S.key, has_c ? S.key2 : nullptr, S.rid, S.n};
+    s.h = reinterpret_cast<const Hdr*>(ws);
+    s.lut = reinterpret_cast<const uint16_t*>(ws + pl.off_lut);
+    s.B = pl.B;
+    s.zero = reinterpret_cast<uint32_t*>(ws + pl.off_zero);
+    s.base = reinterpret_cast<uint32_t*>(ws + pl.off_base);
+    s.cur = reinterpret_cast<uint32_t*>(ws + pl.off_cur);
+    s.extra = reinterpret_cast<uint2*>(ws + pl.off_extra);
+    s.id[0] = reinterpret_cast<uint16_t*>(ws + pl.off_id);
+    s.id[1] = s.id[0] + R.n;
+    s.part[0] = ws + pl.off_pR;
+    s.part[1] = ws + pl.off_pS;
+    s.oa[0] = i32(pl.off_Ra);
+    s.oa[1] = i32(pl.off_Sa);
+    s.oc[0] = i32(pl.off_Rc);
+    s.oc[1] = i32(pl.off_Sc);
+    s.orid[0] = i32(pl.off_Rr);
+    s.orid[1] = i32(pl.off_Sr);
+    if (!pl.direct) {
+        {
+            prof::Scope ps(st, "region.bucket");
+            const uint32_t sR = (uint32_t)(R.n < pl.samples ? R.n : pl.samples);
+            const uint32_t sS = (uint32_t)(S.n < pl.samples ? S.n : pl.samples);
+            int32_t* sample = reinterpret_cast<int32_t*>(ws + pl.off_sample);
+            sample_k<<<(unsigned)ceil_div(sR + sS, kBlk), kBlk, 0, st>>>(s.X[0], s.X[1], sR, sS, sample, s.zero,
+                                                                       (uint32_t)pl.zero_words);
+            setup_k<<<1, kBlk, (size_t)4 << pl.binBits, st>>>(sample, sR + sS, pl.binBits, pl.bits,
+                                                             reinterpret_cast<Hdr*>(ws),
+                                                             reinterpret_cast<uint16_t*>(ws + pl.off_lut));
+            // a workgroup per two CUs' worth of rows, whole tiles: its B counters are flushed once
+            s.chunk = ceil_div(ceil_div(R.n + S.n, 512), kCap) * kCap;
+            s.split = (uint32_t)ceil_div(R.n, s.chunk);
+            sizes_k<<<(unsigned)(s.split + ceil_div(S.n, s.chunk)), kBlk, ((size_t)pl.B * 4) + ((size_t)2 << pl.binBits), st>>>(s);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        s.split = (uint32_t)ceil_div(R.n, kCap);
+        const unsigned tiles = (unsigned)(s.split + ceil_div(S.n, kCap));
+        prof::Scope ps(st, "region.partition");
+        if (has_c) scatter_rows_k<true><<<tiles, kBlk, scatter_lds(pl.B, true), st>>>(s);
+        else scatter_rows_k<false><<<tiles, kBlk, scatter_lds(pl.B, false), st>>>(s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    uint32_t* units = reinterpret_cast<uint32_t*>(ws + pl.off_units);
-    uint64_t* counts = reinterpret_cast<uint64_t*>(ws + pl.off_counts);
-    BucketInfo* info = reinterpret_cast<BucketInfo*>(ws + pl.off_info);
     {
-        prof::Scope ps(st, "region.classify");
-        fill_u64_k<<<256, 256, 0, st>>>(counts, pl.Umax, 0);
-        classify_k<<<(unsigned)(pl.B + 1), kWave, 0, st>>>(
-            reinterpret_cast<const uint32_t*>(ws + pl.off_hR), pl.nChR,
-            reinterpret_cast<const uint32_t*>(ws + pl.off_hS), pl.nChS, (uint32_t)R.n,
-            (uint32_t)S.n, reinterpret_cast<const int64_t*>(ws + pl.off_vlo),
-            reinterpret_cast<const int64_t*>(ws + pl.off_vhi), pl.B, p.op_a,
-            p.op_a == JOIN_OP_BAND ? (int64_t)p.w : 0, has_c ? 1 : 0, split, info, units,
-            counts + pl.Umax);
+        prof::Scope ps(st, "region.sort");
+        const unsigned grid = pl.direct ? 2u : (unsigned)(2 * pl.B + R.n / kCap + S.n / kCap);
+        if (has_c) sort_k<true><<<grid, kSortBlk, kSortLds, st>>>(s, pl.direct);
+        else sort_k<false><<<grid, kSortBlk, kSortLds, st>>>(s, pl.direct);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = exclusive_scan<uint32_t>(units, units, pl.B + 1, &h->U,
-                                 reinterpret_cast<uint32_t*>(ws + pl.off_temp), st);
-    if (e != hipSuccess) return e;
-    {
-        prof::Scope ps(st, "region.classify");
-        expand_k<<<(unsigned)ceil_div(pl.B, 128), 128, 0, st>>>(
-            info, units, pl.B, pl.Umax, reinterpret_cast<uint4*>(ws + pl.off_table));
-    }
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = theta_count_units(unit_args(pl, ws), p, counts, st);
-    if (e != hipSuccess) return e;
-    return exclusive_scan<uint64_t>(counts, counts, pl.nOff, &h->total,
-                                    reinterpret_cast<uint64_t*>(ws + pl.off_temp), st, pub);
+    CountFn f = count_fn(p.op_c);
+    if (!f) return hipErrorInvalidValue;
+    prof::Scope ps(st, "region.count");
+    hipLaunchKernelGGL(f, dim3((unsigned)pl.U), dim3(kJoinBlk), 0, st, join_of(pl, R, S, p, ws),
+                       reinterpret_cast<uint64_t*>(ws), pub);
+    return hipGetLastError();
 }
 
 hipError_t region_write(const RegionPlan& pl, const join_rel_t& R, const join_rel_t& S,
                         const join_pred_t& p, char* ws, int32_t* pairs, uint64_t cap,
                         hipStream_t st)
 {
-    (void)S;
-    const uint64_t* offsets = reinterpret_cast<const uint64_t*>(ws + pl.off_counts);
-    const uint64_t* total = reinterpret_cast<const uint64_t*>(ws);
-    hipError_t e = theta_write_units(unit_args(pl, ws), p, offsets, total, pairs, cap, st);
-    if (e != hipSuccess) return e;
-    if (p.op_c == JOIN_OP_NONE) {  // green spans exist only without a condition on c
-        prof::Scope ps(st, "region.cross");
-        cross_k<<<1024, kCrossWaves * kWave, 0, st>>>(
-            reinterpret_cast<const BucketInfo*>(ws + pl.off_info), pl.B, (uint32_t)R.n,
-            reinterpret_cast<const int32_t*>(ws + pl.off_Rr),
-            reinterpret_cast<const int32_t*>(ws + pl.off_Sr), offsets + pl.Umax, total,
-            reinterpret_cast<int2*>(pairs), cap, reinterpret_cast<const uint64_t*>(ws + kStampOffset),
-            pl.stamp);
-        e = hipGetLastError();
-    }
-    return e;
+    WriteFn f = write_fn(p.op_c);
+    if (!f) return hipErrorInvalidValue;
+    // Long intervals without a condition on c are shared by several workgroups per R block when
+    // the R blocks alone leave the chip idle: one for every 256 pairs a row, up to 64.
+    uint32_t parts = 1;
+    if (p.op_c == JOIN_OP_NONE)
+        while (parts < 64 && pl.U * parts < 2048 && cap / (uint64_t)R.n >= (uint64_t)512 * parts) parts *= 2;
+    prof::Scope ps(st, "region.write");
+    hipLaunchKernelGGL(f, dim3((unsigned)pl.U * parts), dim3(kJoinBlk), 0, st, join_of(pl, R, S, p, ws),
+                       reinterpret_cast<const uint64_t*>(ws), reinterpret_cast<int2*>(pairs), cap, parts);
+    return hipGetLastError();
 }
 
 }  // namespace jl

@@ -1,29 +1,37 @@
-// region.hpp -- theta join with region pruning (bucketed ranges, red/green/white regions).
+// region.hpp -- theta join over sorted sides (the paper's region pruning, taken to single rows).
 #pragma once
 #include "common.hpp"
 
 namespace jl {
 
 struct RegionPlan {
-    int bits, B;                 // B = 2^bits value buckets shared by both sides
-    int64_t chR, chS, nChR, nChS;
-    int64_t Umax;                // bound on red units
-    int64_t K;                   // per-unit match stash (selective predicates)
-    int64_t nOff;                // Umax red counts + 2 green counts per bucket
-    size_t off_hist2, off_lut, off_vlo, off_vhi, off_hR, off_hS;
-    size_t off_Ra, off_Rc, off_Rr, off_Sa, off_Sc, off_Sr;
-    size_t off_info, off_split, off_units, off_table, off_counts, off_stash, off_temp, off_dbg, bytes;
-    uint64_t stamp;  // signature of the fields above (plan_stamp)
+    int direct;                  // 1: both sides fit one workgroup's LDS sort, no partitioning
+    int bits, B;                 // B = 2^bits value buckets shared by both sides (direct: 1)
+    int binBits;                 // 2^binBits value bins, from which the buckets are made
+    int64_t samples;             // rows sampled per side for the bins
+    int64_t rows;                // R rows per unit
+    int64_t U;                   // units: R blocks x Y
+    int Y;                       // S tiles per R block
+    size_t off_zero, zero_words; // cleared first: bucket sizes, arrivals, counters
+    size_t off_base, off_cur, off_extra, off_lut, off_sample, off_id;
+    size_t off_pR, off_pS;       // bucketed rows
+    size_t off_Ra, off_Rc, off_Rr, off_Sa, off_Sc, off_Sr;  // sorted columns
+    size_t off_lo, off_hi;       // each R row's interval of sorted S rows
+    size_t off_counts, off_wave, off_dbg, bytes;
+    uint64_t stamp;              // signature of the fields above (plan_stamp)
 };
 
-RegionPlan region_plan(int64_t nR, int64_t nS, int op_a, int64_t stash_k);
+// op_a JOIN_OP_NONE: unknown, sized for the largest layout.  knob: the theta.stash setting, which
+// changes nothing here but is part of the plan's signature, so that changing it between the two
+// passes is refused as it is for the nested loop.
+RegionPlan region_plan(int64_t nR, int64_t nS, int op_a, int op_c, int num_cus, int64_t knob);
 
-// Range, buckets, partition, classification, red-unit count pass and the scan of all counts.
-// Leaves the exact total at ws[0..8).
+// Buckets, partition, sort, intervals, count pass and the scan of all counts.  Leaves the exact
+// total at ws[0..8).
 hipError_t region_count(const RegionPlan& pl, const join_rel_t& R, const join_rel_t& S,
                         const join_pred_t& p, char* ws, hipStream_t st, uint64_t* pub = nullptr);
 
-// Write pass: red units (stash copy or re-sweep) and green cross products.
+// Write pass from the state region_count left in ws.
 hipError_t region_write(const RegionPlan& pl, const join_rel_t& R, const join_rel_t& S,
                         const join_pred_t& p, char* ws, int32_t* pairs, uint64_t cap,
                         hipStream_t st);

@@ -45,10 +45,6 @@ struct ThetaGeom {
     int64_t U;    // units = R blocks * S tiles
     int2* stash;  // [U][K] matches kept by the count pass (selective predicates), or NULL
     int64_t K;
-    // Explicit unit table (region-pruned theta join): unit u covers R rows [x, y) and S rows
-    // [z, w) of the arrays above; NULL means the dense grid of R blocks x S tiles.
-    const uint4* units;
-    const uint32_t* Uptr;  // device unit count when units != NULL (clamped to U)
     int64_t nOff;          // entries of the offsets array the write pass reads
     uint64_t* stamp_at;    // plan stamp in the workspace header: recorded by the count pass,
     uint64_t stamp;        // checked by the write pass
@@ -127,27 +123,12 @@ __device__ __forceinline__ void load_r(const ThetaGeom& g, int64_t r0, int64_t r
 __device__ __forceinline__ void unit_of(const ThetaGeom& g, int64_t u, int64_t& r0, int64_t& rEnd,
                                         int64_t& s0, int64_t& s1)
 {
-    if (g.units) {  // u is uniform: scalar loads, so the unit's bounds live in SGPRs
-        const cptr<uint32_t> q = as_const(reinterpret_cast<const uint32_t*>(g.units)) + 4 * u;
-        r0 = q[0];
-        rEnd = q[1];
-        s0 = q[2];
-        s1 = q[3];
-        return;
-    }
     const int64_t rb = u / g.nSt;
     const int64_t st = u - rb * g.nSt;
     r0 = rb * kRowsPerWave;
     rEnd = r0 + kRowsPerWave < g.nR ? r0 + kRowsPerWave : g.nR;
     s0 = st * g.TS;
     s1 = s0 + g.TS < g.nS ? s0 + g.TS : g.nS;
-}
-
-__device__ __forceinline__ int64_t unit_count(const ThetaGeom& g)
-{
-    if (!g.units) return g.U;
-    const int64_t U = *g.Uptr;
-    return U < g.U ? U : g.U;
 }
 
 // Evaluate one S row against the wave's kRB R rows exactly and emit the matches in (r, lane)
@@ -260,68 +241,21 @@ __device__ __forceinline__ void sweep_selective(const ThetaGeom& g, const RRows&
 // ------------------------------------------------------------------------------- count pass --
 // Selective predicates also keep up to K matches of the unit in a per-unit stash, so the write
 // pass of a unit with at most K matches is a copy instead of a second sweep.
-// DENSE (region units of a selective predicate): the units were chosen because their value
-// ranges are close, so most 8-row groups hold a match and the group filter would send nearly
-// every group down its exact path.  Instead every S row is evaluated exactly against the wave's R rows
-// (both columns and rids kept in registers), one ballot per R row.
-template <int OPA, int OPC, bool DENSE = false>
+template <int OPA, int OPC>
 __global__ __launch_bounds__(kThetaBlock) void theta_count_k(ThetaGeom g,
                                                              uint64_t* __restrict__ counts)
 {
     const int lane = (int)lane_id();
     if (g.stamp_at && blockIdx.x == 0 && threadIdx.x == 0) *g.stamp_at = g.stamp;  // for the write pass
     const int64_t u = (int64_t)blockIdx.x * kWavesPerBlock + uniform((int32_t)(threadIdx.x >> 6));
-    if (u >= unit_count(g)) return;
+    if (u >= g.U) return;
     {
         int64_t r0, rEnd, s0, s1;
         unit_of(g, u, r0, rEnd, s0, s1);
         RRows rr;
-        load_r<OPA, selective<OPA>() && !DENSE ? JOIN_OP_NONE : OPC>(g, r0, rEnd, lane, rr);
+        load_r<OPA, selective<OPA>() ? JOIN_OP_NONE : OPC>(g, r0, rEnd, lane, rr);
 
-        if constexpr (selective<OPA>() && DENSE) {
-            int32_t rid[kRB];
-            uint64_t vm[kRB];
-            load_rids(g, r0, rEnd, lane, rid, vm);
-            const cptr<int32_t> Sa = as_const(g.Sa);
-            const cptr<int32_t> Sc = as_const(g.Sc);
-            const cptr<int32_t> Srid = as_const(g.Srid);
-            uint64_t n = 0;
-            int2* st = g.stash ? g.stash + u * g.K : nullptr;
-            const uint64_t kcap = st ? (uint64_t)g.K : 0ull;
-            // Region units always come with the bucketed rid column (positions when the input
-            // has none), so the rids load unconditionally with the other columns.
-            // 8 S rows' scalar loads in flight together, the next group's while this one is
-            // evaluated
-            int64_t j = s0;
-            int32_t na[kSGroup], nc[kSGroup], nr[kSGroup];
-            auto fetch = [&](int64_t j0) {
-#pragma unroll
-                for (int k = 0; k < kSGroup; ++k) {
-                    na[k] = Sa[j0 + k];
-                    nc[k] = (OPC != JOIN_OP_NONE) ? Sc[j0 + k] : 0;
-                    nr[k] = Srid[j0 + k];
-                }
-            };
-            if (j + kSGroup <= s1) fetch(j);
-            for (; j + kSGroup <= s1; j += kSGroup) {
-                int32_t sa[kSGroup], sc[kSGroup], sr[kSGroup];
-#pragma unroll
-                for (int k = 0; k < kSGroup; ++k) {
-                    sa[k] = na[k];
-                    sc[k] = nc[k];
-                    sr[k] = nr[k];
-                }
-                if (j + 2 * kSGroup <= s1) fetch(j + kSGroup);
-#pragma unroll
-                for (int k = 0; k < kSGroup; ++k)
-                    emit_row<OPA, OPC>(rr, rid, vm, sa[k], sc[k], sr[k], n, st, kcap, lane);
-            }
-            for (; j < s1; ++j) {
-                const int32_t sc = (OPC != JOIN_OP_NONE) ? Sc[j] : 0;
-                emit_row<OPA, OPC>(rr, rid, vm, Sa[j], sc, Srid[j], n, st, kcap, lane);
-            }
-            if (lane == 0) counts[u] = n;
-        } else if constexpr (selective<OPA>()) {
+        if constexpr (selective<OPA>()) {
             uint64_t n = 0;
             int2* st = g.stash ? g.stash + u * g.K : nullptr;
             sweep_selective<OPA, OPC>(g, rr, r0, rEnd, s0, s1, n, st, st ? (uint64_t)g.K : 0ull,
@@ -366,7 +300,7 @@ __global__ __launch_bounds__(kThetaBlock) void theta_count_k(ThetaGeom g,
 }
 
 // ------------------------------------------------------------------------------- write pass --
-template <int OPA, int OPC, bool DENSE = false>
+template <int OPA, int OPC>
 __global__ __launch_bounds__(kThetaBlock) void theta_write_k(ThetaGeom g,
                                                              const uint64_t* __restrict__ offsets,
                                                              const uint64_t* __restrict__ total,
@@ -378,7 +312,7 @@ __global__ __launch_bounds__(kThetaBlock) void theta_write_k(ThetaGeom g,
     if (tot > cap || (g.stamp_at && *g.stamp_at != g.stamp)) return;
     const int lane = (int)lane_id();
     const int64_t u = (int64_t)blockIdx.x * kWavesPerBlock + uniform((int32_t)(threadIdx.x >> 6));
-    if (u >= unit_count(g)) return;
+    if (u >= g.U) return;
     {
         const uint64_t off = uniform(offsets[u]);
         const uint64_t cnt = (u + 1 < g.nOff ? uniform(offsets[u + 1]) : tot) - off;
@@ -395,7 +329,7 @@ __global__ __launch_bounds__(kThetaBlock) void theta_write_k(ThetaGeom g,
         int64_t r0, rEnd, s0, s1;
         unit_of(g, u, r0, rEnd, s0, s1);
         uint64_t base = off;
-        if constexpr (selective<OPA>() && !DENSE) {
+        if constexpr (selective<OPA>()) {
             RRows rr;
             load_r<OPA, JOIN_OP_NONE>(g, r0, rEnd, lane, rr);
             sweep_selective<OPA, OPC>(g, rr, r0, rEnd, s0, s1, base, out, cap, lane);
@@ -424,61 +358,60 @@ __global__ __launch_bounds__(kThetaBlock) void theta_write_k(ThetaGeom g,
 using CountFn = void (*)(ThetaGeom, uint64_t*);
 using WriteFn = void (*)(ThetaGeom, const uint64_t*, const uint64_t*, int2*, uint64_t);
 
-template <int OPA, bool DENSE>
+template <int OPA>
 struct Table {
     static CountFn count(int opc)
     {
         switch (opc) {
-        case JOIN_OP_NONE: return theta_count_k<OPA, JOIN_OP_NONE, DENSE>;
-        case JOIN_OP_EQ: return theta_count_k<OPA, JOIN_OP_EQ, DENSE>;
-        case JOIN_OP_NE: return theta_count_k<OPA, JOIN_OP_NE, DENSE>;
-        case JOIN_OP_LT: return theta_count_k<OPA, JOIN_OP_LT, DENSE>;
-        case JOIN_OP_LE: return theta_count_k<OPA, JOIN_OP_LE, DENSE>;
-        case JOIN_OP_GT: return theta_count_k<OPA, JOIN_OP_GT, DENSE>;
-        case JOIN_OP_GE: return theta_count_k<OPA, JOIN_OP_GE, DENSE>;
+        case JOIN_OP_NONE: return theta_count_k<OPA, JOIN_OP_NONE>;
+        case JOIN_OP_EQ: return theta_count_k<OPA, JOIN_OP_EQ>;
+        case JOIN_OP_NE: return theta_count_k<OPA, JOIN_OP_NE>;
+        case JOIN_OP_LT: return theta_count_k<OPA, JOIN_OP_LT>;
+        case JOIN_OP_LE: return theta_count_k<OPA, JOIN_OP_LE>;
+        case JOIN_OP_GT: return theta_count_k<OPA, JOIN_OP_GT>;
+        case JOIN_OP_GE: return theta_count_k<OPA, JOIN_OP_GE>;
         default: return nullptr;
         }
     }
     static WriteFn write(int opc)
     {
         switch (opc) {
-        case JOIN_OP_NONE: return theta_write_k<OPA, JOIN_OP_NONE, DENSE>;
-        case JOIN_OP_EQ: return theta_write_k<OPA, JOIN_OP_EQ, DENSE>;
-        case JOIN_OP_NE: return theta_write_k<OPA, JOIN_OP_NE, DENSE>;
-        case JOIN_OP_LT: return theta_write_k<OPA, JOIN_OP_LT, DENSE>;
-        case JOIN_OP_LE: return theta_write_k<OPA, JOIN_OP_LE, DENSE>;
-        case JOIN_OP_GT: return theta_write_k<OPA, JOIN_OP_GT, DENSE>;
-        case JOIN_OP_GE: return theta_write_k<OPA, JOIN_OP_GE, DENSE>;
+        case JOIN_OP_NONE: return theta_write_k<OPA, JOIN_OP_NONE>;
+        case JOIN_OP_EQ: return theta_write_k<OPA, JOIN_OP_EQ>;
+        case JOIN_OP_NE: return theta_write_k<OPA, JOIN_OP_NE>;
+        case JOIN_OP_LT: return theta_write_k<OPA, JOIN_OP_LT>;
+        case JOIN_OP_LE: return theta_write_k<OPA, JOIN_OP_LE>;
+        case JOIN_OP_GT: return theta_write_k<OPA, JOIN_OP_GT>;
+        case JOIN_OP_GE: return theta_write_k<OPA, JOIN_OP_GE>;
         default: return nullptr;
         }
     }
 };
 
-// dense: region units (only the selective operators have a separate dense form)
-CountFn count_fn(int opa, int opc, bool dense = false)
+CountFn count_fn(int opa, int opc)
 {
     switch (opa) {
-    case JOIN_OP_EQ: return dense ? Table<JOIN_OP_EQ, true>::count(opc) : Table<JOIN_OP_EQ, false>::count(opc);
-    case JOIN_OP_NE: return Table<JOIN_OP_NE, false>::count(opc);
-    case JOIN_OP_LT: return Table<JOIN_OP_LT, false>::count(opc);
-    case JOIN_OP_LE: return Table<JOIN_OP_LE, false>::count(opc);
-    case JOIN_OP_GT: return Table<JOIN_OP_GT, false>::count(opc);
-    case JOIN_OP_GE: return Table<JOIN_OP_GE, false>::count(opc);
-    case JOIN_OP_BAND: return dense ? Table<JOIN_OP_BAND, true>::count(opc) : Table<JOIN_OP_BAND, false>::count(opc);
+    case JOIN_OP_EQ: return Table<JOIN_OP_EQ>::count(opc);
+    case JOIN_OP_NE: return Table<JOIN_OP_NE>::count(opc);
+    case JOIN_OP_LT: return Table<JOIN_OP_LT>::count(opc);
+    case JOIN_OP_LE: return Table<JOIN_OP_LE>::count(opc);
+    case JOIN_OP_GT: return Table<JOIN_OP_GT>::count(opc);
+    case JOIN_OP_GE: return Table<JOIN_OP_GE>::count(opc);
+    case JOIN_OP_BAND: return Table<JOIN_OP_BAND>::count(opc);
     default: return nullptr;
     }
 }
 
-WriteFn write_fn(int opa, int opc, bool dense = false)
+WriteFn write_fn(int opa, int opc)
 {
     switch (opa) {
-    case JOIN_OP_EQ: return dense ? Table<JOIN_OP_EQ, true>::write(opc) : Table<JOIN_OP_EQ, false>::write(opc);
-    case JOIN_OP_NE: return Table<JOIN_OP_NE, false>::write(opc);
-    case JOIN_OP_LT: return Table<JOIN_OP_LT, false>::write(opc);
-    case JOIN_OP_LE: return Table<JOIN_OP_LE, false>::write(opc);
-    case JOIN_OP_GT: return Table<JOIN_OP_GT, false>::write(opc);
-    case JOIN_OP_GE: return Table<JOIN_OP_GE, false>::write(opc);
-    case JOIN_OP_BAND: return dense ? Table<JOIN_OP_BAND, true>::write(opc) : Table<JOIN_OP_BAND, false>::write(opc);
+    case JOIN_OP_EQ: return Table<JOIN_OP_EQ>::write(opc);
+    case JOIN_OP_NE: return Table<JOIN_OP_NE>::write(opc);
+    case JOIN_OP_LT: return Table<JOIN_OP_LT>::write(opc);
+    case JOIN_OP_LE: return Table<JOIN_OP_LE>::write(opc);
+    case JOIN_OP_GT: return Table<JOIN_OP_GT>::write(opc);
+    case JOIN_OP_GE: return Table<JOIN_OP_GE>::write(opc);
+    case JOIN_OP_BAND: return Table<JOIN_OP_BAND>::write(opc);
     default: return nullptr;
     }
 }
@@ -501,8 +434,6 @@ ThetaGeom geom(const ThetaPlan& pl, const join_rel_t& R, const join_rel_t& S, co
     g.TS = pl.TS;
     g.nSt = pl.nSt;
     g.U = pl.U;
-    g.units = nullptr;
-    g.Uptr = nullptr;
     g.nOff = pl.U;
     g.stamp_at = reinterpret_cast<uint64_t*>(ws + kStampOffset);
     g.stamp = pl.stamp;
@@ -512,55 +443,7 @@ ThetaGeom geom(const ThetaPlan& pl, const join_rel_t& R, const join_rel_t& S, co
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
-ThetaGeom unit_geom(const ThetaUnitArgs& a, const join_pred_t& p)
-{
-    ThetaGeom g{};
-    g.Ra = a.Ra;
-    g.Rc = a.Rc;
-    g.Rrid = a.Rrid;
-    g.Sa = a.Sa;
-    g.Sc = a.Sc;
-    g.Srid = a.Srid;
-    g.w = p.op_a == JOIN_OP_BAND ? (int64_t)p.w : 0;
-    g.U = a.Umax;
-    g.stash = a.stash;
-    g.K = a.stash ? a.K : 0;
-    g.units = a.units;
-    g.Uptr = a.Uptr;
-    g.nOff = a.nOff;
-    g.stamp_at = a.stamp_at;
-    g.stamp = a.stamp;
-    g.dbg = a.dbg;
-    return g;
-}
-
 }  // namespace
-
-hipError_t theta_count_units(const ThetaUnitArgs& a, const join_pred_t& p, uint64_t* counts,
-                             hipStream_t st)
-{
-    if (a.Umax <= 0) return hipSuccess;
-    CountFn f = count_fn(p.op_a, p.op_c, true);
-    if (!f) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)ceil_div(a.Umax, kWavesPerBlock);
-    prof::Scope ps(st, "region.count");
-    hipLaunchKernelGGL(f, dim3(grid), dim3(kThetaBlock), 0, st, unit_geom(a, p), counts);
-    return hipGetLastError();
-}
-
-hipError_t theta_write_units(const ThetaUnitArgs& a, const join_pred_t& p,
-                             const uint64_t* offsets, const uint64_t* total, int32_t* pairs,
-                             uint64_t cap, hipStream_t st)
-{
-    if (a.Umax <= 0) return hipSuccess;
-    WriteFn f = write_fn(p.op_a, p.op_c, true);
-    if (!f) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)ceil_div(a.Umax, kWavesPerBlock);
-    prof::Scope ps(st, "region.write");
-    hipLaunchKernelGGL(f, dim3(grid), dim3(kThetaBlock), 0, st, unit_geom(a, p), offsets, total,
-                       reinterpret_cast<int2*>(pairs), cap);
-    return hipGetLastError();
-}
 
 ThetaPlan theta_plan(int64_t nR, int64_t nS, int op_a, int64_t target_waves, int64_t ts_override,
                      int64_t stash_k)
