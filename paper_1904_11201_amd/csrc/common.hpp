@@ -66,9 +66,11 @@ __device__ __forceinline__ gptr<T> as_global(const T* p)
     return (gptr<T>)(p);
 }
 
-// 16-byte load of four int32 through a global pointer (p 16-byte aligned).
+// 16-byte load of four int32 through a global pointer.  Global loads of several words need only
+// the alignment of one, so any int32 column may be read this way (the type says so).
 using i32x4 = int32_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ i32x4 load4(gptr<int32_t> p) { return *(const __attribute__((address_space(1))) i32x4*)p; }
+using i32x4_any = int32_t __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ i32x4 load4(gptr<int32_t> p) { return *(const __attribute__((address_space(1))) i32x4_any*)p; }
 
 // Plan stamps.  Every workspace starts with a 256-byte header.  The count pass records at
 // kStampOffset a signature of the plan it ran (sizes, fan-out, capacities, tiles: how the work

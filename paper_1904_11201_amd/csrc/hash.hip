@@ -94,7 +94,6 @@ __global__ void zero_u32_k(uint32_t* __restrict__ p, int64_t n)
 struct SideTwo {
     SideItem one;
     int64_t chunk, n;
-    uint32_t* tot;  // histogram: its partition sizes
     uint32_t* grp;  // histogram: its group shares; scatter: its group cursors
     int2* out;      // scatter: its partitioned tuples
     uint32_t* cnt;  // its per-tile counts (histogram), then its run offsets (scatter)
@@ -129,21 +128,34 @@ __device__ __forceinline__ SideItem side_item(const SideItem* __restrict__ items
     return it;
 }
 
-__device__ __forceinline__ bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
-
 // Chunks are grouped by their workgroup index modulo kGroups, which on this chip is the XCD the
 // workgroup runs on: a group's chunks write each partition through one shared cursor (see the
 // scatter), so the partially written 64-byte granules of a partition stay in one XCD's L2.
-// A chunk counts its tuples per partition in LDS, then adds the counts to tot[part0 + p] (the
-// partition's size) and grp[g * stride + part0 + p] (its group's share of the partition).
+// A chunk counts its tuples per partition in LDS, then adds the counts to
+// grp[g * stride + part0 + p], its group's share of the partition; the partition's size is the
+// sum of its shares.
 __device__ __forceinline__ uint32_t group_of_block() { return blockIdx.x % kGroups; }
 
+// LDS counters per partition.  Lanes of a wave that meet in one counter, or in one bank, add one
+// after the other, and with few partitions they nearly always do (one partition: 64 in turn).  So
+// a partition gets up to 64 counters, one per lane, side by side: with 64 every lane has a bank of
+// its own.  kHistCounters bounds their number: clearing and summing 8192 took longer than they
+// saved (1M x 4M: 23 us, 9 with 2048).
+constexpr int kHistCounters = 2048;
+
+__host__ __device__ constexpr int hist_rep_bits(int bits)
+{
+    int rb = 0;
+    while (rb < 6 && (2 << (bits + rb)) <= kHistCounters) ++rb;
+    return rb;
+}
+
 // Per tile of kScatTile rows of the chunk (the scatter's tiles), the count of every partition
-// goes to the tile's row of the side's count array; the chunk's totals then go to the partition
-// sizes and to the chunk group's shares with one global atomic each.
+// goes to the tile's row of the side's count array; the chunk's totals then go to the chunk
+// group's shares.
 __global__ __launch_bounds__(kHistBlock) void hist_k(const SideItem* __restrict__ items, SideItem one,
-                                                     int64_t chunk, int64_t n, uint32_t* tot,
-                                                     uint32_t* grp, uint32_t stride, uint32_t* cnt,
+                                                     int64_t chunk, int64_t n, uint32_t* grp,
+                                                     uint32_t stride, uint32_t* cnt,
                                                      SideTwo two)
 {
     extern __shared__ uint32_t h[];
@@ -153,74 +165,100 @@ __global__ __launch_bounds__(kHistBlock) void hist_k(const SideItem* __restrict_
     const SideItem it = second ? side_item(nullptr, two.one, two.chunk, two.n, blockIdx.x - two.split)
                                : side_item(items, one, chunk, n, blockIdx.x);
     if (second) {
-        tot = two.tot;
         grp = two.grp;
         cnt = two.cnt;
     }
     const int P = 1 << it.bits;
     const int sh = 32 - it.bits;
-    for (int i = threadIdx.x; i < P; i += kHistBlock) h[i] = 0;
+    const int rb = cnt ? 0 : hist_rep_bits(it.bits), reps = 1 << rb;
+    const uint32_t mine = lane_id() & (uint32_t)(reps - 1);
+    for (int i = threadIdx.x; i < (P << rb); i += kHistBlock) h[i] = 0;
+    auto add = [&](int32_t key) { atomicAdd(&h[(pid_of(key, sh) << rb) + mine], 1u); };
     uint32_t own[2] = {0u, 0u};  // chunk totals of partitions tid and tid + kHistBlock
     __syncthreads();
     const gptr<int32_t> key = as_global(it.key + it.beg);
-    const bool vec = aligned16(it.key + it.beg);
     const int64_t end = it.len;
     // ordered scatter (cnt != NULL): one row per tile; else the chunk is counted as one span
     const int64_t span = cnt ? (int64_t)kScatTile : (end > 0 ? end : 1);
     uint32_t* __restrict__ row = cnt ? cnt + it.cnt0 : nullptr;
+    // One round is up to a tile, the next round's loads in flight while this one is counted.  Only
+    // whole vectors are loaded, with no branch (threads past the last one repeat it); the odd
+    // keys of a span follow at its end.
+    auto load = [&](int64_t i, int64_t to, i32x4 (&k4)[V]) {
+        const int nv = (int)((to - i < kScatTile ? to - i : kScatTile) / 4);  // uniform
+        if (nv == 0) return;
+#pragma unroll
+        for (int v = 0; v < V; ++v) k4[v] = load4(key + i + 4 * min(v * kHistBlock + (int)threadIdx.x, nv - 1));
+    };
     for (int64_t t0 = 0; t0 < end; t0 += span) {
-        const int64_t tn = end - t0 < span ? end - t0 : span;
-        if (!cnt && vec) {
-            int64_t i = 0;
-            for (; i + kScatTile <= tn; i += kScatTile) {
-                i32x4 k4[V];
-#pragma unroll
-                for (int v = 0; v < V; ++v) k4[v] = load4(key + t0 + i + v * 4 * kHistBlock + 4 * threadIdx.x);
-#pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    atomicAdd(&h[pid_of(k4[v].x, sh)], 1u);
-                    atomicAdd(&h[pid_of(k4[v].y, sh)], 1u);
-                    atomicAdd(&h[pid_of(k4[v].z, sh)], 1u);
-                    atomicAdd(&h[pid_of(k4[v].w, sh)], 1u);
-                }
-            }
-            for (i += threadIdx.x; i < tn; i += kHistBlock) atomicAdd(&h[pid_of(key[t0 + i], sh)], 1u);
-        } else if (vec && tn == kScatTile) {
+        const int64_t to = end - t0 < span ? end : t0 + span;
+        i32x4 next[V]{};
+        load(t0, to, next);
+        for (int64_t i = t0; i < to; i += kScatTile) {
             i32x4 k4[V];
 #pragma unroll
-            for (int v = 0; v < V; ++v) k4[v] = load4(key + t0 + v * 4 * kHistBlock + 4 * threadIdx.x);
+            for (int v = 0; v < V; ++v) k4[v] = next[v];
+            if (i + kScatTile < to) load(i + kScatTile, to, next);
+            if (i + kScatTile <= to) {  // uniform
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                atomicAdd(&h[pid_of(k4[v].x, sh)], 1u);
-                atomicAdd(&h[pid_of(k4[v].y, sh)], 1u);
-                atomicAdd(&h[pid_of(k4[v].z, sh)], 1u);
-                atomicAdd(&h[pid_of(k4[v].w, sh)], 1u);
+                for (int v = 0; v < V; ++v) {
+                    add(k4[v].x);
+                    add(k4[v].y);
+                    add(k4[v].z);
+                    add(k4[v].w);
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    if (v * kHistBlock + (int)threadIdx.x < (int)((to - i) / 4)) {
+                        add(k4[v].x);
+                        add(k4[v].y);
+                        add(k4[v].z);
+                        add(k4[v].w);
+                    }
             }
-        } else {
-            for (int64_t i = threadIdx.x; i < tn; i += kHistBlock) atomicAdd(&h[pid_of(key[t0 + i], sh)], 1u);
         }
+        if (threadIdx.x < ((to - t0) & 3)) add(key[to - 1 - threadIdx.x]);
         __syncthreads();
+        if (!cnt) break;  // the whole chunk is counted
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int p = (int)threadIdx.x + j * kHistBlock;
             if (p < P) {
                 const uint32_t v = h[p];
-                if (row) row[p] = v;
+                row[p] = v;
                 own[j] += v;
                 h[p] = 0;
             }
         }
         __syncthreads();
-        if (row) row += P;
+        row += P;
     }
     uint32_t* __restrict__ gs = grp + (size_t)group_of_block() * stride + it.part0;
+    if (!cnt) {
+        // a partition's counters lie in consecutive lanes: summed across them
+        uint32_t* sum = h + (P << rb);
+        for (int i0 = 0; i0 < (P << rb); i0 += kHistBlock) {
+            const int i = i0 + (int)threadIdx.x;
+            uint32_t v = i < (P << rb) ? h[i] : 0u;
+            for (int m = 1; m < reps; m *= 2) v += (uint32_t)__shfl_xor((int)v, m);
+            if (mine == 0 && i < (P << rb)) sum[i >> rb] = v;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int p = (int)threadIdx.x + j * kHistBlock;
+            own[j] = p < P ? sum[p] : 0u;
+        }
+    }
+    // Consecutive lanes add to consecutive counters: an atomic instruction costs one request per
+    // line, and requests to one line follow each other every 10 ns or so (one lane at a time took
+    // 196 us where this takes 8, 1M x 4M).  For the same reason only the group's shares are added
+    // to, an eighth of the workgroups each; the partition sizes are their sums.
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int p = (int)threadIdx.x + j * kHistBlock;
-        if (p < P && own[j]) {
-            atomicAdd(&tot[it.part0 + p], own[j]);
-            atomicAdd(&gs[p], own[j]);
-        }
+        if (p < P && own[j]) atomicAdd(&gs[p], own[j]);
     }
 }
 
@@ -316,6 +354,23 @@ __global__ void band_batch_k(const SideItem* __restrict__ items, const uint32_t*
         }
 }
 
+// Partition sizes of both sides (nil: skipped) from the group shares.
+__global__ void group_sums_k(const uint32_t* __restrict__ grpR, uint32_t* __restrict__ totR,
+                             const uint32_t* __restrict__ grpS, uint32_t* __restrict__ totS,
+                             uint32_t stride, int64_t n)
+{
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    uint32_t r = 0, s = 0;
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        r += totR ? grpR[(size_t)g * stride + p] : 0u;
+        s += totS ? grpS[(size_t)g * stride + p] : 0u;
+    }
+    if (totR) totR[p] = r;
+    if (totS) totS[p] = s;
+}
+
 // Group shares -> group cursors: the groups' ranges follow each other inside every partition,
 // cur[g * stride + p] = base[p] + shares of groups before g.  In place.
 __global__ void group_cursors_k(uint32_t* __restrict__ grp, const uint32_t* __restrict__ base,
@@ -354,17 +409,30 @@ __global__ void group_cursors_k(uint32_t* __restrict__ grp, const uint32_t* __re
 // 16-byte load instruction of a wave reads 1 KB of consecutive input.
 __device__ __forceinline__ int scat_pos(int q) { return 4 * ((q >> 2) * kScatBlock + (int)threadIdx.x) + (q & 3); }
 
+// Tuples per thread of the arrival-order scatter.  Up to 2^kSmallBits partitions a tile of 8K
+// tuples still gives runs of 16 tuples (two 64-byte granules), and its 64 KB let two workgroups
+// share a CU, one's loads and stores overlapping the other's LDS work.
+constexpr int kSmallBits = 9;
+constexpr int kSmallIt = kScatIt / 2;
+// LDS counters of a tile, side by side for one partition like the histogram's.
+constexpr int kScatCounters = 2 * kScatBlock;
+
+__host__ __device__ constexpr int scat_rep_bits(int bits)
+{
+    int rb = 0;
+    while (rb < 6 && (2 << (bits + rb)) <= kScatCounters) ++rb;
+    return rb;
+}
+
 // Loads of a tile's keys or rids: FULL tiles read whole 16-byte vectors; a partial tile (a
-// chunk's last) reads the vectors that lie inside it when the column is 16-byte aligned (vec),
-// and the rest element by element.
-template <bool FULL>
-__device__ __forceinline__ void scat_load(gptr<int32_t> col, int t0, int tn, int32_t (&x)[kScatIt],
-                                          bool vec = true)
+// chunk's last) reads the vectors that lie inside it, and the rest element by element.
+template <bool FULL, int IT>
+__device__ __forceinline__ void scat_load(gptr<int32_t> col, int t0, int tn, int32_t (&x)[IT])
 {
 #pragma unroll
-    for (int v = 0; v < kScatIt / 4; ++v) {
+    for (int v = 0; v < IT / 4; ++v) {
         const int e = scat_pos(4 * v);
-        if (FULL || (vec && e + 4 <= tn)) {
+        if (FULL || e + 4 <= tn) {
             const i32x4 x4 = load4(col + t0 + e);
             x[4 * v] = x4.x; x[4 * v + 1] = x4.y; x[4 * v + 2] = x4.z; x[4 * v + 3] = x4.w;
         } else {
@@ -381,61 +449,76 @@ __device__ __forceinline__ void scat_load(gptr<int32_t> col, int t0, int tn, int
 // group soon after, in the same XCD's L2.  The order of a partition's tuples depends on that
 // arrival order (and, inside a tile, on the order of the LDS atomics of different waves).
 struct ScatLdsA {
-    int2* stg;      // [kScatTile] the tile sorted by partition
-    uint32_t* cnt;  // [P] tile shares, then sorted starts
+    int2* stg;      // [kScatBlock * IT] the tile sorted by partition
+    uint32_t* cnt;  // [kScatCounters] tile shares, then placing cursors: 2^rb per partition
     uint32_t* dlt;  // [P] output position - sorted position
+    uint32_t* beg;  // [P + 1] sorted starts (rb > 0)
     uint32_t* tmp;  // scan scratch
 };
 
 // One tile: k holds raw keys (hashed here), r the row ids (RIDS) or nothing (row id = pos0 + tile
 // position).  cur: this group's cursors of the join's partitions.
-template <bool RIDS, bool FULL>
-__device__ __forceinline__ void scat_tile_a(int32_t (&k)[kScatIt], const int32_t (&r)[kScatIt], int tn,
-                                          int64_t pos0, int P, int sh, const ScatLdsA& L,
+template <bool RIDS, bool FULL, int IT>
+__device__ __forceinline__ void scat_tile_a(int32_t (&k)[IT], const int32_t (&r)[IT], int tn,
+                                          int64_t pos0, int P, int sh, int rb, const ScatLdsA& L,
                                           uint32_t* __restrict__ cur, int2* __restrict__ out)
 {
     const int tid = threadIdx.x;
-    const int pa = 2 * tid, pb = 2 * tid + 1;
+    const int va = 2 * tid, vb = 2 * tid + 1, V = P << rb;  // this thread's two counters
+    const uint32_t mine = lane_id() & ((1u << rb) - 1);
+    auto part = [&](uint32_t h) { return sh >= 32 ? 0u : h >> sh; };
     // 1. shares.  Tuples are written as (hmix(key), rid): the hash is a bijection of the key, so
     // the join kernels compare hashes and never hash again.
 #pragma unroll
-    for (int q = 0; q < kScatIt; ++q) {
+    for (int q = 0; q < IT; ++q) {
         const uint32_t h = hmix((uint32_t)k[q]);
         k[q] = (int32_t)h;
-        if (FULL || scat_pos(q) < tn) atomicAdd(&L.cnt[sh >= 32 ? 0u : h >> sh], 1u);
+        if (FULL || scat_pos(q) < tn) atomicAdd(&L.cnt[(part(h) << rb) + mine], 1u);
     }
     __syncthreads();
-    // 2. output positions from the group cursors; sorted starts (cnt becomes each partition's
-    // placing cursor)
-    const uint32_t ca = pa < P ? L.cnt[pa] : 0u, cb = pb < P ? L.cnt[pb] : 0u;
+    // 2. output positions from the group cursors; sorted starts (cnt becomes the placing cursors)
+    const uint32_t ca = va < V ? L.cnt[va] : 0u, cb = vb < V ? L.cnt[vb] : 0u;
     uint32_t oa = 0, ob = 0;
-    if (ca) oa = atomicAdd(&cur[pa], ca);
-    if (cb) ob = atomicAdd(&cur[pb], cb);
+    if (rb == 0) {  // uniform
+        if (ca) oa = atomicAdd(&cur[va], ca);
+        if (cb) ob = atomicAdd(&cur[vb], cb);
+    }
     uint32_t tot;
     const uint32_t sa = block_excl_scan<kScatBlock>(ca + cb, L.tmp, &tot);
-    if (pa < P) L.cnt[pa] = sa;
-    if (pb < P) L.cnt[pb] = sa + ca;
+    if (va < V) L.cnt[va] = sa;
+    if (vb < V) L.cnt[vb] = sa + ca;
+    if (rb && va < V && (va & ((1 << rb) - 1)) == 0) L.beg[va >> rb] = sa;
+    if (rb && tid == 0) L.beg[P] = (uint32_t)tn;
     __syncthreads();
+    uint32_t s0 = 0;
+    if (rb && tid < P) {
+        s0 = L.beg[tid];
+        const uint32_t c = L.beg[tid + 1] - s0;
+        if (c) oa = atomicAdd(&cur[tid], c);
+    }
     // 3. place in sorted order: each tuple takes the next slot of its partition
 #pragma unroll
-    for (int q = 0; q < kScatIt; ++q) {
+    for (int q = 0; q < IT; ++q) {
         const int e = scat_pos(q);
         if (FULL || e < tn) {
-            const uint32_t h = (uint32_t)k[q];
-            const uint32_t at = atomicAdd(&L.cnt[sh >= 32 ? 0u : h >> sh], 1u);
+            const uint32_t at = atomicAdd(&L.cnt[(part((uint32_t)k[q]) << rb) + mine], 1u);
             L.stg[at] = make_int2(k[q], RIDS ? r[q] : (int32_t)(pos0 + e));
         }
     }
     // shift from sorted position to output position
-    if (pa < P) L.dlt[pa] = oa - sa;
-    if (pb < P) L.dlt[pb] = ob - (sa + ca);
+    if (rb == 0) {
+        if (va < P) L.dlt[va] = oa - sa;
+        if (vb < P) L.dlt[vb] = ob - (sa + ca);
+    } else if (tid < P) {
+        L.dlt[tid] = oa - s0;
+    }
     __syncthreads();
-    if (pa < P) L.cnt[pa] = 0;  // the next tile's shares (nothing reads the cursors any more)
-    if (pb < P) L.cnt[pb] = 0;
+    if (va < V) L.cnt[va] = 0;  // the next tile's shares (nothing reads the cursors any more)
+    if (vb < V) L.cnt[vb] = 0;
     // 4. write the sorted tile, eight LDS reads in flight at a time
     constexpr int G = 8;
 #pragma unroll
-    for (int g = 0; g < kScatIt; g += G) {
+    for (int g = 0; g < IT; g += G) {
         int2 v[G];
         uint32_t d[G];
 #pragma unroll
@@ -444,10 +527,7 @@ __device__ __forceinline__ void scat_tile_a(int32_t (&k)[kScatIt], const int32_t
             v[u] = (FULL || i < tn) ? L.stg[i] : make_int2(0, 0);
         }
 #pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const uint32_t h = (uint32_t)v[u].x;
-            d[u] = L.dlt[sh >= 32 ? 0u : h >> sh];
-        }
+        for (int u = 0; u < G; ++u) d[u] = L.dlt[part((uint32_t)v[u].x)];
 #pragma unroll
         for (int u = 0; u < G; ++u) {
             const int i = (g + u) * kScatBlock + tid;
@@ -460,48 +540,50 @@ __device__ __forceinline__ void scat_tile_a(int32_t (&k)[kScatIt], const int32_t
 // Full tile t of a chunk: the next tile's keys and rids are loaded into nk, nr while this one is
 // worked on, before this tile's stores, so that waiting for them does not wait for the stores
 // (the vector memory counter counts loads and stores in one queue).
-template <bool RIDS>
+template <bool RIDS, int IT>
 __device__ __forceinline__ void scat_full_tile_a(int t, int nfull, gptr<int32_t> key, gptr<int32_t> rid,
-                                               int32_t (&nk)[kScatIt], int32_t (&nr)[kScatIt],
-                                               int64_t beg, int P, int sh, const ScatLdsA& L,
+                                               int32_t (&nk)[IT], int32_t (&nr)[IT],
+                                               int64_t beg, int P, int sh, int rb, const ScatLdsA& L,
                                                uint32_t* __restrict__ cur, int2* __restrict__ out)
 {
-    int32_t k[kScatIt], r[kScatIt];
+    constexpr int T = kScatBlock * IT;
+    int32_t k[IT], r[IT];
 #pragma unroll
-    for (int q = 0; q < kScatIt; ++q) {
+    for (int q = 0; q < IT; ++q) {
         k[q] = nk[q];
         if (RIDS) r[q] = nr[q];
     }
     if (t + 1 < nfull) {
-        scat_load<true>(key, (t + 1) * kScatTile, kScatTile, nk);
-        if (RIDS) scat_load<true>(rid, (t + 1) * kScatTile, kScatTile, nr);
+        scat_load<true>(key, (t + 1) * T, T, nk);
+        if (RIDS) scat_load<true>(rid, (t + 1) * T, T, nr);
     }
-    scat_tile_a<RIDS, true>(k, r, kScatTile, beg + (int64_t)t * kScatTile, P, sh, L, cur, out);
+    scat_tile_a<RIDS, true>(k, r, T, beg + (int64_t)t * T, P, sh, rb, L, cur, out);
 }
 
 // A chunk: its full tiles, then the partial rest.  The first full tile is peeled off the loop,
 // so that every pass through the loop starts in the same state (the loads it needs issued before
 // the previous tile's stores) and waiting for those loads does not wait for the stores.
-template <bool RIDS>
-__device__ __forceinline__ void scat_chunk_a(gptr<int32_t> key, gptr<int32_t> rid, bool vec, int end,
-                                           int64_t beg, int P, int sh, const ScatLdsA& L,
+template <bool RIDS, int IT>
+__device__ __forceinline__ void scat_chunk_a(gptr<int32_t> key, gptr<int32_t> rid, int end,
+                                           int64_t beg, int P, int sh, int rb, const ScatLdsA& L,
                                            uint32_t* __restrict__ cur, int2* __restrict__ out)
 {
-    const int nfull = vec ? end / kScatTile : 0;
-    int32_t nk[kScatIt], nr[kScatIt];
+    constexpr int T = kScatBlock * IT;
+    const int nfull = end / T;
+    int32_t nk[IT], nr[IT];
     if (nfull > 0) {
-        scat_load<true>(key, 0, kScatTile, nk);
-        if (RIDS) scat_load<true>(rid, 0, kScatTile, nr);
-        scat_full_tile_a<RIDS>(0, nfull, key, rid, nk, nr, beg, P, sh, L, cur, out);
+        scat_load<true>(key, 0, T, nk);
+        if (RIDS) scat_load<true>(rid, 0, T, nr);
+        scat_full_tile_a<RIDS>(0, nfull, key, rid, nk, nr, beg, P, sh, rb, L, cur, out);
     }
     for (int t = 1; t < nfull; ++t)
-        scat_full_tile_a<RIDS>(t, nfull, key, rid, nk, nr, beg, P, sh, L, cur, out);
-    for (int t0 = nfull * kScatTile; t0 < end; t0 += kScatTile) {
-        const int tn = end - t0 < kScatTile ? end - t0 : kScatTile;
-        int32_t k[kScatIt], r[kScatIt];
-        scat_load<false>(key, t0, tn, k, vec);
-        if (RIDS) scat_load<false>(rid, t0, tn, r, vec);
-        scat_tile_a<RIDS, false>(k, r, tn, beg + t0, P, sh, L, cur, out);
+        scat_full_tile_a<RIDS>(t, nfull, key, rid, nk, nr, beg, P, sh, rb, L, cur, out);
+    for (int t0 = nfull * T; t0 < end; t0 += T) {
+        const int tn = end - t0 < T ? end - t0 : T;
+        int32_t k[IT], r[IT];
+        scat_load<false>(key, t0, tn, k);
+        if (RIDS) scat_load<false>(rid, t0, tn, r);
+        scat_tile_a<RIDS, false>(k, r, tn, beg + t0, P, sh, rb, L, cur, out);
     }
 }
 
@@ -663,12 +745,12 @@ __device__ __forceinline__ void scat_full_tile(int t, int nfull, gptr<int32_t> k
 // so that every pass through the loop starts in the same state (the loads it needs issued before
 // the previous tile's stores) and waiting for those loads does not wait for the stores.
 template <bool RIDS>
-__device__ __forceinline__ void scat_chunk(gptr<int32_t> key, gptr<int32_t> rid, bool vec, int end,
+__device__ __forceinline__ void scat_chunk(gptr<int32_t> key, gptr<int32_t> rid, int end,
                                            int64_t beg, int P, int sh, const ScatLds& L,
                                            ScatDest d, const uint32_t* __restrict__ cnt0,
                                            int2* __restrict__ out)
 {
-    const int nfull = vec ? end / kScatTile : 0;
+    const int nfull = end / kScatTile;
     int32_t nk[kScatIt], nr[kScatIt];
     if (nfull > 0) {
         scat_offsets(cnt0, 0, P, d.oa, d.ob);
@@ -682,8 +764,8 @@ __device__ __forceinline__ void scat_chunk(gptr<int32_t> key, gptr<int32_t> rid,
         const int tn = end - t0 < kScatTile ? end - t0 : kScatTile;
         int32_t k[kScatIt], r[kScatIt];
         scat_offsets(cnt0, t0 / kScatTile, P, d.oa, d.ob);
-        scat_load<false>(key, t0, tn, k, vec);
-        if (RIDS) scat_load<false>(rid, t0, tn, r, vec);
+        scat_load<false>(key, t0, tn, k);
+        if (RIDS) scat_load<false>(rid, t0, tn, r);
         scat_tile<RIDS, false>(k, r, tn, beg + t0, P, sh, L, d, out);
     }
 }
@@ -790,16 +872,7 @@ __global__ void expand_units_k(const uint32_t* __restrict__ unitStart, const Par
 // part_starts_k runs one workgroup per side.
 constexpr int kFuseBlock = 1024;
 constexpr int kFuseParts = 8192;
-
-__device__ __forceinline__ void group_cursors(uint32_t* __restrict__ grp, uint32_t stride, int p, uint32_t run)
-{
-#pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-        const uint32_t c = grp[(size_t)g * stride + p];
-        grp[(size_t)g * stride + p] = run;
-        run += c;
-    }
-}
+constexpr int kFuseStarts = 65536;  // part_starts_k: about 1 us for every 2048 partitions of a side
 
 // Band work of a single join: 8 groups x ceil(P / kBandQ) partition blocks per side with counts
 // (cnt != NULL).
@@ -808,12 +881,69 @@ __host__ __device__ __forceinline__ int64_t band_blocks(const BandSide& b)
     return b.cnt ? (int64_t)kGroups * (((1 << b.bits) + kBandQ - 1) / kBandQ) : 0;
 }
 
+// One side's partition sizes (the sums of the groups' shares), starts and group starts.  A pass
+// takes PER rows of one partition per thread (consecutive lanes on consecutive partitions), with
+// all its loads in flight and one scan over the PER * 16 wave sums (at most two per lane of a
+// wave).
+template <int PER>
+__device__ void side_starts(uint32_t* __restrict__ tot, uint32_t* __restrict__ base, uint32_t* __restrict__ grp,
+                            uint32_t stride, int n, uint32_t* tmp)
+{
+    constexpr int W = kFuseBlock / kWave;
+    static_assert(PER * W <= 2 * kWave, "one wave scans the wave sums");
+    const int wv = threadIdx.x / kWave;
+    uint32_t carry = 0;
+    for (int b0 = 0; b0 < n; b0 += PER * kFuseBlock) {
+        uint32_t x[PER][kGroups], c[PER], inc[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) {
+                const int p = b0 + j * kFuseBlock + (int)threadIdx.x;
+                x[j][g] = p < n ? grp[(size_t)g * stride + p] : 0u;
+            }
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            c[j] = 0;
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) c[j] += x[j][g];
+            inc[j] = wave_incl_scan(c[j]);
+            if (lane_id() == kWave - 1) tmp[j * W + wv] = inc[j];
+        }
+        __syncthreads();
+        if (wv == 0) {
+            const uint32_t i = 2 * lane_id();
+            const uint32_t a = i < PER * W ? tmp[i] : 0u, b = i + 1 < PER * W ? tmp[i + 1] : 0u;
+            const uint32_t s = wave_incl_scan(a + b);
+            if (i < PER * W) tmp[i] = s - a - b;
+            if (i + 1 < PER * W) tmp[i + 1] = s - b;
+            if (lane_id() == kWave - 1) tmp[PER * W] = s;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int p = b0 + j * kFuseBlock + (int)threadIdx.x;
+            if (p >= n) continue;
+            uint32_t run = carry + tmp[j * W + wv] + inc[j] - c[j];
+            tot[p] = c[j];
+            base[p] = run;
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) {
+                grp[(size_t)g * stride + p] = run;
+                run += x[j][g];
+            }
+        }
+        carry += tmp[PER * W];
+        __syncthreads();
+    }
+}
+
 // Workgroups 0 and 1: each side's partition starts and group starts (a NULL tot skips that
 // side).  Workgroups from 2 on: the run offsets of R's tiles, then of S's (band_side).
-__global__ __launch_bounds__(kFuseBlock) void part_starts_k(const uint32_t* __restrict__ totR,
+__global__ __launch_bounds__(kFuseBlock) void part_starts_k(uint32_t* __restrict__ totR,
                                                             uint32_t* __restrict__ baseR,
                                                             uint32_t* __restrict__ grpR,
-                                                            const uint32_t* __restrict__ totS,
+                                                            uint32_t* __restrict__ totS,
                                                             uint32_t* __restrict__ baseS,
                                                             uint32_t* __restrict__ grpS,
                                                             uint32_t stride, int n, BandSide bR,
@@ -830,29 +960,12 @@ __global__ __launch_bounds__(kFuseBlock) void part_starts_k(const uint32_t* __re
         band_side(b, (int)(k / nq), (int)(k % nq) * kBandQ, tmp);
         return;
     }
-    {
-        const int side = blockIdx.x;  // workgroup 0: R, workgroup 1: S
-        const uint32_t* tot = side ? totS : totR;
-        uint32_t* base = side ? baseS : baseR;
-        uint32_t* grp = side ? grpS : grpR;
-        if (!tot) return;
-        uint32_t carry = 0;
-        for (int b0 = 0; b0 < n; b0 += 2 * kFuseBlock) {
-            const int pa = b0 + 2 * (int)threadIdx.x, pb = pa + 1;
-            const uint32_t ca = pa < n ? tot[pa] : 0u, cb = pb < n ? tot[pb] : 0u;
-            uint32_t t;
-            const uint32_t sa = carry + block_excl_scan<kFuseBlock>(ca + cb, tmp, &t);
-            if (pa < n) {
-                base[pa] = sa;
-                group_cursors(grp, stride, pa, sa);
-            }
-            if (pb < n) {
-                base[pb] = sa + ca;
-                group_cursors(grp, stride, pb, sa + ca);
-            }
-            carry += t;
-        }
-    }
+    uint32_t* tot = blockIdx.x ? totS : totR;
+    uint32_t* base = blockIdx.x ? baseS : baseR;
+    uint32_t* grp = blockIdx.x ? grpS : grpR;
+    if (!tot) return;
+    if (n <= 2 * kFuseBlock) side_starts<2>(tot, base, grp, stride, n, tmp);
+    else side_starts<8>(tot, base, grp, stride, n, tmp);  // a batch's many partitions
 }
 
 // The plans of all partitions by one workgroup of BLOCK threads, two partitions per thread and
@@ -915,7 +1028,8 @@ struct PlanArgs {
 // [kGroups][stride]; cnt: the side's run offsets (band scan).
 // ORDERED: the ordered scatter (runs at the band scan's offsets, ranks from per-wave counters),
 // else the arrival-order one (runs at the group cursors).
-template <bool RIDS, bool ORDERED>
+// IT: tuples per thread of an arrival-order tile (the ordered scatter's tiles are kScatTile).
+template <bool RIDS, bool ORDERED, int IT = kScatIt>
 __global__ __launch_bounds__(kScatBlock) void scatter_k(const SideItem* __restrict__ items, SideItem one,
                                                         int64_t chunk, int64_t n, uint32_t* cur,
                                                         uint32_t stride, int2* out,
@@ -942,21 +1056,21 @@ __global__ __launch_bounds__(kScatBlock) void scatter_k(const SideItem* __restri
     const int tid = threadIdx.x;
     if constexpr (!ORDERED) {
         ScatLdsA L;
+        const int rb = scat_rep_bits(it.bits);
         L.stg = reinterpret_cast<int2*>(lds);
-        L.cnt = lds + 2 * kScatTile;
-        L.dlt = L.cnt + P;
-        L.tmp = L.dlt + P;
-        if (2 * tid < P) L.cnt[2 * tid] = 0;
-        if (2 * tid + 1 < P) L.cnt[2 * tid + 1] = 0;
+        L.cnt = lds + 2 * kScatBlock * IT;
+        L.dlt = L.cnt + kScatCounters;
+        L.beg = L.dlt + P;
+        L.tmp = L.beg + (rb ? P + 1 : 0);
+        L.cnt[2 * tid] = 0;
+        L.cnt[2 * tid + 1] = 0;
         __syncthreads();
         uint32_t* __restrict__ gc = cur + (size_t)group_of_block() * stride + it.part0;
         const gptr<int32_t> key = as_global(it.key + it.beg);
-        const bool kvec = aligned16(it.key + it.beg);
         if (!RIDS || it.rid == nullptr) {
-            scat_chunk_a<false>(key, nullptr, kvec, (int)it.len, it.beg, P, sh, L, gc, out);
+            scat_chunk_a<false, IT>(key, nullptr, (int)it.len, it.beg, P, sh, rb, L, gc, out);
         } else {
-            const bool vec = kvec && aligned16(it.rid + it.beg);
-            scat_chunk_a<true>(key, as_global(it.rid + it.beg), vec, (int)it.len, it.beg, P, sh, L, gc, out);
+            scat_chunk_a<true, IT>(key, as_global(it.rid + it.beg), (int)it.len, it.beg, P, sh, rb, L, gc, out);
         }
         return;
     }
@@ -973,12 +1087,10 @@ __global__ __launch_bounds__(kScatBlock) void scatter_k(const SideItem* __restri
     d.gb = 2 * tid + 1 < P ? gc[2 * tid + 1] : 0u;
     const uint32_t* __restrict__ c0 = cnt + it.cnt0;
     const gptr<int32_t> key = as_global(it.key + it.beg);
-    const bool kvec = aligned16(it.key + it.beg);
     if (!RIDS || it.rid == nullptr) {
-        scat_chunk<false>(key, nullptr, kvec, (int)it.len, it.beg, P, sh, L, d, c0, out);
+        scat_chunk<false>(key, nullptr, (int)it.len, it.beg, P, sh, L, d, c0, out);
     } else {
-        const bool vec = kvec && aligned16(it.rid + it.beg);
-        scat_chunk<true>(key, as_global(it.rid + it.beg), vec, (int)it.len, it.beg, P, sh, L, d, c0, out);
+        scat_chunk<true>(key, as_global(it.rid + it.beg), (int)it.len, it.beg, P, sh, L, d, c0, out);
     }
 }
 
@@ -2245,13 +2357,22 @@ size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 }  // namespace
 
 
-// Arrival order: the sorted tile, shares/starts and shifts per partition, scan scratch.
+// Arrival order: the sorted tile, its counters, shifts and starts per partition, scan scratch.
 // Ordered: half of the sorted tile, per-wave counters and shifts per partition, scan scratch.
 static size_t scatter_lds(int P, bool ordered)
 {
-    if (!ordered) return (size_t)kScatTile * sizeof(int2) + (size_t)P * 8 + (kScatBlock / kWave + 1) * 4;
+    if (!ordered)
+        return (size_t)kScatBlock * (P <= 1 << kSmallBits ? kSmallIt : kScatIt) * sizeof(int2) +
+               (size_t)kScatCounters * 4 + (size_t)P * 8 + 4 + (kScatBlock / kWave + 1) * 4;
     return (size_t)kScatHalf * sizeof(int2) + (size_t)(kScatWaves / 2) * P * 4 + (size_t)P * 4 +
            (kScatWaves + 1) * 4;
+}
+
+// The histogram's counters for items of up to 2^maxBits partitions (fewer partitions never need
+// more counters: 64 a partition, or as many as fit kHistCounters).
+static size_t hist_lds(int maxBits)
+{
+    return ((size_t)4 << (maxBits + hist_rep_bits(maxBits))) + ((size_t)4 << maxBits);
 }
 
 static bool ordered_knob() { return tune_get(TUNE_HASH_DETERMINISTIC, 0) != 0; }
@@ -2437,6 +2558,7 @@ static hipError_t set_attrs()
     const int write_max_b = (int)(160 * 1024 - kBatchStaticLds - 256);
     const void* fns[] = {
         (const void*)scatter_k<true, false>, (const void*)scatter_k<false, false>,
+        (const void*)scatter_k<true, false, kSmallIt>, (const void*)scatter_k<false, false, kSmallIt>,
         (const void*)scatter_k<true, true>, (const void*)scatter_k<false, true>, (const void*)hist_k,
         (const void*)join_count_k<true, false, kJoinBlock>, (const void*)join_count_k<false, false, kJoinBlock>,
         (const void*)join_count_k<true, true, kJoinBlock>, (const void*)join_count_k<true, false, kBatchBlock>,
@@ -2469,22 +2591,22 @@ static SideItem whole_side(const join_rel_t& X, int bits)
 }
 
 static hipError_t hist_side(const SideItem* items, const SideItem& one, int64_t ch, int64_t n,
-                            int64_t grid, int maxBits, uint32_t* tot, uint32_t* grp, int64_t stride,
+                            int64_t grid, int maxBits, uint32_t* grp, int64_t stride,
                             uint32_t* cnt, hipStream_t st, bool is_r)
 {
     if (grid <= 0) return hipSuccess;
-    const size_t hl = (size_t)4 << maxBits;
+    const size_t hl = hist_lds(maxBits);
     SideTwo none{};
     none.split = (uint32_t)grid;
     prof::Scope ph(st, is_r ? "hash.hist.R" : "hash.hist.S");
-    hist_k<<<(unsigned)grid, kHistBlock, hl, st>>>(items, one, ch, n, tot, grp, (uint32_t)stride, cnt, none);
+    hist_k<<<(unsigned)grid, kHistBlock, hl, st>>>(items, one, ch, n, grp, (uint32_t)stride, cnt, none);
     return hipGetLastError();
 }
 
 // Both sides of a single join in one launch, R's chunks first.
 static hipError_t hist_pair(const SideItem& oneR, int64_t chR, int64_t nR, int64_t gridR,
-                            uint32_t* totR, uint32_t* grpR, uint32_t* cntR, const SideItem& oneS,
-                            int64_t chS, int64_t nS, int64_t gridS, uint32_t* totS, uint32_t* grpS,
+                            uint32_t* grpR, uint32_t* cntR, const SideItem& oneS,
+                            int64_t chS, int64_t nS, int64_t gridS, uint32_t* grpS,
                             uint32_t* cntS, int bits, int64_t stride, hipStream_t st)
 {
     if (gridR + gridS <= 0) return hipSuccess;
@@ -2492,13 +2614,12 @@ static hipError_t hist_pair(const SideItem& oneR, int64_t chR, int64_t nR, int64
     two.one = oneS;
     two.chunk = chS;
     two.n = nS;
-    two.tot = totS;
     two.grp = grpS;
     two.cnt = cntS;
     two.split = (uint32_t)gridR;
     prof::Scope ph(st, "hash.hist");
-    hist_k<<<(unsigned)(gridR + gridS), kHistBlock, (size_t)4 << bits, st>>>(
-        nullptr, oneR, chR, nR, totR, grpR, (uint32_t)stride, cntR, two);
+    hist_k<<<(unsigned)(gridR + gridS), kHistBlock, hist_lds(bits), st>>>(
+        nullptr, oneR, chR, nR, grpR, (uint32_t)stride, cntR, two);
     return hipGetLastError();
 }
 
@@ -2515,12 +2636,12 @@ static hipError_t cursors_side(uint32_t* grp, const uint32_t* base, int64_t stri
 // the run offsets of the sides' tiles given by bR and bS (cnt NULL: none): one launch up to
 // kFuseParts partitions, else a scan and a cursor kernel per side (then no run offsets: batches
 // compute theirs with band_batch_k).
-static hipError_t starts_sides(const uint32_t* totR, uint32_t* baseR, uint32_t* grpR,
-                               const uint32_t* totS, uint32_t* baseS, uint32_t* grpS, int64_t n,
+static hipError_t starts_sides(uint32_t* totR, uint32_t* baseR, uint32_t* grpR,
+                               uint32_t* totS, uint32_t* baseS, uint32_t* grpS, int64_t n,
                                uint32_t* temp, hipStream_t st, const BandSide& bR = BandSide{},
                                const BandSide& bS = BandSide{})
 {
-    if (n <= kFuseParts) {
+    if (n <= kFuseStarts) {
         prof::Scope pc(st, "hash.plan");
         const int64_t blocks = 2 + band_blocks(bR) + band_blocks(bS);
         part_starts_k<<<(unsigned)blocks, kFuseBlock, 0, st>>>(totR, baseR, grpR, totS, baseS, grpS,
@@ -2528,8 +2649,12 @@ static hipError_t starts_sides(const uint32_t* totR, uint32_t* baseR, uint32_t* 
         return hipGetLastError();
     }
     if (bR.cnt || bS.cnt) return hipErrorInvalidValue;  // band work rides only on the fused launch
-    hipError_t e = hipSuccess;
-    if (totR) {
+    {
+        prof::Scope pc(st, "hash.plan");
+        group_sums_k<<<(unsigned)ceil_div(n, 256), 256, 0, st>>>(grpR, totR, grpS, totS, (uint32_t)n, n);
+    }
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && totR) {
         e = exclusive_scan<uint32_t>(totR, baseR, n, nullptr, temp, st);
         if (e == hipSuccess) e = cursors_side(grpR, baseR, n, st);
     }
@@ -2579,6 +2704,16 @@ static hipError_t plan_parts(const PartPlan& q, int64_t nParts, PartInfo* info, 
     return hipGetLastError();
 }
 
+using ScatterFn = void (*)(const SideItem*, SideItem, int64_t, int64_t, uint32_t*, uint32_t, int2*,
+                           const uint32_t*, SideTwo, PlanArgs);
+
+// The arrival-order scatter for items of up to 2^maxBits partitions.
+static ScatterFn arrival_scatter(int maxBits, bool rids)
+{
+    if (maxBits <= kSmallBits) return rids ? scatter_k<true, false, kSmallIt> : scatter_k<false, false, kSmallIt>;
+    return rids ? scatter_k<true, false> : scatter_k<false, false>;
+}
+
 static hipError_t scatter_side(const SideItem* items, const SideItem& one, int64_t ch, int64_t n,
                                int64_t grid, int maxBits, uint32_t* cur, int64_t stride,
                                int2* out, const uint32_t* cnt, hipStream_t st, bool is_r,
@@ -2596,8 +2731,7 @@ static hipError_t scatter_side(const SideItem* items, const SideItem& one, int64
         if (rids) scatter_k<true, true><<<(unsigned)all, kScatBlock, sl, st>>>(items, one, ch, n, cur, (uint32_t)stride, out, cnt, none, pa);
         else scatter_k<false, true><<<(unsigned)all, kScatBlock, sl, st>>>(items, one, ch, n, cur, (uint32_t)stride, out, cnt, none, pa);
     } else {
-        if (rids) scatter_k<true, false><<<(unsigned)all, kScatBlock, sl, st>>>(items, one, ch, n, cur, (uint32_t)stride, out, cnt, none, pa);
-        else scatter_k<false, false><<<(unsigned)all, kScatBlock, sl, st>>>(items, one, ch, n, cur, (uint32_t)stride, out, cnt, none, pa);
+        arrival_scatter(maxBits, rids)<<<(unsigned)all, kScatBlock, sl, st>>>(items, one, ch, n, cur, (uint32_t)stride, out, cnt, none, pa);
     }
     return hipGetLastError();
 }
@@ -2628,8 +2762,7 @@ static hipError_t scatter_pair(const SideItem& oneR, int64_t chR, int64_t nR, in
         if (rids) scatter_k<true, true><<<(unsigned)all, kScatBlock, sl, st>>>(nullptr, oneR, chR, nR, curR, (uint32_t)stride, outR, cntR, two, pa);
         else scatter_k<false, true><<<(unsigned)all, kScatBlock, sl, st>>>(nullptr, oneR, chR, nR, curR, (uint32_t)stride, outR, cntR, two, pa);
     } else {
-        if (rids) scatter_k<true, false><<<(unsigned)all, kScatBlock, sl, st>>>(nullptr, oneR, chR, nR, curR, (uint32_t)stride, outR, cntR, two, pa);
-        else scatter_k<false, false><<<(unsigned)all, kScatBlock, sl, st>>>(nullptr, oneR, chR, nR, curR, (uint32_t)stride, outR, cntR, two, pa);
+        arrival_scatter(bits, rids)<<<(unsigned)all, kScatBlock, sl, st>>>(nullptr, oneR, chR, nR, curR, (uint32_t)stride, outR, cntR, two, pa);
     }
     return hipGetLastError();
 }
@@ -2706,10 +2839,10 @@ hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
         uint32_t* cntR = pl.ordered ? reinterpret_cast<uint32_t*>(ws + pl.off_cntR) : nullptr;
         uint32_t* cntS = pl.ordered ? reinterpret_cast<uint32_t*>(ws + pl.off_cntS) : nullptr;
         if (pre)
-            e = hist_side(nullptr, oneS, pl.chS, S.n, pl.nChS, pl.bits, totS, grpS, pl.P, cntS, st, false);
+            e = hist_side(nullptr, oneS, pl.chS, S.n, pl.nChS, pl.bits, grpS, pl.P, cntS, st, false);
         else
-            e = hist_pair(oneR, pl.chR, R.n, pl.nChR, totR, grpR, cntR, oneS, pl.chS, S.n, pl.nChS,
-                          totS, grpS, cntS, pl.bits, pl.P, st);
+            e = hist_pair(oneR, pl.chR, R.n, pl.nChR, grpR, cntR, oneS, pl.chS, S.n, pl.nChS,
+                          grpS, cntS, pl.bits, pl.P, st);
         if (e != hipSuccess) return e;
         // the scatter launch puts R's chunks first (none for a prebuilt R)
         const int64_t sBase = pre ? 0 : pl.nChR;
@@ -2839,7 +2972,7 @@ hipError_t hash_build(const BuildPlan& b, const join_rel_t& R, char* build, hipS
     if (e != hipSuccess) return e;
     const SideItem one = whole_side(R, b.bits);
     uint32_t* cnt = b.ordered ? reinterpret_cast<uint32_t*>(build + b.off_cnt) : nullptr;
-    e = hist_side(nullptr, one, b.chR, R.n, b.nChR, b.bits, tot, grp, b.P, cnt, st, true);
+    e = hist_side(nullptr, one, b.chR, R.n, b.nChR, b.bits, grp, b.P, cnt, st, true);
     if (e != hipSuccess) return e;
     e = starts_sides(tot, base, grp, nullptr, nullptr, nullptr, b.P,
                      reinterpret_cast<uint32_t*>(build + b.off_temp), st,
@@ -3067,9 +3200,9 @@ hipError_t hash_batch_count(const BatchPlan& bp, char* ws, uint64_t* offsets, hi
     if (e != hipSuccess) return e;
     uint32_t* cntR = bp.ordered ? reinterpret_cast<uint32_t*>(ws + bp.off_cntR) : nullptr;
     uint32_t* cntS = bp.ordered ? reinterpret_cast<uint32_t*>(ws + bp.off_cntS) : nullptr;
-    e = hist_side(itemsR, none, 0, 0, bp.nItemsR, bp.maxBits, totR, grpR, bp.nParts, cntR, st, true);
+    e = hist_side(itemsR, none, 0, 0, bp.nItemsR, bp.maxBits, grpR, bp.nParts, cntR, st, true);
     if (e != hipSuccess) return e;
-    e = hist_side(itemsS, none, 0, 0, bp.nItemsS, bp.maxBits, totS, grpS, bp.nParts, cntS, st, false);
+    e = hist_side(itemsS, none, 0, 0, bp.nItemsS, bp.maxBits, grpS, bp.nParts, cntS, st, false);
     if (e != hipSuccess) return e;
     e = starts_sides(totR, baseR, grpR, totS, baseS, grpS, bp.nParts, reinterpret_cast<uint32_t*>(temp), st);
     if (e != hipSuccess) return e;
