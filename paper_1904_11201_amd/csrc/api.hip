@@ -1,5 +1,6 @@
 // api.hip -- the C ABI of libjoin (include/join.h): validation, plans, launch sequencing and
 // the single 8-byte host read of the exact count.
+#include <atomic>
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -38,12 +39,17 @@ namespace {
 
 constexpr int64_t kMaxRows = 2147483647;  // rids and positions are int32
 
+// Compute units of the current device (kept per device: every call plans with it).
 int num_cus()
 {
+    constexpr int kDevices = 64;
+    static std::atomic<int> known[kDevices];
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 256;
+    if (dev >= 0 && dev < kDevices && (n = known[dev].load(std::memory_order_relaxed)) > 0) return n;
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
         return 256;
+    if (dev >= 0 && dev < kDevices) known[dev].store(n, std::memory_order_relaxed);
     return n;
 }
 
@@ -135,31 +141,35 @@ RegionPlan plan_region(int64_t nR, int64_t nS, const join_pred_t* p)
                        theta_stash_k());
 }
 
-// Signature of the plan a call of this kind makes for these sizes under the current knobs
-// (the same value the count pass records in the workspace header).
-uint64_t plan_stamp_of(int kind, int64_t nR, int64_t nS, const join_pred_t* p)
+// The plan a call of this kind makes for these sizes under the current knobs, made once per call.
+struct AnyPlan {
+    HashPlan hash;
+    PrefilterPlan prefilter;
+    ThetaPlan theta;
+    RegionPlan region;
+    size_t bytes;    // workspace
+    uint64_t stamp;  // signature (the same value the count pass records in the workspace header)
+};
+
+AnyPlan plan_of(int kind, int64_t nR, int64_t nS, const join_pred_t* p)
 {
-    if (kind == JOIN_KIND_HASH) return hash_plan(nR, nS, num_cus()).stamp;
-    if (kind == JOIN_KIND_HASH_PREFILTER) return prefilter_plan(nR, nS, num_cus()).stamp;
-    if (kind == JOIN_KIND_THETA_REGION) return plan_region(nR, nS, p).stamp;
-    return plan_theta(nR, nS, p).stamp;
+    AnyPlan a{};
+    auto keep = [&](const auto& pl) {
+        a.bytes = pl.bytes;
+        a.stamp = pl.stamp;
+    };
+    if (kind == JOIN_KIND_HASH) keep(a.hash = hash_plan(nR, nS, num_cus()));
+    else if (kind == JOIN_KIND_HASH_PREFILTER) keep(a.prefilter = prefilter_plan(nR, nS, num_cus()));
+    else if (kind == JOIN_KIND_THETA_REGION) keep(a.region = plan_region(nR, nS, p));
+    else keep(a.theta = plan_theta(nR, nS, p));
+    return a;
 }
 
-size_t ws_needed(int kind, int64_t nR, int64_t nS, const join_pred_t* p)
+int check_ws(const AnyPlan& pl, void* ws, size_t ws_bytes)
 {
-    if (kind == JOIN_KIND_HASH) return hash_plan(nR, nS, num_cus()).bytes;
-    if (kind == JOIN_KIND_HASH_PREFILTER) return prefilter_plan(nR, nS, num_cus()).bytes;
-    if (kind == JOIN_KIND_THETA_REGION) return plan_region(nR, nS, p).bytes;
-    return plan_theta(nR, nS, p).bytes;
-}
-
-int check_ws(int kind, const join_rel_t* R, const join_rel_t* S, const join_pred_t* p, void* ws,
-             size_t ws_bytes)
-{
-    const size_t need = ws_needed(kind, R->n, S->n, p);
-    if (!ws || ws_bytes < need) {
+    if (!ws || ws_bytes < pl.bytes) {
         set_error("workspace %p of %zu bytes is smaller than the %zu bytes this join needs", ws,
-                  ws_bytes, need);
+                  ws_bytes, pl.bytes);
         return JOIN_E_WORKSPACE;
     }
     return JOIN_OK;
@@ -348,8 +358,8 @@ hipError_t read_word(const void* src, uint64_t* v, hipStream_t st)
 }
 #endif
 
-int count_impl(int kind, const join_rel_t* R, const join_rel_t* S, const join_pred_t* p, void* ws,
-               hipStream_t st, uint64_t* count)
+int count_impl(int kind, const AnyPlan& pl, const join_rel_t* R, const join_rel_t* S,
+               const join_pred_t* p, void* ws, hipStream_t st, uint64_t* count)
 {
     g_last.valid = false;
     if (R->n == 0 || S->n == 0) {
@@ -360,17 +370,14 @@ int count_impl(int kind, const join_rel_t* R, const join_rel_t* S, const join_pr
         size_t total_at = 0;  // where the exact total lands in ws
         uint64_t* pub = arm_published_slot();
         if (kind == JOIN_KIND_HASH) {
-            const HashPlan pl = hash_plan(R->n, S->n, num_cus());
-            e = hash_count(pl, *R, *S, w, st, nullptr, pub);
+            e = hash_count(pl.hash, *R, *S, w, st, nullptr, pub);
         } else if (kind == JOIN_KIND_HASH_PREFILTER) {
-            const PrefilterPlan pl = prefilter_plan(R->n, S->n, num_cus());
-            e = prefilter_count(pl, *R, *S, w, st, num_cus(), pub);
-            total_at = prefilter_total_offset(pl);
+            e = prefilter_count(pl.prefilter, *R, *S, w, st, num_cus(), pub);
+            total_at = prefilter_total_offset(pl.prefilter);
         } else if (kind == JOIN_KIND_THETA_REGION) {
-            e = region_count(plan_region(R->n, S->n, p), *R, *S, *p, w, st, pub);
+            e = region_count(pl.region, *R, *S, *p, w, st, pub);
         } else {
-            const ThetaPlan pl = plan_theta(R->n, S->n, p);
-            e = theta_count(pl, *R, *S, *p, w, st, pub);
+            e = theta_count(pl.theta, *R, *S, *p, w, st, pub);
         }
         if (e != hipSuccess) return hip_fail(e, is_theta(kind) ? "theta count pass" : "hash count pass");
         e = take_total(pub, w + total_at, st, count);
@@ -387,12 +394,12 @@ int count_impl(int kind, const join_rel_t* R, const join_rel_t* S, const join_pr
     if (p) g_last.p = *p;
     g_last.ws = ws;
     g_last.count = *count;
-    g_last.stamp = plan_stamp_of(kind, R->n, S->n, p);
+    g_last.stamp = pl.stamp;
     return JOIN_OK;
 }
 
-int write_impl(int kind, const join_rel_t* R, const join_rel_t* S, const join_pred_t* p, void* ws,
-               int32_t* pairs, uint64_t capacity, hipStream_t st)
+int write_impl(int kind, const AnyPlan& pl, const join_rel_t* R, const join_rel_t* S,
+               const join_pred_t* p, void* ws, int32_t* pairs, uint64_t capacity, hipStream_t st)
 {
     if (R->n == 0 || S->n == 0) return JOIN_OK;
     if (capacity > 0 && !pairs) {
@@ -420,15 +427,13 @@ int write_impl(int kind, const join_rel_t* R, const join_rel_t* S, const join_pr
     }
 #endif
     if (kind == JOIN_KIND_HASH) {
-        const HashPlan pl = hash_plan(R->n, S->n, num_cus());
-        e = hash_write(pl, *R, *S, w, pairs, capacity, st);
+        e = hash_write(pl.hash, *R, *S, w, pairs, capacity, st);
     } else if (kind == JOIN_KIND_HASH_PREFILTER) {
-        e = prefilter_write(prefilter_plan(R->n, S->n, num_cus()), *R, *S, w, pairs, capacity, st, num_cus());
+        e = prefilter_write(pl.prefilter, *R, *S, w, pairs, capacity, st, num_cus());
     } else if (kind == JOIN_KIND_THETA_REGION) {
-        e = region_write(plan_region(R->n, S->n, p), *R, *S, *p, w, pairs, capacity, st);
+        e = region_write(pl.region, *R, *S, *p, w, pairs, capacity, st);
     } else {
-        const ThetaPlan pl = plan_theta(R->n, S->n, p);
-        e = theta_write(pl, *R, *S, *p, w, pairs, capacity, st);
+        e = theta_write(pl.theta, *R, *S, *p, w, pairs, capacity, st);
     }
     if (e != hipSuccess) return hip_fail(e, is_theta(kind) ? "theta write pass" : "hash write pass");
 #if JL_DEBUG
@@ -462,7 +467,7 @@ size_t join_workspace_bytes(int kind, int64_t nR, int64_t nS, const join_pred_t*
          kind != JOIN_KIND_HASH_PREFILTER) ||
         nR < 0 || nS < 0)
         return 0;
-    return ws_needed(kind, nR, nS, pred);
+    return plan_of(kind, nR, nS, pred).bytes;
 }
 
 int join_count(int kind, const join_rel_t* R, const join_rel_t* S, const join_pred_t* pred,
@@ -474,8 +479,9 @@ int join_count(int kind, const join_rel_t* R, const join_rel_t* S, const join_pr
         set_error("count is NULL");
         return JOIN_E_INVAL;
     }
-    if ((rc = check_ws(kind, R, S, pred, ws, ws_bytes)) != JOIN_OK) return rc;
-    return count_impl(kind, R, S, pred, ws, static_cast<hipStream_t>(stream), count);
+    const AnyPlan pl = plan_of(kind, R->n, S->n, pred);
+    if ((rc = check_ws(pl, ws, ws_bytes)) != JOIN_OK) return rc;
+    return count_impl(kind, pl, R, S, pred, ws, static_cast<hipStream_t>(stream), count);
 }
 
 int join_materialize(int kind, const join_rel_t* R, const join_rel_t* S, const join_pred_t* pred,
@@ -483,9 +489,10 @@ int join_materialize(int kind, const join_rel_t* R, const join_rel_t* S, const j
 {
     int rc = check_args(kind, R, S, pred);
     if (rc != JOIN_OK) return rc;
-    if ((rc = check_ws(kind, R, S, pred, ws, ws_bytes)) != JOIN_OK) return rc;
+    const AnyPlan pl = plan_of(kind, R->n, S->n, pred);
+    if ((rc = check_ws(pl, ws, ws_bytes)) != JOIN_OK) return rc;
     if (matches_last(kind, R, S, pred, ws)) {
-        if (g_last.stamp != plan_stamp_of(kind, R->n, S->n, pred)) {
+        if (g_last.stamp != pl.stamp) {
             set_error("the plan differs from the one join_count ran on this workspace (a tuning "
                       "knob changed in between); count again");
             return JOIN_E_INVAL;
@@ -496,7 +503,7 @@ int join_materialize(int kind, const join_rel_t* R, const join_rel_t* S, const j
             return JOIN_E_CAPACITY;
         }
     }
-    return write_impl(kind, R, S, pred, ws, pairs, capacity, static_cast<hipStream_t>(stream));
+    return write_impl(kind, pl, R, S, pred, ws, pairs, capacity, static_cast<hipStream_t>(stream));
 }
 
 static int one_shot(int kind, const join_rel_t* R, const join_rel_t* S, const join_pred_t* pred,
@@ -509,15 +516,16 @@ static int one_shot(int kind, const join_rel_t* R, const join_rel_t* S, const jo
         set_error("count is NULL");
         return JOIN_E_INVAL;
     }
-    if ((rc = check_ws(kind, R, S, pred, ws, ws_bytes)) != JOIN_OK) return rc;
+    const AnyPlan pl = plan_of(kind, R->n, S->n, pred);
+    if ((rc = check_ws(pl, ws, ws_bytes)) != JOIN_OK) return rc;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if ((rc = count_impl(kind, R, S, pred, ws, st, count)) != JOIN_OK) return rc;
+    if ((rc = count_impl(kind, pl, R, S, pred, ws, st, count)) != JOIN_OK) return rc;
     if (*count > capacity) {
         set_error("capacity %llu is below the exact count %llu", (unsigned long long)capacity,
                   (unsigned long long)*count);
         return JOIN_E_CAPACITY;
     }
-    return write_impl(kind, R, S, pred, ws, pairs, capacity, st);
+    return write_impl(kind, pl, R, S, pred, ws, pairs, capacity, st);
 }
 
 int join_hash(const join_rel_t* R, const join_rel_t* S, void* ws, size_t ws_bytes, int32_t* pairs,

@@ -99,6 +99,40 @@ __device__ __forceinline__ void publish_total(uint64_t* pub, uint64_t v)
     __hip_atomic_store(pub, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Waits for every memory access of the wave, and keeps the compiler from moving any across.
+__device__ __forceinline__ void drain()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+}
+
+// A value another workgroup of the same launch reads after this one arrived (arrive_last): the
+// atomic store reaches memory by itself, so after a drain() the arrival needs no release fence,
+// which would write back the XCD's whole L2.
+__device__ __forceinline__ void store_shared(uint64_t* p, uint64_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Whether this is the last of `total` workgroups to arrive (one thread calls it, workgroup id <
+// total).  Atomics on one address take about 10 ns each, 41 us for 4096 workgroups, so the
+// workgroups arrive at kArrivals counters on lines of their own, and the last at each at one
+// more.  A set is all zero before and after.
+constexpr uint32_t kArrivals = 32;
+constexpr uint32_t kArrivalWords = (kArrivals + 1) * 32;
+
+__device__ __forceinline__ bool arrive_last(uint32_t* set, uint32_t id, uint32_t total)
+{
+    uint32_t* mine = set + (id % kArrivals + 1) * 32;
+    const uint32_t expect = (total - id % kArrivals + kArrivals - 1) / kArrivals;
+    if (atomicAdd(mine, 1u) != expect - 1) return false;
+    atomicExch(mine, 0u);
+    if (atomicAdd(set, 1u) != min(total, kArrivals) - 1) return false;
+    atomicExch(set, 0u);
+    return true;
+}
+
 // DPP control codes (GFX9 encoding).
 constexpr int kDppRowShr1 = 0x111;
 constexpr int kDppRowShr2 = 0x112;

@@ -1993,7 +1993,7 @@ __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_m
         }
         wave_off[(size_t)u * kWaveRec + threadIdx.x] = threadIdx.x == 0 ? any : before;
         if (threadIdx.x == 0) {
-            counts[u] = sum;
+            store_shared(&counts[u], sum);
             if (any && rec_word) atomicOr(rec_word, 1u << kRecOrder);
         }
     }
@@ -2043,7 +2043,7 @@ __device__ void scan_counts_block(uint64_t* counts, uint32_t U, int64_t Umax, ui
     }
 }
 
-// done: NULL, or a zeroed arrival counter; then the last workgroup to arrive scans the counts
+// done: NULL, or a zeroed arrival set; then the last workgroup to arrive scans the counts
 // (Umax <= kFuseScanMax) and writes the sum to *total and, when pub is not NULL, to that pinned
 // host slot.
 template <bool AOS, bool SEMI, int B>
@@ -2118,13 +2118,12 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
         un = nx;
     }
     if (done) {
-        // Thread 0 wrote every count of this workgroup: a device-scope release orders them before
-        // its arrival.  Only the last to arrive acquires (an acquire also drops the L2 lines that
-        // workgroups still running on this XCD are reading).
+        // Thread 0 wrote every count of this workgroup.  Only the last to arrive acquires (an
+        // acquire also drops the L2 lines that workgroups still running on this XCD are reading).
         __shared__ uint32_t last;
         if (threadIdx.x == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            last = atomicAdd(done, 1u) == gridDim.x - 1;
+            drain();
+            last = arrive_last(done, blockIdx.x, gridDim.x);
         }
         __syncthreads();
         if (last) {
@@ -2500,7 +2499,7 @@ HashPlan hash_plan(int64_t nR, int64_t nS, int num_cus, int prebuilt_bits, bool 
         pl.off_grpS = off + (size_t)2 * pl.P * 4;
         pl.off_grpR = pl.off_grpS + (size_t)kGroups * pl.P * 4;
         pl.off_done = pl.off_grpR + (size_t)kGroups * pl.P * 4;  // cleared with the sizes and shares
-        off = align_up(pl.off_done + 4);
+        off = align_up(pl.off_done + kArrivalWords * 4);
         pl.off_baseR = off;
         off = align_up(off + (size_t)(pl.P + 1) * 4);
         pl.off_baseS = off;
@@ -2830,7 +2829,7 @@ hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
             // a prebuilt R keeps its sizes: only the S sizes and shares are cleared
             prof::Scope pz(st, "hash.plan");
             uint32_t* z = pre ? totS : totR;
-            const int64_t nz = reinterpret_cast<uint32_t*>(ws + pl.off_done) + 1 - z;
+            const int64_t nz = reinterpret_cast<uint32_t*>(ws + pl.off_done) + kArrivalWords - z;
             zero_u32_k<<<(unsigned)ceil_div(nz, 256), 256, 0, st>>>(z, nz);
         }
         e = hipGetLastError();

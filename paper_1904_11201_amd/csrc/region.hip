@@ -65,9 +65,8 @@ struct Hdr {
 // kCap rows, then these counters.
 constexpr int kCntExtra = 0;  // entries of the extra chunk list
 constexpr int kCntHist = 32;  // workgroups that finished the bucket sizes (an arrival set each)
-constexpr int kArrivals = 32; // counters of an arrival set, and the words between two of them
-constexpr int kCntCount = kCntHist + (kArrivals + 1) * 32;  // workgroups that finished counting
-constexpr int kCounters = kCntCount + (kArrivals + 1) * 32;
+constexpr int kCntCount = kCntHist + kArrivalWords;  // workgroups that finished counting
+constexpr int kCounters = kCntCount + kArrivalWords;
 
 struct Cols {
     const int32_t *a, *c, *rid;
@@ -109,25 +108,6 @@ __device__ __forceinline__ void block_range(int32_t& lo, int32_t& hi, int32_t* r
         hi = max(hi, red[W + w]);
     }
     __syncthreads();
-}
-
-// Waits for every memory access of the wave, and keeps the compiler from moving any across.
-__device__ __forceinline__ void drain()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0);
-    asm volatile("" ::: "memory");
-}
-
-// Whether this is the last of `total` workgroups to arrive (one thread calls it, workgroup id <
-// total).  Atomics on one address take about 10 ns each, 41 us for 4096 workgroups, so the
-// workgroups arrive at 32 counters on lines of their own, and the last at each at one more.
-__device__ __forceinline__ bool arrive_last(uint32_t* set, uint32_t id, uint32_t total)
-{
-    const uint32_t k = id % kArrivals;
-    const uint32_t expect = (total - k + kArrivals - 1) / kArrivals;
-    if (atomicAdd(&set[(k + 1) * 32], 1u) != expect - 1) return false;
-    return atomicAdd(set, 1u) == min(total, (uint32_t)kArrivals) - 1;
 }
 
 // Bits to shift a value span so that it falls below 2^bits.
@@ -909,8 +889,7 @@ __global__ __launch_bounds__(kJoinBlk) void region_count_k(Join g, uint64_t* __r
             g.wave_off[(uint64_t)u * kJoinWaves + w] = run;
             run += wsum[w];
         }
-        // an atomic store reaches memory by itself: no fence that writes back the L2 per workgroup
-        __hip_atomic_store(&g.counts[u], run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        store_shared(&g.counts[u], run);
         drain();
         last = arrive_last(g.done, u, g.U);
     }

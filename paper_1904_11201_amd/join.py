@@ -90,7 +90,8 @@ class Pred:
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the current stream's handle without building a Stream object (3 us a call)
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
@@ -110,12 +111,15 @@ def workspace(kind: int, nR: int, nS: int, pred: Pred | None = None, device="cud
 def join_count(kind: int, R: Relation, S: Relation, pred: Pred | None, ws: torch.Tensor,
                stream=None) -> int:
     """Exact number of output pairs (count pass + device scan; one 8-byte host read)."""
+    return _count(kind, R.c(), S.c(), _pred_ptr(pred), ws, _stream(stream))
+
+
+def _count(kind, rr, sr, pred, ws, stream) -> int:
     cnt = ctypes.c_uint64(0)
-    rr, sr = R.c(), S.c()
-    _check(_native.lib.join_count(kind, ctypes.byref(rr), ctypes.byref(sr), _pred_ptr(pred),
-                                  ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream(stream),
+    _check(_native.lib.join_count(kind, ctypes.byref(rr), ctypes.byref(sr), pred,
+                                  ctypes.c_void_p(ws.data_ptr()), ws.numel(), stream,
                                   ctypes.byref(cnt)))
-    return int(cnt.value)
+    return cnt.value
 
 
 def join_materialize(kind: int, R: Relation, S: Relation, pred: Pred | None, ws: torch.Tensor,
@@ -123,12 +127,15 @@ def join_materialize(kind: int, R: Relation, S: Relation, pred: Pred | None, ws:
     """Write pass into pairs ([capacity, 2] int32) from the state join_count left in ws."""
     if pairs.dtype != torch.int32 or not pairs.is_contiguous():
         raise ValueError("pairs must be a contiguous int32 tensor")
-    rr, sr = R.c(), S.c()
+    _materialize(kind, R.c(), S.c(), _pred_ptr(pred), ws, pairs, _stream(stream))
+
+
+def _materialize(kind, rr, sr, pred, ws, pairs, stream) -> None:
     cap = pairs.numel() // 2
-    _check(_native.lib.join_materialize(kind, ctypes.byref(rr), ctypes.byref(sr), _pred_ptr(pred),
+    _check(_native.lib.join_materialize(kind, ctypes.byref(rr), ctypes.byref(sr), pred,
                                         ctypes.c_void_p(ws.data_ptr()), ws.numel(),
                                         ctypes.c_void_p(pairs.data_ptr()) if cap else None, cap,
-                                        _stream(stream)))
+                                        stream))
 
 
 def join_hash(R: Relation, S: Relation, ws: torch.Tensor, pairs: torch.Tensor | None,
@@ -248,9 +255,12 @@ def prof_wall_clock_hz() -> float:
 def _exact(kind, R, S, pred, ws, stream):
     if ws is None:
         ws = workspace(kind, R.n, S.n, pred, device=R.key.device)
-    n = join_count(kind, R, S, pred, ws, stream)
+    # the arguments are made once for both calls: the GPU is idle from the count's arrival until
+    # the write pass is launched
+    rr, sr, pr, st = R.c(), S.c(), _pred_ptr(pred), _stream(stream)
+    n = _count(kind, rr, sr, pr, ws, st)
     out = torch.empty((n, 2), dtype=torch.int32, device=R.key.device)
-    join_materialize(kind, R, S, pred, ws, out, stream)
+    _materialize(kind, rr, sr, pr, ws, out, st)
     return out
 
 
@@ -450,27 +460,32 @@ class ResidentBuild:
         return torch.empty(self.workspace_bytes(nS), dtype=torch.uint8, device=device)
 
     def count(self, S: Relation, ws: torch.Tensor, stream=None) -> int:
+        return self._count(S.c(), ws, _stream(stream))
+
+    def _count(self, sr, ws, stream) -> int:
         cnt = ctypes.c_uint64(0)
-        sr = S.c()
         _check(_native.lib.join_probe_count(ctypes.byref(self.desc), ctypes.c_void_p(self.buf.data_ptr()),
                                             ctypes.byref(sr), ctypes.c_void_p(ws.data_ptr()), ws.numel(),
-                                            _stream(stream), ctypes.byref(cnt)))
-        return int(cnt.value)
+                                            stream, ctypes.byref(cnt)))
+        return cnt.value
 
     def materialize(self, S: Relation, ws: torch.Tensor, pairs: torch.Tensor, stream=None) -> None:
         if pairs.dtype != torch.int32 or not pairs.is_contiguous():
             raise ValueError("pairs must be a contiguous int32 tensor")
+        self._materialize(S.c(), ws, pairs, _stream(stream))
+
+    def _materialize(self, sr, ws, pairs, stream) -> None:
         cap = pairs.numel() // 2
-        sr = S.c()
         _check(_native.lib.join_probe_materialize(
             ctypes.byref(self.desc), ctypes.c_void_p(self.buf.data_ptr()), ctypes.byref(sr),
             ctypes.c_void_p(ws.data_ptr()), ws.numel(),
-            ctypes.c_void_p(pairs.data_ptr()) if cap else None, cap, _stream(stream)))
+            ctypes.c_void_p(pairs.data_ptr()) if cap else None, cap, stream))
 
     def probe(self, S: Relation, stream=None) -> torch.Tensor:
         """R ⋈ S with R from this build: the exact-size [count, 2] int32 pairs."""
         ws = self.workspace(S.n, device=self.buf.device)
-        n = self.count(S, ws, stream)
+        sr, st = S.c(), _stream(stream)
+        n = self._count(sr, ws, st)
         out = torch.empty((n, 2), dtype=torch.int32, device=self.buf.device)
-        self.materialize(S, ws, out, stream)
+        self._materialize(sr, ws, out, st)
         return out
