@@ -185,6 +185,7 @@ struct LastCount {
     void* ws;
     uint64_t count;
     uint64_t stamp;  // plan stamp of that count pass
+    bool crowded;    // whether it may have found crowded units (hash_write)
 };
 thread_local LastCount g_last{};
 
@@ -297,8 +298,18 @@ hipError_t wait_published(hipStream_t st, uint64_t* count)
 uint64_t* arm_published_slot()
 {
     uint64_t* pub = published_slot();
-    if (pub) *pinned_slot() = kUnpublished;
+    if (pub) {
+        pinned_slot()[0] = kUnpublished;
+        pinned_slot()[1] = 0;
+    }
     return pub;
+}
+
+// Whether the hash count pass whose total was taken from the slot found crowded units (true when
+// that is not known).
+bool crowded_said(const uint64_t* pub)
+{
+    return !pub || static_cast<volatile uint64_t*>(pinned_slot())[1] != 0;
 }
 
 // The exact total of the count pass just enqueued: from the slot, or copied from `src`.
@@ -362,6 +373,7 @@ int count_impl(int kind, const AnyPlan& pl, const join_rel_t* R, const join_rel_
                const join_pred_t* p, void* ws, hipStream_t st, uint64_t* count)
 {
     g_last.valid = false;
+    g_last.crowded = true;
     if (R->n == 0 || S->n == 0) {
         *count = 0;
     } else {
@@ -382,6 +394,7 @@ int count_impl(int kind, const AnyPlan& pl, const join_rel_t* R, const join_rel_
         if (e != hipSuccess) return hip_fail(e, is_theta(kind) ? "theta count pass" : "hash count pass");
         e = take_total(pub, w + total_at, st, count);
         if (e != hipSuccess) return hip_fail(e, "reading the exact total");
+        g_last.crowded = crowded_said(pub);
 #if JL_DEBUG
         e = debug_fingerprint(kind, R, S, p, w, kDebugFpOffset, st);
         if (e != hipSuccess) return hip_fail(e, "checking build: fingerprint");
@@ -399,7 +412,8 @@ int count_impl(int kind, const AnyPlan& pl, const join_rel_t* R, const join_rel_
 }
 
 int write_impl(int kind, const AnyPlan& pl, const join_rel_t* R, const join_rel_t* S,
-               const join_pred_t* p, void* ws, int32_t* pairs, uint64_t capacity, hipStream_t st)
+               const join_pred_t* p, void* ws, int32_t* pairs, uint64_t capacity, hipStream_t st,
+               bool crowded)
 {
     if (R->n == 0 || S->n == 0) return JOIN_OK;
     if (capacity > 0 && !pairs) {
@@ -427,9 +441,9 @@ int write_impl(int kind, const AnyPlan& pl, const join_rel_t* R, const join_rel_
     }
 #endif
     if (kind == JOIN_KIND_HASH) {
-        e = hash_write(pl.hash, *R, *S, w, pairs, capacity, st);
+        e = hash_write(pl.hash, *R, *S, w, pairs, capacity, st, nullptr, crowded);
     } else if (kind == JOIN_KIND_HASH_PREFILTER) {
-        e = prefilter_write(pl.prefilter, *R, *S, w, pairs, capacity, st, num_cus());
+        e = prefilter_write(pl.prefilter, *R, *S, w, pairs, capacity, st, num_cus(), crowded);
     } else if (kind == JOIN_KIND_THETA_REGION) {
         e = region_write(pl.region, *R, *S, *p, w, pairs, capacity, st);
     } else {
@@ -491,7 +505,9 @@ int join_materialize(int kind, const join_rel_t* R, const join_rel_t* S, const j
     if (rc != JOIN_OK) return rc;
     const AnyPlan pl = plan_of(kind, R->n, S->n, pred);
     if ((rc = check_ws(pl, ws, ws_bytes)) != JOIN_OK) return rc;
+    bool crowded = true;  // unless the count pass ran on this thread and said otherwise
     if (matches_last(kind, R, S, pred, ws)) {
+        crowded = g_last.crowded;
         if (g_last.stamp != pl.stamp) {
             set_error("the plan differs from the one join_count ran on this workspace (a tuning "
                       "knob changed in between); count again");
@@ -503,7 +519,7 @@ int join_materialize(int kind, const join_rel_t* R, const join_rel_t* S, const j
             return JOIN_E_CAPACITY;
         }
     }
-    return write_impl(kind, pl, R, S, pred, ws, pairs, capacity, static_cast<hipStream_t>(stream));
+    return write_impl(kind, pl, R, S, pred, ws, pairs, capacity, static_cast<hipStream_t>(stream), crowded);
 }
 
 static int one_shot(int kind, const join_rel_t* R, const join_rel_t* S, const join_pred_t* pred,
@@ -525,7 +541,7 @@ static int one_shot(int kind, const join_rel_t* R, const join_rel_t* S, const jo
                   (unsigned long long)*count);
         return JOIN_E_CAPACITY;
     }
-    return write_impl(kind, pl, R, S, pred, ws, pairs, capacity, st);
+    return write_impl(kind, pl, R, S, pred, ws, pairs, capacity, st, g_last.crowded);
 }
 
 int join_hash(const join_rel_t* R, const join_rel_t* S, void* ws, size_t ws_bytes, int32_t* pairs,
@@ -674,6 +690,7 @@ static thread_local struct {
     void* ws;
     uint64_t count;
     uint64_t stamp;
+    bool crowded;
 } g_last_probe{};
 
 size_t join_build_bytes(int64_t nR)
@@ -757,6 +774,7 @@ int join_probe_count(const join_build_t* desc, const void* build, const join_rel
         if (e != hipSuccess) return hip_fail(e, "probe count pass");
         const hipError_t er = take_total(pub, ws, st, count);
         if (er != hipSuccess) return hip_fail(er, "reading the exact total");
+        g_last_probe.crowded = crowded_said(pub);
     }
     g_last_probe.valid = true;
     g_last_probe.build = build;
@@ -782,8 +800,10 @@ int join_probe_materialize(const join_build_t* desc, const void* build, const jo
         set_error("pairs is NULL with capacity %llu", (unsigned long long)capacity);
         return JOIN_E_INVAL;
     }
+    bool crowded = true;  // unless the count pass ran on this thread and said otherwise
     if (g_last_probe.valid && g_last_probe.build == build && g_last_probe.ws == ws &&
         same_rel(g_last_probe.S, *S)) {
+        crowded = g_last_probe.crowded;
         if (g_last_probe.stamp != pl.stamp) {
             set_error("the plan differs from the one join_probe_count ran on this workspace (a "
                       "tuning knob changed in between); count again");
@@ -800,7 +820,7 @@ int join_probe_materialize(const join_build_t* desc, const void* build, const jo
     R.n = b.nR;
     const RView v = build_view(b, build);
     const hipError_t e = hash_write(pl, R, *S, static_cast<char*>(ws), pairs, capacity,
-                                    static_cast<hipStream_t>(stream), &v);
+                                    static_cast<hipStream_t>(stream), &v, crowded);
     return e == hipSuccess ? JOIN_OK : hip_fail(e, "probe write pass");
 }
 

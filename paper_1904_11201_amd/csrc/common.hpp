@@ -72,6 +72,14 @@ using i32x4 = int32_t __attribute__((ext_vector_type(4)));
 using i32x4_any = int32_t __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ i32x4 load4(gptr<int32_t> p) { return *(const __attribute__((address_space(1))) i32x4_any*)p; }
 
+// 8-byte load of a tuple through a global pointer.
+using i32x2 = int32_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int2 load2(const int2* p)
+{
+    const i32x2 v = *(const __attribute__((address_space(1))) i32x2*)p;
+    return make_int2(v.x, v.y);
+}
+
 // Plan stamps.  Every workspace starts with a 256-byte header.  The count pass records at
 // kStampOffset a signature of the plan it ran (sizes, fan-out, capacities, tiles: how the work
 // was cut up), and the write pass, which plans again from its own arguments and the tuning

@@ -828,6 +828,9 @@ __device__ __forceinline__ uint32_t plan_part(const PartPlan& q, int p, PartInfo
 constexpr int kRecBitsShift = 24;
 constexpr int kRecShared = 28;
 constexpr int kRecOrder = 29;
+// Set by the count pass for a unit whose table was crowded: write_crowded_k writes its pairs, and
+// the write pass takes it as empty.
+constexpr int kRecCrowded = 30;
 __host__ __device__ __forceinline__ uint4 unit_rec(const PartInfo& pi, uint32_t local, uint32_t cap)
 {
     const uint32_t rc = local / pi.nSs;
@@ -1100,6 +1103,7 @@ struct Unit {
     int bits;     // fan-out of the unit's join: the table position uses the hash bits below it
     bool shared;  // other units (other R chunks) probe the same S slice
     bool order;   // partitioned joins, after the count pass: the table needs canonical order
+    bool crowded; // partitioned joins, after the count pass: kRecCrowded
 };
 
 __device__ __forceinline__ Unit unit_of(uint4 r)
@@ -1112,6 +1116,7 @@ __device__ __forceinline__ Unit unit_of(uint4 r)
     o.bits = (int)((r.y >> kRecBitsShift) & ((1u << (kRecShared - kRecBitsShift)) - 1));
     o.shared = ((r.y >> kRecShared) & 1u) != 0;
     o.order = ((r.y >> kRecOrder) & 1u) != 0;
+    o.crowded = ((r.y >> kRecCrowded) & 1u) != 0;
     return o;
 }
 
@@ -1174,6 +1179,10 @@ __device__ __forceinline__ void choices(uint32_t h, int bits, uint32_t nb, uint3
 // path's raw keys, batch joins of fan-out 0 or 1) compare against the claim counters.
 constexpr uint32_t kOverflow = 1u << 30;
 
+// The dynamic LDS of the count and write passes (the table), at file scope for the functions that
+// are not inlined.
+extern __shared__ uint4 join_lds[];
+
 struct Table {
     const uint4* keys;    // [nb]: the 4 keys of each bucket
     const uint4* rids;    // [nb]: their rids (write pass only)
@@ -1187,6 +1196,15 @@ struct Table {
 __host__ __device__ constexpr size_t table_lds(uint32_t cap, bool rids)
 {
     return (size_t)table_buckets(cap) * (rids ? 36 : 20) + 64;
+}
+
+// LDS bytes of the sorted entries (with rids) of a crowded unit in the write pass; the count pass's
+// sorted keys, half of that, always fit its table.
+__host__ __device__ constexpr size_t sorted_lds(uint32_t cap)
+{
+    size_t N = 1;
+    while (N < cap) N *= 2;
+    return N * 8;
 }
 
 // One R chunk held in registers between its load and its insertion.
@@ -1272,9 +1290,17 @@ __device__ __forceinline__ uint32_t marker_hash(const JoinGeom& g, const Unit& u
     return HASHED && un.bits >= 2 ? (uint32_t)g.rt[un.rBeg].x : 0u;
 }
 
+// crowded (count pass): a word of LDS, zero on entry; set when an entry found no slot within
+// kWalkMax buckets of its own, because a key has hundreds of entries in the chunk: the walk of
+// every entry and probe that meets its buckets would pass them all (67 ms for a build of 0.8M Zipf
+// keys).  Such a unit is joined by its sorted entries instead (see below), in both passes.  The
+// write pass, which never builds the table of a unit found crowded, walks without a limit: its
+// table may come out a little more crowded than the count pass's, as the inserts race.
+constexpr uint32_t kWalkMax = 64;
+
 template <bool RIDS, bool HASHED, int B, bool CLEARED = false>
 __device__ __forceinline__ Table insert_chunk(const JoinGeom& g, const Unit& un, const Chunk<RIDS>& c,
-                                              uint4* lds, uint32_t (&pos)[kBuildItems])
+                                              uint4* lds, uint32_t (&pos)[kBuildItems], uint32_t* crowded = nullptr)
 {
     const int tid = threadIdx.x;
     const uint32_t nb = table_buckets(un.rN);
@@ -1302,10 +1328,15 @@ __device__ __forceinline__ Table insert_chunk(const JoinGeom& g, const Unit& un,
                 old = atomicAdd(&cnt[b], 1u);
                 if (old >= (uint32_t)kSlots) {
                     b = b2;
+                    uint32_t steps = 0;
                     do {  // ends: 4 * nb slots > rN entries
                         b = next_bucket(b, nb);
                         old = atomicAdd(&cnt[b], 1u);
-                    } while (old >= (uint32_t)kSlots);
+                    } while (old >= (uint32_t)kSlots && (RIDS || ++steps < kWalkMax));
+                    if (!RIDS && old >= (uint32_t)kSlots) {  // goes anywhere: the table is not used
+                        *crowded = 1;
+                        old = 0;
+                    }
                 }
             }
             keys[b * kSlots + old] = c.k[i];
@@ -1586,9 +1617,8 @@ __device__ __forceinline__ void emit_many(const Table& t, int bits, uint32_t x, 
 // the probe loop.
 constexpr int kManyQ = 64;  // a whole wave's worth: one tuple index of a round always fits
 
-// The write pass's LDS: its dynamic table, and the queues at file scope, so that the emitting
-// function below, which is not inlined, still addresses them as LDS.
-extern __shared__ uint4 write_lds[];
+// The write pass's queues, at file scope like the table, so that the emitting function below, which
+// is not inlined, still addresses them as LDS.
 __shared__ uint4 write_manyq[kJoinBlock / kWave * kManyQ];       // 1024-thread workgroups
 __shared__ uint4 write_manyq_b[kBatchBlock / kWave * kManyQ];    // 512-thread workgroups
 
@@ -1610,9 +1640,9 @@ __device__ __attribute__((noinline)) uint64_t flush_many(uint32_t nb, int bits, 
                                                          uint64_t at, int2* __restrict__ out, uint64_t cap)
 {
     Table t;
-    t.keys = write_lds;
-    t.rids = write_lds + nb;
-    t.cnt = reinterpret_cast<const uint32_t*>(write_lds + 2 * nb);
+    t.keys = join_lds;
+    t.rids = join_lds + nb;
+    t.cnt = reinterpret_cast<const uint32_t*>(join_lds + 2 * nb);
     t.nb = nb;
     t.marked = MARKED;
     const uint4* q = manyq<B>() + wv * kManyQ;
@@ -1873,6 +1903,122 @@ __device__ __forceinline__ void load_keys(const JoinGeom& g, const Unit& un, uin
     load_keys_of<AOS, B>(g, un, e0, xs);
 }
 
+// ------------------------------------------------------------------------ crowded units --
+// A chunk with keys of hundreds of entries is sorted in LDS instead of hashed: the matches of a
+// probe are then one run, found by two binary searches whatever its length.  Sorting takes about
+// 15 us for 9K entries and a probe 28 LDS reads, so only units whose table would be walked take
+// this path; the code is kept out of the kernels' loops.
+constexpr uint32_t kWaveRun = 64;  // longer runs are written by the whole wave
+
+// What the functions below need of their unit, in LDS: they are not inlined, and arguments by
+// reference would put the kernels' own copies into scratch memory.
+struct CrowdedUnit {
+    const int2 *rt, *st;
+    const int32_t *rk, *rr, *sk, *sr;
+    uint32_t* semi;  // NULL: not recorded
+    uint32_t rBeg, rN, sBeg, sN;
+};
+__shared__ CrowdedUnit crowded_unit;
+
+// Thread 0 fills it in; every thread passes the barrier.
+__device__ __forceinline__ void set_crowded(const JoinGeom& g, const Unit& un)
+{
+    if (threadIdx.x == 0)
+        crowded_unit = CrowdedUnit{g.rt, g.st, g.rk, g.rr, g.sk, g.sr, un.shared ? nullptr : g.semi,
+                                   un.rBeg, un.rN, un.sBeg, un.sN};
+    __syncthreads();
+}
+
+// Sorts v[0, N), N a power of two, by a bitonic network over B threads.
+template <int B, typename T>
+__device__ void bitonic(T* v, uint32_t N)
+{
+    for (uint32_t k = 2; k <= N; k *= 2)
+        for (uint32_t j = k / 2; j > 0; j /= 2) {
+            __syncthreads();
+            for (uint32_t i = threadIdx.x; i < N / 2; i += B) {
+                const uint32_t x = 2 * j * (i / j) + i % j, y = x + j;
+                const T a = v[x], b = v[y];
+                if ((a > b) == ((x & k) == 0)) {
+                    v[x] = b;
+                    v[y] = a;
+                }
+            }
+        }
+    __syncthreads();
+}
+
+__host__ __device__ constexpr uint32_t pow2_at_least(uint32_t n)
+{
+    uint32_t N = 1;
+    while (N < n) N *= 2;
+    return N;
+}
+
+// The chunk of a unit sorted in LDS: its keys, or with RIDS key << 32 | rid (rids as signed values
+// ascending).  Called by the whole workgroup, after a barrier.  join_lds: the dynamic LDS.
+template <bool AOS, bool RIDS, int B>
+__device__ __forceinline__ void sort_chunk()
+{
+    const CrowdedUnit& u = crowded_unit;
+    const uint32_t rN = uniform(u.rN), N = pow2_at_least(rN);
+    for (uint32_t e = threadIdx.x; e < N; e += B) {
+        const uint32_t i = u.rBeg + (e < rN ? e : 0u);
+        uint32_t k, r = 0;
+        if constexpr (AOS) {
+            const int2 t = load2(u.rt + i);
+            k = (uint32_t)t.x;
+            r = (uint32_t)t.y;
+        } else {
+            k = (uint32_t)as_global(u.rk)[i];
+            if constexpr (RIDS) r = u.rr ? (uint32_t)as_global(u.rr)[i] : i;
+        }
+        if constexpr (RIDS)
+            reinterpret_cast<uint64_t*>(join_lds)[e] = e < rN ? (uint64_t)k << 32 | (r ^ 0x80000000u) : ~0ull;
+        else
+            reinterpret_cast<uint32_t*>(join_lds)[e] = e < rN ? k : ~0u;
+    }
+    if constexpr (RIDS) bitonic<B>(reinterpret_cast<uint64_t*>(join_lds), N);
+    else bitonic<B>(reinterpret_cast<uint32_t*>(join_lds), N);
+}
+
+// The run of key x among the n sorted entries.
+template <bool RIDS>
+__device__ __forceinline__ void run_of(uint32_t n, uint32_t x, uint32_t& lo, uint32_t& hi)
+{
+    auto key = [&](uint32_t i) {
+        return RIDS ? reinterpret_cast<const uint32_t*>(join_lds)[2 * i + 1]
+                    : reinterpret_cast<const uint32_t*>(join_lds)[i];
+    };
+    uint32_t a = 0, b = n;
+    while (a < b) {
+        const uint32_t m = (a + b) / 2;
+        if (key(m) < x) a = m + 1;
+        else b = m;
+    }
+    lo = a;
+    b = n;
+    while (a < b) {
+        const uint32_t m = (a + b) / 2;
+        if (key(m) <= x) a = m + 1;
+        else b = m;
+    }
+    hi = a;
+}
+
+// Probe row e of the unit: its key and its rid.
+template <bool AOS>
+__device__ __forceinline__ int2 probe_row(uint32_t e)
+{
+    const CrowdedUnit& u = crowded_unit;
+    const uint32_t i = u.sBeg + e;
+    if constexpr (AOS) {
+        return load2(u.st + i);
+    } else {
+        return make_int2(as_global(u.sk)[i], u.sr ? as_global(u.sr)[i] : (int32_t)i);
+    }
+}
+
 // Count pass.  A workgroup walks the units of its sequence (Sched).  The S keys come in
 // batches of kCountBatch per thread through two register buffers used in turn: while one batch
 // is probed the next is in flight, and the next unit's first batch while the last one probes.
@@ -1940,15 +2086,48 @@ __device__ __forceinline__ uint32_t count_batch(const Table& t, const Unit& un, 
     return count_batch_of<AOS, MARKED, false, SEMI, B>(t, un, e0, xs, multi, many, sm);
 }
 
+// The count pass of a crowded unit (lane totals as count_batch leaves them).
+struct UnitCount {
+    uint64_t cnt, many;
+    bool multi;
+    uint32_t semi;  // uniform: the wave's probe rows with matches
+};
+
+template <bool AOS, bool SEMI, int B>
+__device__ __attribute__((noinline)) UnitCount count_crowded()
+{
+    sort_chunk<AOS, false, B>();
+    const uint32_t rN = uniform(crowded_unit.rN), sN = uniform(crowded_unit.sN);
+    UnitCount c{0, 0, false, 0};
+    Semi sm{SEMI ? crowded_unit.semi : nullptr, crowded_unit.sBeg, 0u};
+    const int wv = (int)(threadIdx.x / kWave);
+    for (uint32_t e0 = 0; e0 < sN; e0 += B) {
+        const uint32_t e = e0 + threadIdx.x;
+        uint32_t lo = 0, hi = 0;
+        if (e < sN) run_of<false>(rN, (uint32_t)probe_row<AOS>(e).x, lo, hi);
+        const uint32_t m = hi - lo;
+        c.cnt += m;
+        c.many += m > 2 ? m : 0u;
+        c.multi = c.multi || m > (uint32_t)kEmitSort;
+        if (SEMI && sm.rows) {  // uniform
+            const uint64_t bm = ballot(m > 0);
+            if (m > 0) sm.rows[semi_slot(sm.sBeg, sm.k + mask_rank(bm), wv)] = sm.sBeg + e;
+            sm.k += (uint32_t)__builtin_popcountll(bm);
+        }
+    }
+    c.semi = sm.k;
+    return c;
+}
+
 // Each wave of the count and write passes takes the same probe tuples of a unit: those at
 // positions e with (e mod kJoinBlock) / 64 equal to its index.  The count pass records, per
 // unit and wave, where the wave's pairs start inside the unit's output range, so the write pass
 // needs no shared cursor and every pair lands at a position that depends on the input and the
 // plan alone.  Entry 0 of a unit (wave 0 starts at 0) instead holds 1 when some probe of the
-// unit has more than kEmitSort entries in its table.  Inside a wave's range the pairs of probes
-// with at most two matches come first, in (batch, tuple, lane) order, then those of probes with
-// more, in the order the wave queued them; the second half of the unit's record holds, per wave,
-// where that second block starts inside the wave's range.
+// unit has more than kEmitSort entries in its table, plus 2 when the table was crowded.  Inside a
+// wave's range the pairs of probes with at most two matches come first, in (batch, tuple, lane)
+// order, then those of probes with more, in the order the wave queued them; the second half of the
+// unit's record holds, per wave, where that second block starts inside the wave's range.
 constexpr int kJoinWaves = kJoinBlock / kWave;
 constexpr int kWaveRec = 2 * kJoinWaves;  // uint64 entries per unit in the wave record
 constexpr int kWaveHalf = kJoinWaves;     // its second half (a 512-thread workgroup uses 8 + 8)
@@ -1956,6 +2135,7 @@ constexpr int kWaveHalf = kJoinWaves;     // its second half (a 512-thread workg
 constexpr size_t kWriteStaticLds = (size_t)kJoinWaves * kManyQ * 16;
 constexpr size_t kBatchStaticLds = (size_t)(kBatchBlock / kWave) * kManyQ * 16;
 static_assert(table_lds(kMaxCap, true) + kWriteStaticLds <= 160 * 1024, "write pass LDS");
+static_assert(sorted_lds(kMaxCap) + kJoinBlock * 4 + 256 <= 160 * 1024, "crowded units' LDS");
 static_assert(2 * (table_lds(kBatchCap, true) + kBatchStaticLds + 256) <= 160 * 1024,
               "two batch write workgroups per CU");
 
@@ -1970,7 +2150,7 @@ template <int B, typename Between>
 __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_many, bool multi,
                                             uint32_t semi_rows, uint32_t u, uint64_t* __restrict__ counts,
                                             uint64_t* __restrict__ wave_off, uint64_t* sh, uint32_t* rec_word,
-                                            Between between)
+                                            bool crowded, Between between)
 {
     const uint64_t wt = wave_sum64(lane_total);
     const uint64_t wmany = wave_sum64(lane_many);
@@ -1991,10 +2171,11 @@ __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_m
             sum += c;
             any |= v >> 63;
         }
-        wave_off[(size_t)u * kWaveRec + threadIdx.x] = threadIdx.x == 0 ? any : before;
+        wave_off[(size_t)u * kWaveRec + threadIdx.x] = threadIdx.x == 0 ? any | (crowded ? 2u : 0u) : before;
         if (threadIdx.x == 0) {
             store_shared(&counts[u], sum);
-            if (any && rec_word) atomicOr(rec_word, 1u << kRecOrder);
+            const uint32_t flags = (any ? 1u << kRecOrder : 0u) | (crowded ? 1u << kRecCrowded : 0u);
+            if (flags && rec_word) atomicOr(rec_word, flags);
         }
     }
     between();  // every wave has finished the unit's probes
@@ -2052,12 +2233,14 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
                                            uint32_t* __restrict__ done, uint64_t* __restrict__ total,
                                            uint64_t* pub)
 {
-    extern __shared__ uint4 tab[];
+    uint4* const tab = join_lds;
     __shared__ uint64_t wsum[B / kWave + 1];
     constexpr uint32_t kB = B * kCountBatch;  // keys per batch
     const uint32_t U = unit_total(g);
     if (g.stamp_at && blockIdx.x == 0 && threadIdx.x == 0) *g.stamp_at = g.stamp;  // for the write pass
     __shared__ uint32_t slot[2];
+    __shared__ uint32_t crowded;
+    if (threadIdx.x == 0) crowded = 0;
     Sched sc = make_sched(U, false, g.sched);
     uint32_t u, nxi;
     sched_start(sc, u, nxi, slot);
@@ -2077,7 +2260,7 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
         Chunk<false> ch;
         load_chunk<AOS, false, B>(g, un, ch);
         uint32_t pos[kBuildItems];
-        const Table t = insert_chunk<false, AOS, B, true>(g, un, ch, tab, pos);
+        const Table t = insert_chunk<false, AOS, B, true>(g, un, ch, tab, pos, &crowded);
         __builtin_amdgcn_s_waitcnt(0);  // nothing in flight enters the batch loop
         const bool more = nxi < U;
         const Unit nx = more ? decode_unit<AOS>(g, nxi) : Unit{};
@@ -2097,9 +2280,23 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
                 many += (uint64_t)ma + mb;
             }
         };
-        if (AOS && t.marked) batches(std::true_type{});
-        else batches(std::false_type{});
-        if (un.sN == 0 && more) load_keys<AOS, B>(g, nx, 0, xa);
+        const bool by_sort = uniform(crowded) != 0;
+        if (by_sort) {
+            set_crowded(g, un);
+            // told to the host at once: it is read with the total, which is published later
+            if (pub && threadIdx.x == 0)
+                __hip_atomic_store(pub + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            const UnitCount c = count_crowded<AOS, SEMI, B>();
+            cnt = c.cnt;
+            many = c.many;
+            multi = c.multi;
+            sm.k = c.semi;
+            if (more) load_keys<AOS, B>(g, nx, 0, xa);
+        } else {
+            if (AOS && t.marked) batches(std::true_type{});
+            else batches(std::false_type{});
+            if (un.sN == 0 && more) load_keys<AOS, B>(g, nx, 0, xa);
+        }
         sched_put(sc, need, tk, slot);
         // a partitioned join's record is read only by this workgroup in this pass (it decoded it
         // before), so the flag can go into it
@@ -2108,8 +2305,9 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
         // comes from the next unit's first probe keys, loaded during the last batch: every hash
         // of a partition has the partition's top bits (a unit without probe keys never reads
         // its table, so its marker does not matter).
-        unit_totals<B>(cnt, many, multi, sm.k, u, counts, wave_off, wsum, rec_word, [&] {
+        unit_totals<B>(cnt, many, multi, sm.k, u, counts, wave_off, wsum, rec_word, by_sort, [&] {
             if (more) clear_table<false, AOS, B>(nx, xa[0], tab);
+            if (threadIdx.x == 0) crowded = 0;
         });  // ends with a barrier
         const uint32_t nn = sched_after(sc, need, nxi, slot);
         u = nxi;
@@ -2144,7 +2342,26 @@ template <bool PART>
 __device__ __forceinline__ bool unit_order(const uint64_t* wave_off, uint32_t v, const Unit& n)
 {
     if constexpr (PART) return n.order;
-    else return as_const(wave_off)[(size_t)v * kWaveRec] != 0;
+    else return (as_const(wave_off)[(size_t)v * kWaveRec] & 1) != 0;
+}
+
+// Whether the count pass found unit u (record n) crowded: entry 0 of its wave_off record has 2
+// added, a partitioned join's record the flag.
+template <bool PART>
+__device__ __forceinline__ bool unit_crowded(const uint64_t* wave_off, uint32_t u, const Unit& n)
+{
+    if constexpr (PART) return n.crowded;
+    else return (as_const(wave_off)[(size_t)u * kWaveRec] & 2) != 0;
+}
+
+// Unit u as the write pass takes it: a crowded one is empty when write_crowded_k follows; when the
+// host did not expect one, its table is built and walked after all.
+template <bool PART>
+__device__ __forceinline__ Unit decode_written(const JoinGeom& g, const uint64_t* wave_off, uint32_t u)
+{
+    Unit n = decode_unit<PART>(g, u);
+    if (g.crowded_apart && unit_crowded<PART>(wave_off, u, n)) n.rN = n.sN = 0;
+    return n;
 }
 
 // Whether any unit of [u, end) that shares unit u's R chunk had a probe with more than
@@ -2156,11 +2373,95 @@ __device__ __forceinline__ bool chunk_needs_order(const JoinGeom& g, const uint6
 {
     bool any = unit_order<PART>(wave_off, u, un);
     for (uint32_t v = u + 1; v < end && !any; ++v) {
-        const Unit n = decode_unit<PART>(g, v);
+        const Unit n = decode_written<PART>(g, wave_off, v);
         if (!same_chunk(n, un)) break;
         any = unit_order<PART>(wave_off, v, n);
     }
     return any;
+}
+
+// The pairs of a crowded unit: this wave's pairs of probes with one or two matches from `cursor` on,
+// those of probes with more from `cmany` on; returns how many of both together.
+template <bool AOS, int B>
+__device__ __forceinline__ uint64_t write_crowded(uint64_t cursor, uint64_t cmany, int2* __restrict__ out,
+                                                  uint64_t cap)
+{
+    sort_chunk<AOS, true, B>();
+    const uint32_t rN = uniform(crowded_unit.rN), sN = uniform(crowded_unit.sN);
+    const uint64_t at0 = cursor + cmany;
+    const uint32_t* w = reinterpret_cast<const uint32_t*>(join_lds);
+    auto pair = [&](uint32_t i, int32_t srid) { return make_int2((int32_t)(w[2 * i] ^ 0x80000000u), srid); };
+    for (uint32_t e0 = 0; e0 < sN; e0 += B) {
+        const uint32_t e = e0 + threadIdx.x;
+        uint32_t lo = 0, hi = 0;
+        int2 p = make_int2(0, 0);
+        if (e < sN) {
+            p = probe_row<AOS>(e);
+            run_of<true>(rN, (uint32_t)p.x, lo, hi);
+        }
+        const uint32_t m = hi - lo, few = m <= 2 ? m : 0u, many = m > 2 ? m : 0u;
+        const uint32_t fi = wave_incl_scan(few), mi = wave_incl_scan(many);
+        for (uint32_t k = 0; k < few; ++k)
+            if (cursor + fi - few + k < cap) put_pair(&out[cursor + fi - few + k], pair(lo + k, p.y));
+        if (many <= kWaveRun)
+            for (uint32_t k = 0; k < many; ++k)
+                if (cmany + mi - many + k < cap) put_pair(&out[cmany + mi - many + k], pair(lo + k, p.y));
+        for (uint64_t b = ballot(many > kWaveRun); b; b &= b - 1) {
+            const int q = __builtin_ctzll(b);
+            const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)many, q);
+            const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)lo, q);
+            const uint64_t at = cmany + (uint32_t)__builtin_amdgcn_readlane((int)(mi - many), q);
+            const int32_t srid = __builtin_amdgcn_readlane(p.y, q);
+            for (uint32_t k = lane_id(); k < n; k += kWave)
+                if (at + k < cap) put_pair(&out[at + k], pair(first + k, srid));
+        }
+        cursor += (uint32_t)__builtin_amdgcn_readlane((int)fi, kWave - 1);
+        cmany += (uint32_t)__builtin_amdgcn_readlane((int)mi, kWave - 1);
+    }
+    return cursor + cmany - at0;
+}
+
+// The write pass of the crowded units, which join_write_k leaves out (inside it this code's
+// registers cost every other unit 5 to 10%).  Launched when the count pass said there are any, or
+// when its word about it is not at hand.  Workgroup b looks through units b, b + grid, ..., B at a
+// time, and writes those that are flagged (crowded units lie next to each other, so neighbouring
+// units go to different workgroups).
+template <bool AOS, int B>
+__global__ JL_WRITE_ATTR(B) void write_crowded_k(JoinGeom g, const uint64_t* __restrict__ offsets,
+                                                 const uint64_t* __restrict__ wave_off,
+                                                 const uint64_t* __restrict__ total,
+                                                 int2* __restrict__ out, uint64_t cap)
+{
+    if (*total > cap || (g.stamp_at && *g.stamp_at != g.stamp)) return;
+    __shared__ uint32_t found[B], nfound;
+    const uint32_t U = unit_total(g);
+    const int wv = uniform((int32_t)(threadIdx.x / kWave));
+    const cptr<uint64_t> offs = as_const(offsets);
+    const cptr<uint64_t> wo = as_const(wave_off);
+    for (uint64_t u0 = blockIdx.x; u0 < U; u0 += (uint64_t)gridDim.x * B) {
+        if (threadIdx.x == 0) nfound = 0;
+        __syncthreads();
+        const uint64_t mine64 = u0 + (uint64_t)threadIdx.x * gridDim.x;
+        const uint32_t mine = mine64 < U ? (uint32_t)mine64 : U;
+        if (mine < U && (AOS ? unit_of(g.urec[mine]).crowded : (wave_off[(size_t)mine * kWaveRec] & 2) != 0))
+            found[atomicAdd(&nfound, 1u)] = mine;
+        __syncthreads();
+        const uint32_t n = uniform(nfound);
+        for (uint32_t k = 0; k < n; ++k) {
+            const uint32_t u = uniform(found[k]);
+            set_crowded(g, decode_unit<AOS>(g, u));
+            const uint64_t at = uniform(offs[u]) + (wv ? uniform(wo[(size_t)u * kWaveRec + wv]) : 0ull);
+            const uint64_t few = (uint32_t)uniform(wo[(size_t)u * kWaveRec + kWaveHalf + wv]);
+            const uint64_t wrote = write_crowded<AOS, B>(at, at + few, out, cap);
+#if JL_DEBUG
+            if (g.dbg && lane_id() == 0 && wrote > 0)
+                atomicAdd(reinterpret_cast<unsigned long long*>(&g.dbg[u]), (unsigned long long)wrote);
+#else
+            (void)wrote;
+#endif
+            __syncthreads();
+        }
+    }
 }
 
 // Write pass.  Units are walked in a Sched sequence (for one join a contiguous run per
@@ -2174,7 +2475,7 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
                                            const uint64_t* __restrict__ total,
                                            int2* __restrict__ out, uint64_t cap)
 {
-    uint4* const tab = write_lds;
+    uint4* const tab = join_lds;
     // an output too small for the exact count, or a plan other than the count pass's, receives
     // nothing
     if (*total > cap || (g.stamp_at && *g.stamp_at != g.stamp)) return;
@@ -2199,7 +2500,7 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
     uint32_t nx[kWriteLoad];
     int32_t nr[kWriteLoad];
     if (u < U) {
-        un = decode_unit<AOS>(g, u);
+        un = decode_written<AOS>(g, wave_off, u);
         load_chunk<AOS, true, B>(g, un, ch);
         if constexpr (!SEMI) load_tuples<AOS, B>(g, un, 0, nx, nr);
     }
@@ -2232,7 +2533,7 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
         const uint64_t cursor0 = cursor, cmany0 = cmany;
 #endif
         const Table t = table_of<true, AOS>(un, tab);
-        const Unit nxt = more ? decode_unit<AOS>(g, nxi) : Unit{};
+        const Unit nxt = more ? decode_written<AOS>(g, wave_off, nxi) : Unit{};
         if (more && (!next_in_run || !same_chunk(nxt, un))) load_chunk<AOS, true, B>(g, nxt, ch);
         const uint32_t* rw = reinterpret_cast<const uint32_t*>(t.rids);
         auto batches = [&](auto marked) {
@@ -2567,7 +2868,8 @@ static hipError_t set_attrs()
         if (e != hipSuccess) return e;
     }
     for (const void* f : {(const void*)join_write_k<true, false, kJoinBlock>, (const void*)join_write_k<false, false, kJoinBlock>,
-                          (const void*)join_write_k<true, true, kJoinBlock>}) {
+                          (const void*)join_write_k<true, true, kJoinBlock>, (const void*)write_crowded_k<true, kJoinBlock>,
+                          (const void*)write_crowded_k<false, kJoinBlock>, (const void*)write_crowded_k<true, kBatchBlock>}) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, write_max);
         if (e != hipSuccess) return e;
     }
@@ -2885,7 +3187,7 @@ hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
                              ? reinterpret_cast<uint32_t*>(ws + pl.off_done) : nullptr;
         uint64_t* wave_off = reinterpret_cast<uint64_t*>(ws + pl.off_wave);
         prof::Scope pc(st, "hash.count");
-        if (pl.single) join_count_k<false, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, nullptr, total, nullptr);
+        if (pl.single) join_count_k<false, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, nullptr, total, pub);
         else if (pl.semi) join_count_k<true, true, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, done, total, pub);
         else join_count_k<true, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, done, total, pub);
         e = hipGetLastError();
@@ -2896,7 +3198,7 @@ hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
 }
 
 hipError_t hash_write(const HashPlan& pl, const join_rel_t& R, const join_rel_t& S, char* ws,
-                      int32_t* pairs, uint64_t cap, hipStream_t st, const RView* pre)
+                      int32_t* pairs, uint64_t cap, hipStream_t st, const RView* pre, bool crowded)
 {
     if (pl.Umax <= 0) return hipSuccess;
     hipError_t e = set_attrs();
@@ -2904,7 +3206,8 @@ hipError_t hash_write(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
     const uint64_t* offsets = reinterpret_cast<const uint64_t*>(ws + pl.off_counts);
     const uint64_t* wave_off = reinterpret_cast<const uint64_t*>(ws + pl.off_wave);
     const uint64_t* total = reinterpret_cast<const uint64_t*>(ws);
-    const JoinGeom g = make_geom(pl, R, S, ws, pre);
+    JoinGeom g = make_geom(pl, R, S, ws, pre);
+    g.crowded_apart = crowded ? 1 : 0;
     const unsigned grid = (unsigned)(pl.single ? pl.Umax : pl.gridWrite);
     const size_t lds = table_lds((uint32_t)pl.cap, true);
     int2* out = reinterpret_cast<int2*>(pairs);
@@ -2912,6 +3215,13 @@ hipError_t hash_write(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
     if (pl.single) join_write_k<false, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
     else if (pl.semi) join_write_k<true, true, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
     else join_write_k<true, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
+    if (crowded) {
+        // one unit per workgroup while there are few: a unit takes some 50 us
+        const unsigned cg = (unsigned)(pl.Umax < pl.gridWrite ? pl.Umax : pl.gridWrite);
+        const size_t cl = sorted_lds((uint32_t)pl.cap);
+        if (pl.single) write_crowded_k<false, kJoinBlock><<<cg, kJoinBlock, cl, st>>>(g, offsets, wave_off, total, out, cap);
+        else write_crowded_k<true, kJoinBlock><<<cg, kJoinBlock, cl, st>>>(g, offsets, wave_off, total, out, cap);
+    }
     return hipGetLastError();
 }
 
@@ -3247,12 +3557,17 @@ hipError_t hash_batch_write(const BatchPlan& bp, char* ws, int32_t* pairs, uint6
     if (bp.Umax <= 0) return hipSuccess;
     hipError_t e = set_attrs();
     if (e != hipSuccess) return e;
-    const JoinGeom g = batch_geom(bp, ws);
+    JoinGeom g = batch_geom(bp, ws);
+    g.crowded_apart = 1;
     prof::Scope pw(st, "hash.write");
+    const uint64_t* offsets = reinterpret_cast<const uint64_t*>(ws + bp.off_counts);
+    const uint64_t* wave_off = reinterpret_cast<const uint64_t*>(ws + bp.off_wave);
+    const uint64_t* total = reinterpret_cast<const uint64_t*>(ws);
+    int2* out = reinterpret_cast<int2*>(pairs);
     join_write_k<true, false, kBatchBlock><<<(unsigned)bp.gridWrite, kBatchBlock, table_lds((uint32_t)bp.cap, true), st>>>(
-        g, reinterpret_cast<const uint64_t*>(ws + bp.off_counts),
-        reinterpret_cast<const uint64_t*>(ws + bp.off_wave), reinterpret_cast<const uint64_t*>(ws),
-        reinterpret_cast<int2*>(pairs), cap);
+        g, offsets, wave_off, total, out, cap);
+    write_crowded_k<true, kBatchBlock><<<(unsigned)bp.gridWrite, kBatchBlock, sorted_lds((uint32_t)bp.cap), st>>>(
+        g, offsets, wave_off, total, out, cap);
     return hipGetLastError();
 }
 

@@ -41,6 +41,7 @@ struct JoinGeom {
     int bits;                   // partition bits; the table position uses the bits below them
     int P;
     int single;
+    int crowded_apart;  // write pass: a kernel of their own writes the crowded units
     int contig;  // write pass: contiguous runs of units per workgroup (else round robin)
     uint64_t* stamp_at;  // plan stamp in the workspace header (NULL for batches: no re-planning)
     uint64_t stamp;      // this plan's stamp: the count pass records it, the write pass checks it
@@ -98,13 +99,16 @@ RView build_view(const BuildPlan& b, const void* build);
 
 // Histogram, scatter, planning, count pass and the scan of counts.  Leaves the exact total at
 // ws[0..8) and the per-unit offsets in ws; pub (may be NULL): a pinned host slot (its device
-// address) that the kernel producing the total also stores it into.
+// address) that the kernel producing the total also stores it into; the word after it is set to 1
+// when some unit was crowded (see hash_write).
 hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t& S, char* ws,
                       hipStream_t st, const RView* pre = nullptr, uint64_t* pub = nullptr);
 
-// Write pass from the state hash_count left in ws.
+// Write pass from the state hash_count left in ws.  crowded: whether the count pass may have found
+// crowded units, which a kernel of their own writes.
 hipError_t hash_write(const HashPlan& pl, const join_rel_t& R, const join_rel_t& S, char* ws,
-                      int32_t* pairs, uint64_t cap, hipStream_t st, const RView* pre = nullptr);
+                      int32_t* pairs, uint64_t cap, hipStream_t st, const RView* pre = nullptr,
+                      bool crowded = true);
 
 // A batch of independent equi joins: layout of the shared workspace and launch sizes.  Kept
 // by the caller as an opaque join_batch_plan_t between the prepare, count and write calls.

@@ -350,10 +350,11 @@ hipError_t prefilter_count(const PrefilterPlan& pl, const join_rel_t& R, const j
 }
 
 hipError_t prefilter_write(const PrefilterPlan& pl, const join_rel_t& R, const join_rel_t& S,
-                           char* ws, int32_t* pairs, uint64_t cap, hipStream_t st, int num_cus)
+                           char* ws, int32_t* pairs, uint64_t cap, hipStream_t st, int num_cus,
+                           bool crowded)
 {
     if (pl.semi)
-        return hash_write(hash_plan(pl.nR, pl.nS, num_cus, -1, true), R, S, ws + pl.off_inner, pairs, cap, st);
+        return hash_write(hash_plan(pl.nR, pl.nS, num_cus, -1, true), R, S, ws + pl.off_inner, pairs, cap, st, nullptr, crowded);
     uint32_t n[2] = {0, 0};
     if (g_seen.ws == ws && g_seen.stamp == pl.stamp) {
         n[0] = g_seen.n[0];
@@ -365,7 +366,7 @@ hipError_t prefilter_write(const PrefilterPlan& pl, const join_rel_t& R, const j
     join_rel_t R2, S2;
     survivors(pl, ws, n, R, S, &R2, &S2);
     if (R2.n == 0 || S2.n == 0) return hipSuccess;
-    return hash_write(hash_plan(R2.n, S2.n, num_cus), R2, S2, ws + pl.off_inner, pairs, cap, st);
+    return hash_write(hash_plan(R2.n, S2.n, num_cus), R2, S2, ws + pl.off_inner, pairs, cap, st, nullptr, crowded);
 }
 
 }  // namespace jl

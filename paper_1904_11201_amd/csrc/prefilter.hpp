@@ -32,7 +32,8 @@ hipError_t prefilter_count(const PrefilterPlan& pl, const join_rel_t& R, const j
 // Reads the surviving sizes (one 8-byte read, none if neither side has a filter), then the
 // inner hash join's write pass.
 hipError_t prefilter_write(const PrefilterPlan& pl, const join_rel_t& R, const join_rel_t& S,
-                           char* ws, int32_t* pairs, uint64_t cap, hipStream_t st, int num_cus);
+                           char* ws, int32_t* pairs, uint64_t cap, hipStream_t st, int num_cus,
+                           bool crowded);
 
 // The exact total of the last count pass lives at the start of the inner workspace.
 inline uint64_t prefilter_total_offset(const PrefilterPlan& pl) { return pl.off_inner; }
