@@ -204,12 +204,16 @@ bool matches_last(int kind, const join_rel_t* R, const join_rel_t* S, const join
     return true;
 }
 
-// Pinned 8-byte landing slot for the count read (one per thread, kept for the process).
+// Pinned landing words for the count read (one set per thread, kept for the process): the total,
+// the crowded flag, and from word kUnitSlot the counts of single units.
+constexpr int kUnitSlot = 8;
+
 uint64_t* pinned_slot()
 {
     static thread_local uint64_t* slot = nullptr;
     if (!slot) {
-        if (hipHostMalloc((void**)&slot, 64, hipHostMallocDefault) != hipSuccess) slot = nullptr;
+        if (hipHostMalloc((void**)&slot, (kUnitSlot + kDirectUnits) * 8, hipHostMallocDefault) != hipSuccess)
+            slot = nullptr;
     }
     return slot;
 }
@@ -276,9 +280,8 @@ uint64_t* published_slot()
     return m.addr;
 }
 
-hipError_t wait_published(hipStream_t st, uint64_t* count)
+hipError_t wait_published(volatile uint64_t* slot, hipStream_t st, uint64_t* count)
 {
-    volatile uint64_t* slot = pinned_slot();
     uint64_t v;
     uint32_t spins = 0;
     while ((v = *slot) == kUnpublished) {
@@ -294,13 +297,16 @@ hipError_t wait_published(hipStream_t st, uint64_t* count)
     return hipSuccess;
 }
 
-// The slot the next count pass stores its total into (NULL: read it by copy), reset first.
-uint64_t* arm_published_slot()
+// The slot the next count pass stores its total into (NULL: read it by copy), and the slots of its
+// first `units` units, reset first.
+uint64_t* arm_published_slot(int units = 0)
 {
     uint64_t* pub = published_slot();
     if (pub) {
-        pinned_slot()[0] = kUnpublished;
-        pinned_slot()[1] = 0;
+        uint64_t* slot = pinned_slot();
+        slot[0] = kUnpublished;
+        slot[1] = 0;
+        for (int u = 0; u < units; ++u) slot[kUnitSlot + u] = kUnpublished;
     }
     return pub;
 }
@@ -315,7 +321,21 @@ bool crowded_said(const uint64_t* pub)
 // The exact total of the count pass just enqueued: from the slot, or copied from `src`.
 hipError_t take_total(uint64_t* pub, const void* src, hipStream_t st, uint64_t* count)
 {
-    return pub ? wait_published(st, count) : read_total(src, st, count);
+    return pub ? wait_published(pinned_slot(), st, count) : read_total(src, st, count);
+}
+
+// The same for a count pass whose units each publish their count: their sum.
+hipError_t take_units(int units, hipStream_t st, uint64_t* count)
+{
+    uint64_t sum = 0;
+    for (int u = 0; u < units; ++u) {
+        uint64_t c = 0;
+        const hipError_t e = wait_published(pinned_slot() + kUnitSlot + u, st, &c);
+        if (e != hipSuccess) return e;
+        sum += c;
+    }
+    *count = sum;
+    return hipSuccess;
 }
 
 #if JL_DEBUG
@@ -380,9 +400,11 @@ int count_impl(int kind, const AnyPlan& pl, const join_rel_t* R, const join_rel_
         char* w = static_cast<char*>(ws);
         hipError_t e;
         size_t total_at = 0;  // where the exact total lands in ws
-        uint64_t* pub = arm_published_slot();
+        int units = kind == JOIN_KIND_HASH ? hash_direct_units(pl.hash) : 0;
+        uint64_t* pub = arm_published_slot(units);
+        if (!pub) units = 0;
         if (kind == JOIN_KIND_HASH) {
-            e = hash_count(pl.hash, *R, *S, w, st, nullptr, pub);
+            e = hash_count(pl.hash, *R, *S, w, st, nullptr, pub, units ? pub + kUnitSlot : nullptr);
         } else if (kind == JOIN_KIND_HASH_PREFILTER) {
             e = prefilter_count(pl.prefilter, *R, *S, w, st, num_cus(), pub);
             total_at = prefilter_total_offset(pl.prefilter);
@@ -392,7 +414,7 @@ int count_impl(int kind, const AnyPlan& pl, const join_rel_t* R, const join_rel_
             e = theta_count(pl.theta, *R, *S, *p, w, st, pub);
         }
         if (e != hipSuccess) return hip_fail(e, is_theta(kind) ? "theta count pass" : "hash count pass");
-        e = take_total(pub, w + total_at, st, count);
+        e = units ? take_units(units, st, count) : take_total(pub, w + total_at, st, count);
         if (e != hipSuccess) return hip_fail(e, "reading the exact total");
         g_last.crowded = crowded_said(pub);
 #if JL_DEBUG

@@ -2150,7 +2150,7 @@ template <int B, typename Between>
 __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_many, bool multi,
                                             uint32_t semi_rows, uint32_t u, uint64_t* __restrict__ counts,
                                             uint64_t* __restrict__ wave_off, uint64_t* sh, uint32_t* rec_word,
-                                            bool crowded, Between between)
+                                            bool crowded, uint64_t* unit_pub, Between between)
 {
     const uint64_t wt = wave_sum64(lane_total);
     const uint64_t wmany = wave_sum64(lane_many);
@@ -2174,6 +2174,7 @@ __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_m
         wave_off[(size_t)u * kWaveRec + threadIdx.x] = threadIdx.x == 0 ? any | (crowded ? 2u : 0u) : before;
         if (threadIdx.x == 0) {
             store_shared(&counts[u], sum);
+            if (unit_pub) __hip_atomic_store(&unit_pub[u], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             const uint32_t flags = (any ? 1u << kRecOrder : 0u) | (crowded ? 1u << kRecCrowded : 0u);
             if (flags && rec_word) atomicOr(rec_word, flags);
         }
@@ -2237,7 +2238,7 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
     __shared__ uint64_t wsum[B / kWave + 1];
     constexpr uint32_t kB = B * kCountBatch;  // keys per batch
     const uint32_t U = unit_total(g);
-    if (g.stamp_at && blockIdx.x == 0 && threadIdx.x == 0) *g.stamp_at = g.stamp;  // for the write pass
+    if (g.stamp_at && blockIdx.x == 0 && threadIdx.x == 0) *g.stamp_at = g.unit_pub ? ~g.stamp : g.stamp;
     __shared__ uint32_t slot[2];
     __shared__ uint32_t crowded;
     if (threadIdx.x == 0) crowded = 0;
@@ -2286,6 +2287,7 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
             // told to the host at once: it is read with the total, which is published later
             if (pub && threadIdx.x == 0)
                 __hip_atomic_store(pub + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            drain();  // before this unit's count is
             const UnitCount c = count_crowded<AOS, SEMI, B>();
             cnt = c.cnt;
             many = c.many;
@@ -2305,7 +2307,8 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
         // comes from the next unit's first probe keys, loaded during the last batch: every hash
         // of a partition has the partition's top bits (a unit without probe keys never reads
         // its table, so its marker does not matter).
-        unit_totals<B>(cnt, many, multi, sm.k, u, counts, wave_off, wsum, rec_word, by_sort, [&] {
+        unit_totals<B>(cnt, many, multi, sm.k, u, counts, wave_off, wsum, rec_word, by_sort,
+                       AOS ? nullptr : g.unit_pub, [&] {
             if (more) clear_table<false, AOS, B>(nx, xa[0], tab);
             if (threadIdx.x == 0) crowded = 0;
         });  // ends with a barrier
@@ -2380,6 +2383,36 @@ __device__ __forceinline__ bool chunk_needs_order(const JoinGeom& g, const uint6
     return any;
 }
 
+// The units' counts where the count pass left them unscanned (at most kDirectUnits of them, two per
+// lane): their sum, and the sum of those before a unit.
+struct RawCounts {
+    bool on;         // uniform
+    uint64_t total;  // uniform
+    uint64_t c0, c1; // counts of units lane and lane + 64
+
+    __device__ __forceinline__ uint64_t before(uint32_t u) const
+    {
+        const uint32_t l = lane_id();
+        return wave_sum64((l < u ? c0 : 0ull) + (l + kWave < u ? c1 : 0ull));
+    }
+};
+
+template <bool PART>
+__device__ __forceinline__ RawCounts raw_counts(const JoinGeom& g, const uint64_t* counts, uint32_t U)
+{
+    RawCounts r{};
+    if constexpr (!PART) {
+        if (g.Umax <= kDirectUnits) {
+            const uint32_t l = lane_id();
+            r.c0 = l < U ? counts[l] : 0;
+            r.c1 = l + kWave < U ? counts[l + kWave] : 0;
+            r.on = uniform(*g.stamp_at) == ~g.stamp;
+            r.total = wave_sum64(r.c0 + r.c1);
+        }
+    }
+    return r;
+}
+
 // The pairs of a crowded unit: this wave's pairs of probes with one or two matches from `cursor` on,
 // those of probes with more from `cmany` on; returns how many of both together.
 template <bool AOS, int B>
@@ -2432,9 +2465,10 @@ __global__ JL_WRITE_ATTR(B) void write_crowded_k(JoinGeom g, const uint64_t* __r
                                                  const uint64_t* __restrict__ total,
                                                  int2* __restrict__ out, uint64_t cap)
 {
-    if (*total > cap || (g.stamp_at && *g.stamp_at != g.stamp)) return;
     __shared__ uint32_t found[B], nfound;
     const uint32_t U = unit_total(g);
+    const RawCounts raw = raw_counts<AOS>(g, offsets, U);
+    if ((raw.on ? raw.total : *total) > cap || (g.stamp_at && !raw.on && *g.stamp_at != g.stamp)) return;
     const int wv = uniform((int32_t)(threadIdx.x / kWave));
     const cptr<uint64_t> offs = as_const(offsets);
     const cptr<uint64_t> wo = as_const(wave_off);
@@ -2450,7 +2484,7 @@ __global__ JL_WRITE_ATTR(B) void write_crowded_k(JoinGeom g, const uint64_t* __r
         for (uint32_t k = 0; k < n; ++k) {
             const uint32_t u = uniform(found[k]);
             set_crowded(g, decode_unit<AOS>(g, u));
-            const uint64_t at = uniform(offs[u]) + (wv ? uniform(wo[(size_t)u * kWaveRec + wv]) : 0ull);
+            const uint64_t at = (raw.on ? raw.before(u) : uniform(offs[u])) + (wv ? uniform(wo[(size_t)u * kWaveRec + wv]) : 0ull);
             const uint64_t few = (uint32_t)uniform(wo[(size_t)u * kWaveRec + kWaveHalf + wv]);
             const uint64_t wrote = write_crowded<AOS, B>(at, at + few, out, cap);
 #if JL_DEBUG
@@ -2476,10 +2510,17 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
                                            int2* __restrict__ out, uint64_t cap)
 {
     uint4* const tab = join_lds;
+    const uint32_t U = unit_total(g);
     // an output too small for the exact count, or a plan other than the count pass's, receives
     // nothing
-    if (*total > cap || (g.stamp_at && *g.stamp_at != g.stamp)) return;
-    const uint32_t U = unit_total(g);
+    bool raw_on = false;        // uniform: the unit counts are not scanned
+    uint64_t raw_before = 0;    // then: pairs of the units before this workgroup's only one
+    {
+        const RawCounts raw = raw_counts<AOS>(g, offsets, U);
+        if ((raw.on ? raw.total : *total) > cap || (g.stamp_at && !raw.on && *g.stamp_at != g.stamp)) return;
+        raw_on = raw.on;
+        if (raw_on) raw_before = uniform(raw.before(blockIdx.x));
+    }
     const bool contig = g.contig != 0;  // uniform
     const int wv = uniform((int32_t)(threadIdx.x / kWave));
     uint4* q = manyq<B>() + wv * kManyQ;  // this wave's queue of probes with many matches
@@ -2525,7 +2566,7 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
             tu = un;
         }
         // this wave's first output slot in unit u, and the start of its block of many-match pairs
-        uint64_t cursor = uniform(offs[u]) + (wv ? uniform(wo[(size_t)u * kWaveRec + wv]) : 0ull);
+        uint64_t cursor = (raw_on ? raw_before : uniform(offs[u])) + (wv ? uniform(wo[(size_t)u * kWaveRec + wv]) : 0ull);
         const uint64_t wrec = uniform(wo[(size_t)u * kWaveRec + kWaveHalf + wv]);
         uint64_t cmany = cursor + (uint32_t)wrec;
         const uint32_t semi_rows = (uint32_t)(wrec >> 32);  // the semi-join's rows of this wave
@@ -3110,8 +3151,13 @@ static JoinGeom make_geom(const HashPlan& pl, const join_rel_t& R, const join_re
     return g;
 }
 
+int hash_direct_units(const HashPlan& pl)
+{
+    return pl.single && pl.Umax <= kDirectUnits && !JL_DEBUG ? (int)pl.Umax : 0;
+}
+
 hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t& S, char* ws,
-                      hipStream_t st, const RView* pre, uint64_t* pub)
+                      hipStream_t st, const RView* pre, uint64_t* pub, uint64_t* unit_pub)
 {
     hipError_t e = set_attrs();
     if (e != hipSuccess) return e;
@@ -3179,7 +3225,8 @@ hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
         }
     }
     if (pl.Umax > 0) {
-        const JoinGeom g = make_geom(pl, R, S, ws, pre);
+        JoinGeom g = make_geom(pl, R, S, ws, pre);
+        g.unit_pub = unit_pub;
         const unsigned grid = (unsigned)(pl.single ? pl.Umax : pl.gridCount);
         const size_t lds = table_lds((uint32_t)pl.cap, false);
         // the partitioned path cleared the arrival counter with the partition sizes
@@ -3191,7 +3238,7 @@ hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
         else if (pl.semi) join_count_k<true, true, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, done, total, pub);
         else join_count_k<true, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, done, total, pub);
         e = hipGetLastError();
-        if (e != hipSuccess || done) return e;
+        if (e != hipSuccess || done || unit_pub) return e;
     }
     return exclusive_scan<uint64_t>(counts, counts, pl.Umax, total, reinterpret_cast<uint64_t*>(temp), st,
                                     pub);

@@ -44,7 +44,9 @@ struct JoinGeom {
     int crowded_apart;  // write pass: a kernel of their own writes the crowded units
     int contig;  // write pass: contiguous runs of units per workgroup (else round robin)
     uint64_t* stamp_at;  // plan stamp in the workspace header (NULL for batches: no re-planning)
-    uint64_t stamp;      // this plan's stamp: the count pass records it, the write pass checks it
+    uint64_t stamp;      // this plan's stamp: the count pass records it, the write pass checks it;
+                         // its complement where the unit counts were left unscanned
+    uint64_t* unit_pub;  // count pass: pinned words of the units' counts (NULL: they are scanned)
     uint64_t* dbg;       // checking build: pairs written per unit (NULL: not counted)
     uint32_t* semi;      // the probe rows with matches, per unit and wave (NULL: not recorded)
     uint32_t* sched;     // [3]: count ticket, write ticket, write arrivals (NULL: static shares)
@@ -101,8 +103,18 @@ RView build_view(const BuildPlan& b, const void* build);
 // ws[0..8) and the per-unit offsets in ws; pub (may be NULL): a pinned host slot (its device
 // address) that the kernel producing the total also stores it into; the word after it is set to 1
 // when some unit was crowded (see hash_write).
+// unit_pub (may be NULL): device address of hash_direct_units(pl) pinned words; then every unit
+// stores its count there by itself, the total is neither scanned nor published, and the write pass
+// sums the counts it needs.
 hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t& S, char* ws,
-                      hipStream_t st, const RView* pre = nullptr, uint64_t* pub = nullptr);
+                      hipStream_t st, const RView* pre = nullptr, uint64_t* pub = nullptr,
+                      uint64_t* unit_pub = nullptr);
+
+// Units of a join that publishes their counts one by one, 0 for a join that does not: a few units
+// of the unpartitioned path, where a scan kernel behind the count kernel costs more than the reads
+// of the counts (1K x 4K: 3.5 us of the GPU's time and a launch, of 39 us a join).
+constexpr int kDirectUnits = 128;
+int hash_direct_units(const HashPlan& pl);
 
 // Write pass from the state hash_count left in ws.  crowded: whether the count pass may have found
 // crowded units, which a kernel of their own writes.

@@ -58,3 +58,25 @@ def test_noalloc_keeps_small_builds_with_many_probe_rows():
     count = torch.zeros(1, dtype=torch.int64, device="cuda")
     J.join_hash_noalloc(R, S, out, count)
     assert int(count[0]) == want.numel() and torch.equal(_sorted(out), want)
+
+
+@gpu
+@pytest.mark.parametrize("nS", [1024, 65 * 1024, 128 * 1024, 128 * 1024 + 1, 130 * 1024])
+def test_unit_counts_published_or_scanned(nS):
+    """One probe unit per 1024 rows: up to 128 units publish their counts themselves, more are
+    scanned; a second write from the same count, into a larger output, gives the same pairs."""
+    from paper_1904_11201_amd import join as J
+    need_gpu()
+    R, S = _relations(3000, nS, nS, rids=True)
+    log(f"unit counts 3000 x {nS}")
+    ws = J.workspace(J.JOIN_KIND_HASH, R.n, S.n)
+    n = J.join_count(J.JOIN_KIND_HASH, R, S, None, ws)
+    out = torch.full((n + 5, 2), -9, dtype=torch.int32, device="cuda")
+    with pytest.raises(J.JoinError):
+        J.join_materialize(J.JOIN_KIND_HASH, R, S, None, ws, out[:n - 1])
+    J.join_materialize(J.JOIN_KIND_HASH, R, S, None, ws, out)
+    assert bool((out[n:] == -9).all())
+    pairs = torch.empty((n, 2), dtype=torch.int32, device="cuda")
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    J.join_hash_noalloc(R, S, pairs, count)  # always scanned
+    assert int(count[0]) == n and torch.equal(out[:n], pairs)
