@@ -80,6 +80,22 @@ __device__ __forceinline__ int2 load2(const int2* p)
     return make_int2(v.x, v.y);
 }
 
+// The same loads, and that of a tuple's first word, non-temporal: the lines pass through the caches
+// without displacing what the rest of the pass reads there.
+__device__ __forceinline__ i32x4 load4_once(gptr<int32_t> p)
+{
+    return __builtin_nontemporal_load((const __attribute__((address_space(1))) i32x4_any*)p);
+}
+__device__ __forceinline__ int2 load2_once(const int2* p)
+{
+    const i32x2 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) i32x2*)p);
+    return make_int2(v.x, v.y);
+}
+__device__ __forceinline__ int32_t load_key_once(const int2* p)
+{
+    return __builtin_nontemporal_load((gptr<int32_t>)&p->x);
+}
+
 // Plan stamps.  Every workspace starts with a 256-byte header.  The count pass records at
 // kStampOffset a signature of the plan it ran (sizes, fan-out, capacities, tiles: how the work
 // was cut up), and the write pass, which plans again from its own arguments and the tuning

@@ -181,6 +181,8 @@ __global__ __launch_bounds__(kHistBlock) void hist_k(const SideItem* __restrict_
     // ordered scatter (cnt != NULL): one row per tile; else the chunk is counted as one span
     const int64_t span = cnt ? (int64_t)kScatTile : (end > 0 ? end : 1);
     uint32_t* __restrict__ row = cnt ? cnt + it.cnt0 : nullptr;
+    // The keys are read non-temporally (24M rows: 26 -> 20 us, 80M: 62 -> 56; the scatter's reads of
+    // them, also non-temporal, 227 -> 221 at 80M; 5M rows: no difference).
     // One round is up to a tile, the next round's loads in flight while this one is counted.  Only
     // whole vectors are loaded, with no branch (threads past the last one repeat it); the odd
     // keys of a span follow at its end.
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(kHistBlock) void hist_k(const SideItem* __restrict_
         const int nv = (int)((to - i < kScatTile ? to - i : kScatTile) / 4);  // uniform
         if (nv == 0) return;
 #pragma unroll
-        for (int v = 0; v < V; ++v) k4[v] = load4(key + i + 4 * min(v * kHistBlock + (int)threadIdx.x, nv - 1));
+        for (int v = 0; v < V; ++v) k4[v] = load4_once(key + i + 4 * min(v * kHistBlock + (int)threadIdx.x, nv - 1));
     };
     for (int64_t t0 = 0; t0 < end; t0 += span) {
         const int64_t to = end - t0 < span ? end : t0 + span;
@@ -433,7 +435,7 @@ __device__ __forceinline__ void scat_load(gptr<int32_t> col, int t0, int tn, int
     for (int v = 0; v < IT / 4; ++v) {
         const int e = scat_pos(4 * v);
         if (FULL || e + 4 <= tn) {
-            const i32x4 x4 = load4(col + t0 + e);
+            const i32x4 x4 = load4_once(col + t0 + e);
             x[4 * v] = x4.x; x[4 * v + 1] = x4.y; x[4 * v + 2] = x4.z; x[4 * v + 3] = x4.w;
         } else {
 #pragma unroll
@@ -1841,6 +1843,29 @@ constexpr int kWriteLoadOf = B == kBatchBlock ? 2 : JL_HASH_WRITE_LOAD;
 static_assert(kWriteLoadOf<kJoinBlock> % kWriteBatch == 0 && kWriteLoadOf<kBatchBlock> % kWriteBatch == 0,
               "write loads are probed kWriteBatch tuples at a time");
 
+// Above this many bytes of tuples on both sides, the count and write passes read the probe tuples
+// non-temporally.  The line lies a little above the 256 MB of the last-level cache: tuples that fit
+// are still there from the scatter, and the write pass finds those of the count pass there, which
+// non-temporal reads would give up (16M rows: count 43 us, non-temporal 50; 40M rows: 87 and 84,
+// write 152 and 155).  Past it, ordinary reads of tuples that will not be there again push out those
+// that would (52M rows: count 115 -> 105 us; 80M rows: count 199 -> 166, write 315 -> 312).
+constexpr int64_t kStreamBytes = 320ll << 20;
+int stream_rows(int64_t rows) { return rows * (int64_t)sizeof(int2) > kStreamBytes; }
+
+// load(std::true_type) when the join streams its tuples, else load(std::false_type).  The empty
+// statements keep the compiler from merging the two sides' loads into ordinary ones.
+template <bool AOS, typename Load>
+__device__ __forceinline__ void by_stream(const JoinGeom& g, Load load)
+{
+    if (AOS && g.stream) {  // uniform
+        asm volatile("");
+        load(std::true_type{});
+        asm volatile("");
+    } else {
+        load(std::false_type{});
+    }
+}
+
 template <bool AOS, int B>
 __device__ __forceinline__ void load_tuples(const JoinGeom& g, const Unit& un, uint32_t e0,
                                             uint32_t (&x)[kWriteLoadOf<B>], int32_t (&r)[kWriteLoadOf<B>])
@@ -1851,25 +1876,28 @@ __device__ __forceinline__ void load_tuples(const JoinGeom& g, const Unit& un, u
         for (int i = 0; i < kWriteLoadOf<B>; ++i) x[i] = 0u, r[i] = 0;
         return;
     }
+    auto load = [&](auto once) {
 #pragma unroll
-    for (int i = 0; i < kWriteLoadOf<B>; ++i) {
-        const uint32_t e = e0 + i * B + threadIdx.x;
-        const bool ok = full || e < un.sN;
-        uint32_t idx = un.sBeg + (ok ? e : 0u);
-        // computed where the load is issued: hoisted out of the probe loop, the addresses of the
-        // next unit's first loads would occupy registers through it
-        asm volatile("" : "+v"(idx));
-        // no select on the loaded values: the probe masks the out-of-range lanes, and a select
-        // here would wait for the loads
-        if constexpr (AOS) {
-            const int2 t = g.st[idx];
-            x[i] = (uint32_t)t.x;
-            r[i] = t.y;
-        } else {
-            x[i] = (uint32_t)g.sk[idx];
-            r[i] = g.sr ? g.sr[idx] : (int32_t)idx;
+        for (int i = 0; i < kWriteLoadOf<B>; ++i) {
+            const uint32_t e = e0 + i * B + threadIdx.x;
+            const bool ok = full || e < un.sN;
+            uint32_t idx = un.sBeg + (ok ? e : 0u);
+            // computed where the load is issued: hoisted out of the probe loop, the addresses of
+            // the next unit's first loads would occupy registers through it
+            asm volatile("" : "+v"(idx));
+            // no select on the loaded values: the probe masks the out-of-range lanes, and a select
+            // here would wait for the loads
+            if constexpr (AOS) {
+                const int2 t = once ? load2_once(g.st + idx) : load2(g.st + idx);
+                x[i] = (uint32_t)t.x;
+                r[i] = t.y;
+            } else {
+                x[i] = (uint32_t)g.sk[idx];
+                r[i] = g.sr ? g.sr[idx] : (int32_t)idx;
+            }
         }
-    }
+    };
+    by_stream<AOS>(g, load);
 }
 
 // A batch of S keys of a unit with un.sN > 0.  Out-of-range lanes read the unit's first tuple and
@@ -1879,15 +1907,17 @@ __device__ __forceinline__ void load_keys_of(const JoinGeom& g, const Unit& un, 
                                              uint32_t (&xs)[kCountBatch])
 {
     const bool full = e0 + (uint32_t)(kCountBatch * B) <= un.sN;  // uniform
+    by_stream<AOS>(g, [&](auto once) {
 #pragma unroll
-    for (int i = 0; i < kCountBatch; ++i) {
-        const uint32_t e = e0 + i * B + threadIdx.x;
-        const bool ok = full || e < un.sN;
-        const uint32_t idx = un.sBeg + (ok ? e : 0u);
-        // no select on the loaded value: the probe masks the out-of-range lanes
-        if constexpr (AOS) xs[i] = (uint32_t)g.st[idx].x;
-        else xs[i] = (uint32_t)g.sk[idx];
-    }
+        for (int i = 0; i < kCountBatch; ++i) {
+            const uint32_t e = e0 + i * B + threadIdx.x;
+            const bool ok = full || e < un.sN;
+            const uint32_t idx = un.sBeg + (ok ? e : 0u);
+            // no select on the loaded value: the probe masks the out-of-range lanes
+            if constexpr (AOS) xs[i] = (uint32_t)(once ? load_key_once(g.st + idx) : g.st[idx].x);
+            else xs[i] = (uint32_t)g.sk[idx];
+        }
+    });
 }
 
 // The same for any unit: a unit without probes loads nothing.
@@ -3144,6 +3174,7 @@ static JoinGeom make_geom(const HashPlan& pl, const join_rel_t& R, const join_re
         g.urec = reinterpret_cast<const uint4*>(ws + pl.off_umap);
         g.Uptr = reinterpret_cast<const uint32_t*>(ws + 8);
         g.P = pl.P;
+        g.stream = stream_rows(pl.nR + pl.nS);
         // one join's units are even and its write pass keeps a table across consecutive units of
         // one R chunk: static shares (tickets measured slower on 16M x 64M and 1M x 64M)
         g.sched = nullptr;
@@ -3504,6 +3535,7 @@ static JoinGeom batch_geom(const BatchPlan& bp, char* ws)
     g.urec = reinterpret_cast<const uint4*>(ws + bp.off_umap);
     g.Uptr = reinterpret_cast<const uint32_t*>(ws + 8);
     g.P = (int)bp.nParts;
+    g.stream = stream_rows(bp.sumR + bp.sumS);
     g.sched = reinterpret_cast<uint32_t*>(ws + bp.off_tot) + (2 + 2 * kGroups) * bp.nParts;
     return g;
 }

@@ -49,6 +49,7 @@ struct JoinGeom {
     uint64_t* unit_pub;  // count pass: pinned words of the units' counts (NULL: they are scanned)
     uint64_t* dbg;       // checking build: pairs written per unit (NULL: not counted)
     uint32_t* semi;      // the probe rows with matches, per unit and wave (NULL: not recorded)
+    int stream;          // the probe tuples are read non-temporally (kStreamBytes)
     uint32_t* sched;     // [3]: count ticket, write ticket, write arrivals (NULL: static shares)
 };
 
