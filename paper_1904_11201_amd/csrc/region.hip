@@ -130,10 +130,20 @@ __global__ __launch_bounds__(kBlk) void sample_k(Cols R, Cols S, uint32_t sR, ui
     for (uint32_t z = i; z < zeroWords; z += gridDim.x * kBlk) zero[z] = 0;
 }
 
+// A word of an LDS counter array of which each thread scans 2^PB consecutive ones: one word of
+// padding after each thread's, so that a wave's lanes read different banks (2^14 counters without
+// it: 16 reads of 64 lanes on 4 banks).
+template <int PB>
+__host__ __device__ constexpr uint32_t padded(uint32_t i)
+{
+    return i + (i >> PB);
+}
+
 // One workgroup: bins over the sampled range, buckets of about equal sample counts.  Rows outside
 // the sampled range fall into the outer bins, so an outlier does not stretch the bins.  A
-// bucket's size follows its sample count, 16 rows or more, so that it stays under kCap (twice the
-// mean or more) for all but a few buckets; those are sorted in several chunks.
+// bucket's size follows its sample count, 32 rows: it stays under kCap, twice the mean or more,
+// but for a few in a million (16 samples: one or two of 2048 buckets were larger, and merging the
+// chunks of an S bucket ended 25 us after the other sorts, 52 us at 4M rows a side).
 __global__ __launch_bounds__(kBlk) void setup_k(const int32_t* __restrict__ sample, uint32_t m, int binBits,
                                                 int bits, Hdr* __restrict__ h, uint16_t* __restrict__ lut)
 {
@@ -142,7 +152,8 @@ __global__ __launch_bounds__(kBlk) void setup_k(const int32_t* __restrict__ samp
     __shared__ uint32_t wsum[kBlk / kWave + 1];
     const int tid = threadIdx.x;
     const int nb = 1 << binBits;
-    for (int i = tid; i < nb; i += kBlk) bins[i] = 0;
+    constexpr int kPad = kMaxBinBits - 10;  // 16 counters a thread at most
+    for (int i = tid; i < (int)padded<kPad>(nb); i += kBlk) bins[i] = 0;
     constexpr int kBatch = 16;  // loads of a thread in flight together
     auto each = [&](auto f) {
         for (uint32_t i0 = 0; i0 < m; i0 += kBlk * kBatch) {
@@ -162,18 +173,22 @@ __global__ __launch_bounds__(kBlk) void setup_k(const int32_t* __restrict__ samp
     block_range<kBlk>(lo, hi, red);
     const Hdr hh{0, lo, span_shift((uint32_t)hi - (uint32_t)lo, binBits), (uint32_t)nb};
     if (tid == 0) *h = hh;
-    each([&](int32_t a) { atomicAdd(&bins[bin_of(a, hh)], 1u); });
+    each([&](int32_t a) { atomicAdd(&bins[padded<kPad>(bin_of(a, hh))], 1u); });
     __syncthreads();
     const int per = nb / kBlk;
     uint32_t s = 0, tot;
-    for (int k = 0; k < per; ++k) s += bins[tid * per + k];
+    for (int k = 0; k < per; ++k) s += bins[padded<kPad>(tid * per + k)];
     uint32_t run = block_excl_scan<kBlk>(s, wsum, &tot);
+    const float scale = (float)(1u << bits) / (float)tot;  // rounded, but never falling as run rises
     for (int k = 0; k < per; ++k) {
-        const uint32_t c = bins[tid * per + k];
-        const uint32_t b = (run << bits) / tot;  // run <= tot <= 2^16, bits <= 13
-        lut[tid * per + k] = (uint16_t)min(b, (1u << bits) - 1);
+        uint32_t& c = bins[padded<kPad>(tid * per + k)];
+        const uint32_t b = (uint32_t)((float)run * scale);  // run <= tot <= 2^17: exact as a float
         run += c;
+        c = min(b, (1u << bits) - 1);
     }
+    __syncthreads();
+    for (int i = tid; i < nb / 2; i += kBlk)
+        reinterpret_cast<uint32_t*>(lut)[i] = bins[padded<kPad>(2 * i)] | bins[padded<kPad>(2 * i + 1)] << 16;
 }
 
 // --------------------------------------------------------------------------- bucket sizes --
@@ -462,6 +477,11 @@ __device__ void bitonic_ranks(const Row (&v)[kSortPer], uint32_t n, uint64_t* ke
     __syncthreads();
 }
 
+constexpr int kSubPad = 3;  // log2 of the bins a thread scans
+static_assert(kSub == kSortBlk << kSubPad, "bins of a sort");
+__device__ __forceinline__ uint32_t sub_at(uint32_t i) { return padded<kSubPad>(i); }
+constexpr uint32_t kSubWords = padded<kSubPad>(kSub) + 1;
+
 // One chunk of up to kCap rows of one bucket per workgroup, sorted by a: counted into kSub value
 // bins of the chunk's own range (about one row each), placed by bin, and each row of S ranked
 // against the rows of its bin (nothing to do when a bin holds one value; when some bin holds more
@@ -470,7 +490,7 @@ __device__ void bitonic_ranks(const Row (&v)[kSortPer], uint32_t n, uint64_t* ke
 // of the bins: its rows only have to lie near each other.  direct: the input columns, one
 // workgroup per side; else workgroup i < 2B takes bucket i's first chunk, the others the list of
 // further chunks.
-// LDS: bins[kSub + 1] | one column of kCap rows, which stages a, then rid and c, into sorted order
+// LDS: bins[kSub + 1] (padded) | one column of kCap rows, which stages a, then rid and c, into sorted order
 template <bool HAS_C>
 __global__ __launch_bounds__(kSortBlk) void sort_k(Sides s, int direct)
 {
@@ -480,7 +500,7 @@ __global__ __launch_bounds__(kSortBlk) void sort_k(Sides s, int direct)
     __shared__ uint32_t last, crowded;
     if (threadIdx.x == 0) crowded = 0;
     uint32_t* bin = lds;
-    int32_t* ta = reinterpret_cast<int32_t*>(bin + kSub + 1);
+    int32_t* ta = reinterpret_cast<int32_t*>(bin + kSubWords);
     const int tid = threadIdx.x;
     int side;
     uint32_t b0, at, n, total;  // the bucket's first row, the chunk's first row and rows, the bucket's rows
@@ -525,7 +545,7 @@ __global__ __launch_bounds__(kSortBlk) void sort_k(Sides s, int direct)
             v[q] = part_row<HAS_C>(s.part[side], i);
         }
     }
-    for (int i = tid; i <= kSub; i += kSortBlk) bin[i] = 0;
+    for (int i = tid; i < (int)kSubWords; i += kSortBlk) bin[i] = 0;
 #pragma unroll
     for (int q = 0; q < kSortPer; ++q) {
         lo = min(lo, v[q].a);
@@ -536,7 +556,7 @@ __global__ __launch_bounds__(kSortBlk) void sort_k(Sides s, int direct)
 #pragma unroll
     for (int q = 0; q < kSortPer; ++q) {
         sub[q] = ((uint32_t)v[q].a - (uint32_t)lo) >> sh;
-        if ((uint32_t)(q * kSortBlk + tid) < n) rank[q] = atomicAdd(&bin[sub[q]], 1u);
+        if ((uint32_t)(q * kSortBlk + tid) < n) rank[q] = atomicAdd(&bin[sub_at(sub[q])], 1u);
     }
     __syncthreads();
     {
@@ -544,17 +564,17 @@ __global__ __launch_bounds__(kSortBlk) void sort_k(Sides s, int direct)
         uint32_t x[S], sum = 0, tot;
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-            x[k] = bin[tid * S + k];
+            x[k] = bin[sub_at(tid * S + k)];
             sum += x[k];
             if (x[k] > kRankBin) crowded = 1;
         }
         uint32_t run = block_excl_scan<kSortBlk>(sum, wsum, &tot);
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-            bin[tid * S + k] = run;
+            bin[sub_at(tid * S + k)] = run;
             run += x[k];
         }
-        if (tid == 0) bin[kSub] = n;
+        if (tid == 0) bin[sub_at(kSub)] = n;
     }
     __syncthreads();
     const bool exact = sh && side == 1;  // uniform: a bin spans several values, and S needs them in order
@@ -564,7 +584,7 @@ __global__ __launch_bounds__(kSortBlk) void sort_k(Sides s, int direct)
 #pragma unroll
         for (int q = 0; q < kSortPer; ++q)
             if ((uint32_t)(q * kSortBlk + tid) < n) {
-                rank[q] += bin[sub[q]];
+                rank[q] += bin[sub_at(sub[q])];
                 if (exact) ta[rank[q]] = v[q].a;
             }
         __syncthreads();
@@ -572,7 +592,7 @@ __global__ __launch_bounds__(kSortBlk) void sort_k(Sides s, int direct)
 #pragma unroll
             for (int q = 0; q < kSortPer; ++q)
                 if ((uint32_t)(q * kSortBlk + tid) < n) {
-                    const uint32_t p0 = bin[sub[q]], p1 = bin[sub[q] + 1], mine = rank[q];
+                    const uint32_t p0 = bin[sub_at(sub[q])], p1 = bin[sub_at(sub[q] + 1)], mine = rank[q];
                     uint32_t less = 0;
                     for (uint32_t p = p0; p < p1; ++p)
                         less += ta[p] < v[q].a || (ta[p] == v[q].a && p < mine) ? 1u : 0u;
@@ -992,7 +1012,7 @@ size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 size_t scatter_lds(int B, bool has_c) { return (size_t)B * 8 + (size_t)kCap * (has_c ? 14 : 10); }
 
-constexpr size_t kSortLds = (size_t)(kSub + 1) * 4 + (size_t)kCap * 4;
+constexpr size_t kSortLds = (size_t)kSubWords * 4 + (size_t)kCap * 4;
 
 }  // namespace
 
@@ -1005,7 +1025,7 @@ RegionPlan region_plan(int64_t nR, int64_t nS, int op_a, int op_c, int num_cus, 
     while (!pl.direct && pl.bits < kMaxBits && (n >> pl.bits) > kMeanRows) ++pl.bits;
     pl.B = 1 << pl.bits;
     pl.binBits = pl.bits + 4 < kMinBinBits ? kMinBinBits : (pl.bits + 4 > kMaxBinBits ? kMaxBinBits : pl.bits + 4);
-    pl.samples = (int64_t)8 * pl.B < 4096 ? 4096 : ((int64_t)8 * pl.B > 32768 ? 32768 : (int64_t)8 * pl.B);
+    pl.samples = (int64_t)16 * pl.B < 4096 ? 4096 : ((int64_t)16 * pl.B > 65536 ? 65536 : (int64_t)16 * pl.B);
     pl.rows = ceil_div(ceil_div(nR > 0 ? nR : 1, kMaxBlocks), kJoinBlk) * kJoinBlk;
     const int64_t blocks = nR > 0 && nS > 0 ? ceil_div(nR, pl.rows) : 0;
     // A condition on c inside intervals of a large share of S is the one thing that costs more
@@ -1129,7 +1149,7 @@ hipError_t region_count(const RegionPlan& pl, const join_rel_t& R, const join_re
             int32_t* sample = reinterpret_cast<int32_t*>(ws + pl.off_sample);
             sample_k<<<(unsigned)ceil_div(sR + sS, kBlk), kBlk, 0, st>>>(s.X[0], s.X[1], sR, sS, sample, s.zero,
                                                                        (uint32_t)pl.zero_words);
-            setup_k<<<1, kBlk, (size_t)4 << pl.binBits, st>>>(sample, sR + sS, pl.binBits, pl.bits,
+            setup_k<<<1, kBlk, (size_t)4 * padded<kMaxBinBits - 10>(1u << pl.binBits), st>>>(sample, sR + sS, pl.binBits, pl.bits,
                                                              reinterpret_cast<Hdr*>(ws),
                                                              reinterpret_cast<uint16_t*>(ws + pl.off_lut));
             // a workgroup per two CUs' worth of rows, whole tiles: its B counters are flushed once
