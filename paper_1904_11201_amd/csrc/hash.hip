@@ -1818,6 +1818,24 @@ __device__ __forceinline__ uint32_t sched_after(const Sched& s, bool need, uint3
     return nxi < s.U ? s.at(s.pos + 2) : s.U;
 }
 
+// A SIMD issues from its oldest ready wave first, so of the waves of a workgroup that has the CU to
+// itself, all with the same number of probe batches, the oldest finished a unit 9 us before the last
+// of 39 (write pass, 16M x 64M) and waited at its closing barrier while the CU's loads in flight
+// dwindled.  The waves of one SIMD (every fourth) take turns at each priority, batch by batch: the
+// wait falls to 2 us.  Write pass of one join, us: 16M x 64M 315 -> 302, 8M x 32M 160 -> 154,
+// 4M x 16M and 100K x 16M 72 -> 67, 1M x 4M 28 -> 26.  Where workgroups share the CU one fills the
+// other's waits, and it does not pay: a batch's passes 1550 -> 1580 together, one join's count pass
+// 178 -> 173 and 94 -> 97.  (The youngest always first in the write pass: no gain either.)
+__device__ __forceinline__ void take_turn(uint32_t round)
+{
+    switch ((uniform((uint32_t)threadIdx.x / (4 * kWave)) + round) & 3) {  // uniform
+    case 0: __builtin_amdgcn_s_setprio(0); break;
+    case 1: __builtin_amdgcn_s_setprio(1); break;
+    case 2: __builtin_amdgcn_s_setprio(2); break;
+    default: __builtin_amdgcn_s_setprio(3);
+    }
+}
+
 #ifndef JL_HASH_COUNT_BATCH
 #define JL_HASH_COUNT_BATCH 2
 #endif
@@ -2678,6 +2696,7 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
             } else {
                 if (SEMI) load_tuples<AOS, B>(g, un, 0, nx, nr);  // not loaded ahead in this mode
                 for (uint32_t e0 = 0; e0 < un.sN; e0 += B * kWriteLoad) {
+                    if constexpr (B == kJoinBlock) take_turn(e0 / (B * kWriteLoad));
                     uint32_t cx[kWriteLoad];
                     int32_t cr[kWriteLoad];
 #pragma unroll
