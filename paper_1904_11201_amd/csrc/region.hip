@@ -22,9 +22,9 @@
 // What bounds it: launches and dependent memory round trips up to 1M rows a side (every pass
 // moves 8 to 32 MB, 2 to 8 us at the copy rate, and takes 4 to 29), from 4M on the LDS work of
 // the sort and the partition's traffic.  Count pass of a band of w = 8 at 4M x 4M: sample and
-// setup 19 us, sizes 24, scatter 58, sort 79, intervals and counts 55.  The former design put
+// setup 22 us, sizes 24, scatter 58, sort 50, intervals and counts 55.  The former design put
 // every R row of a bucket against every S row of its red span, in 26 launches: 1M x 1M with a
-// condition on c 414 us of kernels, now 110; the count at 4M x 4M 1200, now 239.
+// condition on c 414 us of kernels, now 110; the count at 4M x 4M 1200, now 211.
 #include "region.hpp"
 #include "debug.hpp"
 
@@ -42,7 +42,7 @@ constexpr int kSortPer = kCap / kSortBlk;
 constexpr int kMeanRows = 2048;   // a bucket's mean size, at most (while B < kMaxBuckets)
 constexpr int kMaxBits = 13;      // 2^13 buckets: 64 KB of LDS state beside the scatter's tile
 constexpr int kMinBinBits = 10;   // at least one bin per thread of the setup workgroup
-constexpr int kMaxBinBits = 14;   // 64 KB of LDS counters
+constexpr int kMaxBinBits = 14;   // 68 KB of LDS counters, padding included
 constexpr int kSubBits = 12;      // value bins of one LDS sort: about one row each
 constexpr int kSub = 1 << kSubBits;
 constexpr uint32_t kRankBin = 64; // rows of a bin ranked one against the other, at most
@@ -490,6 +490,7 @@ constexpr uint32_t kSubWords = padded<kSubPad>(kSub) + 1;
 // of the bins: its rows only have to lie near each other.  direct: the input columns, one
 // workgroup per side; else workgroup i < 2B takes bucket i's first chunk, the others the list of
 // further chunks.
+// (4M rows a side: 50 us, 79 with unpadded bins and buckets of 16 samples, a few of which were merged.)
 // LDS: bins[kSub + 1] (padded) | one column of kCap rows, which stages a, then rid and c, into sorted order
 template <bool HAS_C>
 __global__ __launch_bounds__(kSortBlk) void sort_k(Sides s, int direct)
