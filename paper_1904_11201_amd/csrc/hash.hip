@@ -1229,7 +1229,7 @@ __device__ __forceinline__ void load_chunk(const JoinGeom& g, const Unit& un, Ch
         c.k[i] = 0u;
         if constexpr (RIDS) c.r[i] = 0u;
     }
-    if (un.rN > 0) {  // every unit has rN >= 1; the guard keeps the clamped index in bounds
+    if (un.rN > 0) {  // the write pass empties crowded units; the guard keeps the clamped index in bounds
 #pragma unroll
         for (int i = 0; i < kBuildItems; ++i) {
             const uint32_t e = (uint32_t)(i * B + tid);
@@ -2624,7 +2624,9 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
         uint64_t cursor = (raw_on ? raw_before : uniform(offs[u])) + (wv ? uniform(wo[(size_t)u * kWaveRec + wv]) : 0ull);
         const uint64_t wrec = uniform(wo[(size_t)u * kWaveRec + kWaveHalf + wv]);
         uint64_t cmany = cursor + (uint32_t)wrec;
-        const uint32_t semi_rows = (uint32_t)(wrec >> 32);  // the semi-join's rows of this wave
+        // the semi-join's rows of this wave; none for a crowded unit emptied above, whose rows are
+        // write_crowded_k's (in its empty table a probe may match markers, or walk without end)
+        const uint32_t semi_rows = un.sN > 0 ? (uint32_t)(wrec >> 32) : 0u;
 #if JL_DEBUG
         const uint64_t cursor0 = cursor, cmany0 = cmany;
 #endif

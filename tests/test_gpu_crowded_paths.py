@@ -1,0 +1,57 @@
+"""Hot build keys (hundreds of copies in one LDS table, so the unit is joined by sorted entries)
+through each way into the hash join, against the oracle's pairs."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1904_11201_amd import datagen
+from tests.gpu_util import canon_gpu, dev_rel, gpu, log, need_gpu
+
+
+def _key_of_hash(h):
+    """The int32 key whose hash (common.hpp hmix) is h: the finaliser's steps undone in turn."""
+    m = 0xFFFFFFFF
+    h ^= h >> 16
+    h = h * pow(0xC2B2AE35, -1, 1 << 32) & m
+    h ^= h >> 13 ^ h >> 26
+    h = h * pow(0x85EBCA6B, -1, 1 << 32) & m
+    h ^= h >> 16
+    return h - (1 << 32) if h >= 1 << 31 else h
+
+
+# a key of each pair of top hash bits (the partition's, which an empty slot's marker is made from),
+# and the one whose hash is the marker of a table made from hash 0
+HOT = [2, 1, 3, 5, _key_of_hash(0x80000000)]
+
+
+def _hot_join(hot, nR, nS, copies, seed=91, domain=10_000_000):
+    """R: nR uniform keys and `copies` rows of each hot key; S: nS uniform keys and 40 of each."""
+    g = datagen.rng_for(seed)
+    rk = np.concatenate([datagen.uniform_keys(g, nR, 0, domain), np.repeat(np.array(hot, np.int32), copies)])
+    sk = np.concatenate([datagen.uniform_keys(g, nS, 0, domain), np.repeat(np.array(hot, np.int32), 40)])
+    R = datagen.Rel(key=g.permutation(rk).astype(np.int32), rid=g.permutation(len(rk)).astype(np.int32))
+    return R, datagen.Rel(key=g.permutation(sk).astype(np.int32), rid=g.permutation(len(sk)).astype(np.int32))
+
+
+def _expect(R, S):
+    n, ref = oracle.equi_sortmerge(R.key, S.key, Rrid=R.rid, Srid=S.rid)
+    assert len(ref) == n
+    return ref
+
+
+@gpu
+@pytest.mark.parametrize("hot,copies", [([k], 1000) for k in HOT] + [(HOT, 300), (HOT, 1000)])
+def test_semi_join_of_a_hot_build_key(hot, copies):
+    """More than 2^21 probe rows, so the count pass records the matching ones, in partitions of one
+    chunk: the record covers the crowded units, which another kernel writes."""
+    need_gpu()
+    from paper_1904_11201_amd.join import hash_join
+    R, S = _hot_join(hot, 200_000, (1 << 21) + 1001, copies)
+    ref = _expect(R, S)
+    dR, dS = dev_rel(R), dev_rel(S)
+    log(f"semi-join, hot keys {hot}, {copies} copies each")
+    got = canon_gpu(hash_join(dR, dS, prefilter=True))
+    assert np.array_equal(got, ref)
+    assert np.array_equal(canon_gpu(hash_join(dR, dS)), ref)
