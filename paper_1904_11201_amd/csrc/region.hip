@@ -51,7 +51,8 @@ constexpr int kJoinWaves = kJoinBlk / kWave;
 constexpr int64_t kMaxBlocks = 4096;  // R blocks of the count pass
 // Intervals up to this length are walked lane by lane: neighbouring rows' intervals start close
 // together, so each step's loads are nearly consecutive.  Longer ones are walked by the whole
-// wave, one S row (condition on c) or one R row (none) at a time.
+// wave: without a condition on c one R row at a time, with one by whichever of two ways has fewer
+// steps (by_rows).
 constexpr uint32_t kSerial = 32;
 
 struct Hdr {
@@ -637,7 +638,8 @@ struct Join {
     int64_t w;
     uint32_t rows;  // R rows per unit (a multiple of kJoinBlk)
     uint32_t U;     // units
-    int Y;          // S tiles: unit u = R block u / Y, tile u % Y
+    int log_y;      // 2^log_y shares of an R block's work: unit u = R block u >> log_y, share the bits below
+    int tiled;      // the shares are S tiles (else equal parts of every interval)
     int direct;     // S is one bucket
     const Hdr* h;
     const uint16_t* lut;
@@ -752,9 +754,69 @@ __device__ __forceinline__ uint32_t wave_max_u(uint32_t v)
     return uniform(v);
 }
 
-// Matches of this lane's R row among the S rows [l, h) (l == h: none), by the whole wave.  Long
-// intervals: the wave walks the union of its rows' intervals one S row at a time, the S value in
-// a scalar register; where every interval of the wave covers the S row nothing but c is compared.
+// How a wave walks long intervals under a condition on c.  By S rows: from the first to the last S
+// row of any interval, every lane comparing its own R row; best when the intervals overlap.  By R
+// rows: each interval by 64 lanes, four rows' loads in flight; best when R is sparse, and the
+// intervals leave gaps or overlap little (1K x 1M, w = 1000: intervals of 125 rows spread over 64K;
+// count 3710 us by S rows, 85 by R rows).  A step by R rows has a load's latency for four of them and
+// is taken for eight steps by S rows.
+constexpr int kRowsAtOnce = 4;
+
+__device__ __forceinline__ bool by_rows(uint32_t len, uint32_t span)
+{
+    return 8ull * wave_sum64((len + kWave - 1) / kWave) < span;
+}
+
+// By R rows: f(x, r, in, v) for kRowsAtOnce R rows at a time (x, r: theirs) and 64 S rows of each
+// (v: the lane's, if it has one).
+template <typename Load, typename F>
+__device__ __forceinline__ void walk_by_rows(int32_t x, int32_t r, uint32_t l, uint32_t len, Load load, F f)
+{
+    for (int q0 = 0; q0 < kWave; q0 += kRowsAtOnce) {
+        uint32_t first[kRowsAtOnce], n[kRowsAtOnce], longest = 0;
+#pragma unroll
+        for (int i = 0; i < kRowsAtOnce; ++i) {
+            n[i] = (uint32_t)__builtin_amdgcn_readlane((int)len, q0 + i);
+            first[i] = (uint32_t)__builtin_amdgcn_readlane((int)l, q0 + i);
+            longest = max(longest, n[i]);
+        }
+        for (uint32_t k0 = 0; k0 < longest; k0 += kWave) {
+            const uint32_t k = k0 + lane_id();
+            decltype(load(0u)) v[kRowsAtOnce];
+#pragma unroll
+            for (int i = 0; i < kRowsAtOnce; ++i) v[i] = load(k < n[i] ? first[i] + k : 0u);
+#pragma unroll
+            for (int i = 0; i < kRowsAtOnce; ++i)
+                f(__builtin_amdgcn_readlane(x, q0 + i), __builtin_amdgcn_readlane(r, q0 + i), k < n[i], v[i]);
+        }
+    }
+}
+
+// By S rows: f(j, v, k, covered) for the S rows [j0, j1) in turn, and some beyond j1; lane k's v is
+// load(j), loaded 64 rows at a time, the next 64 in flight meanwhile.  covered: a constant, true where
+// j lies in [i0, i1).  (By a scalar load for a row or eight rows, each waits for its own round trip:
+// 1K x 1M, <, count 1320 us, 540 this way.)
+template <typename Load, typename F>
+__device__ __forceinline__ void walk_by_s(uint32_t j0, uint32_t j1, uint32_t i0, uint32_t i1, Load load, F f)
+{
+    constexpr uint32_t G = 8;
+    auto next = load(min(j0 + lane_id(), j1 - 1));
+    for (uint32_t j = j0; j < j1; j += kWave) {
+        const auto v = next;
+        if (j1 - j > (uint32_t)kWave) next = load(min(j + kWave + lane_id(), j1 - 1));
+        const uint32_t n = min(j1 - j, (uint32_t)kWave);
+        auto rows = [&](auto covered) {
+            for (uint32_t k = 0; k < n; k += G)
+#pragma unroll
+                for (uint32_t q = 0; q < G; ++q) f(j + k + q, v, k + q, covered);
+        };
+        if (j >= i0 && j + kWave <= i1) rows(std::true_type{});  // uniform
+        else rows(std::false_type{});
+    }
+}
+
+// Matches of this lane's R row among the S rows [l, h) (l == h: none), by the whole wave; of long
+// intervals walked by R rows, the lane's share of the wave's matches.
 template <int OPC>
 __device__ __forceinline__ uint64_t count_in(const Join& g, int32_t xc, uint32_t l, uint32_t h)
 {
@@ -774,26 +836,22 @@ __device__ __forceinline__ uint64_t count_in(const Join& g, int32_t xc, uint32_t
         }
         return n;
     }
-    const cptr<int32_t> Sc = as_const(g.Sc);
     const uint32_t j0 = wave_min_u(len ? l : ~0u), j1 = wave_max_u(len ? h : 0u);
-    uint32_t i0 = wave_max_u(len ? l : 0u), i1 = wave_min_u(len ? h : ~0u);
-    if (i1 < i0) i0 = i1 = j1;  // no S row is in every interval
-    auto checked = [&](uint32_t a, uint32_t b) {
-        for (uint32_t j = a; j < b; ++j) n += j >= l && j < h && holds_c<OPC>(xc, Sc[j]) ? 1u : 0u;
-    };
-    checked(j0, i0);
-    constexpr uint32_t G = 8;
-    uint32_t j = i0, m = 0;
-    for (; j + G <= i1; j += G) {
-        int32_t sc[G];
-#pragma unroll
-        for (uint32_t k = 0; k < G; ++k) sc[k] = Sc[j + k];
-#pragma unroll
-        for (uint32_t k = 0; k < G; ++k) m += holds_c<OPC>(xc, sc[k]) ? 1u : 0u;
+    if (by_rows(len, j1 - j0)) {  // uniform
+        uint64_t m = 0;
+        walk_by_rows(xc, 0, l, len, [&](uint32_t i) { return g.Sc[i]; },
+                     [&](int32_t x, int32_t, bool in, int32_t sc) { m += in && holds_c<OPC>(x, sc) ? 1u : 0u; });
+        return m;
     }
-    if (len) n += m;
-    checked(j, j1);
-    return n;
+    // the S rows in all of the wave's intervals: there nothing but c is compared
+    const uint32_t i0 = wave_max_u(len ? l : 0u), i1 = wave_min_u(len ? h : ~0u);
+    uint32_t m = 0;
+    walk_by_s(j0, j1, i0, i1, [&](uint32_t j) { return g.Sc[j]; }, [&](uint32_t j, int32_t v, uint32_t k, auto covered) {
+        const int32_t sc = __builtin_amdgcn_readlane(v, k);
+        if constexpr (decltype(covered)::value) m += holds_c<OPC>(xc, sc) ? 1u : 0u;
+        else n += j - l < len && holds_c<OPC>(xc, sc) ? 1u : 0u;
+    });
+    return len ? n + m : n;
 }
 
 // The pairs of this lane's R row (row id rr) with the S rows [l, h) from slot `at` on; the wave's
@@ -806,11 +864,12 @@ __device__ __forceinline__ void write_in(const Join& g, int32_t xc, int32_t rr, 
     const uint32_t len = h - l;
     const uint32_t longest = wave_max_u(len);
     if (longest == 0) return;
-    auto emit = [&](bool match, int32_t srid) {
+    auto emit_of = [&](bool match, int32_t rrid, int32_t srid) {
         const uint64_t m = ballot(match);
-        if (match) out[at + mask_rank(m)] = make_int2(rr, srid);
+        if (match) out[at + mask_rank(m)] = make_int2(rrid, srid);
         at += (uint64_t)__builtin_popcountll(m);
     };
+    auto emit = [&](bool match, int32_t srid) { emit_of(match, rr, srid); };
     if (longest <= kSerial) {
         if (OPC == JOIN_OP_NONE && part) {  // uniform: the first workgroup writes short intervals
             at += wave_sum64(len);
@@ -835,30 +894,48 @@ __device__ __forceinline__ void write_in(const Join& g, int32_t xc, int32_t rr, 
             at += n;
         }
     } else {
-        const cptr<int32_t> Sc = as_const(g.Sc);
-        const cptr<int32_t> Sr = as_const(g.Sr);
         const uint32_t j0 = wave_min_u(len ? l : ~0u), j1 = wave_max_u(len ? h : 0u);
-        for (uint32_t j = j0; j < j1; ++j) emit(j >= l && j < h && holds_c<OPC>(xc, Sc[j]), Sr[j]);
+        auto row_of = [&](uint32_t j) { return make_int2(g.Sc[j], g.Sr[j]); };
+        if (by_rows(len, j1 - j0)) {  // uniform
+            walk_by_rows(xc, rr, l, len, row_of,
+                         [&](int32_t x, int32_t r, bool in, int2 s) { emit_of(in && holds_c<OPC>(x, s.x), r, s.y); });
+            return;
+        }
+        walk_by_s(j0, j1, j1, j1, row_of, [&](uint32_t j, int2 v, uint32_t k, auto) {
+            emit(j - l < len && holds_c<OPC>(xc, __builtin_amdgcn_readlane(v.x, k)), __builtin_amdgcn_readlane(v.y, k));
+        });
     }
 }
 
-// Unit u: R rows [r0, r1) and S rows [t0, t1).
-__device__ __forceinline__ void unit_of(const Join& g, uint32_t u, uint32_t& r0, uint32_t& r1, uint32_t& t0,
-                                        uint32_t& t1)
+// Unit u: R rows [r0, r1) and share y of them.
+__device__ __forceinline__ void unit_of(const Join& g, uint32_t u, uint32_t& r0, uint32_t& r1, uint32_t& y)
 {
-    const uint32_t rb = u / (uint32_t)g.Y, y = u - rb * (uint32_t)g.Y;
+    const uint32_t rb = u >> g.log_y;
+    y = u - (rb << g.log_y);
     r0 = rb * g.rows;
     r1 = g.nR - r0 < g.rows ? g.nR : r0 + g.rows;
-    t0 = (uint32_t)((uint64_t)g.nS * y / (uint32_t)g.Y);
-    t1 = (uint32_t)((uint64_t)g.nS * (y + 1) / (uint32_t)g.Y);
 }
 
-// Both intervals of a row inside the tile [t0, t1): f(first, last + 1).  != has the rows before
-// and after its equal run, every other operator one interval.
-template <typename F>
-__device__ __forceinline__ void each_interval(const Join& g, uint32_t lo, uint32_t hi, uint32_t t0,
-                                              uint32_t t1, bool valid, F f)
+// Share y of [0, n).
+__device__ __forceinline__ uint32_t share_at(const Join& g, uint32_t n, uint32_t y)
 {
+    return (uint32_t)((uint64_t)n * y >> g.log_y);
+}
+
+// Share y of a row's intervals: f(first, last + 1).  != has the rows before and after its equal
+// run, every other operator one interval.  The intervals of =, and of a band, lie where the row's value
+// does, so a tile of S would hold few rows' (the shares are parts of the interval); the others'
+// reach an end of S, and S rows are best shared by all rows of a wave (the shares are tiles).
+template <typename F>
+__device__ __forceinline__ void each_interval(const Join& g, uint32_t lo, uint32_t hi, uint32_t y, bool valid, F f)
+{
+    if (!g.tiled) {  // uniform
+        const uint32_t n = valid ? hi - lo : 0u;
+        const uint32_t a = share_at(g, n, y), b = share_at(g, n, y + 1);
+        f(a < b ? lo + a : 0u, a < b ? lo + b : 0u);
+        return;
+    }
+    const uint32_t t0 = share_at(g, g.nS, y), t1 = share_at(g, g.nS, y + 1);
     auto clip = [&](uint32_t a, uint32_t b) {
         const uint32_t l = max(a, t0), h = min(b, t1);
         const bool some = valid && l < h;
@@ -883,8 +960,8 @@ __global__ __launch_bounds__(kJoinBlk) void region_count_k(Join g, uint64_t* __r
     const int wv = uniform((int32_t)(threadIdx.x / kWave));
     const uint32_t u = blockIdx.x;
     if (u == 0 && threadIdx.x == 0) *g.stamp_at = g.stamp;  // for the write pass
-    uint32_t r0, r1, t0, t1;
-    unit_of(g, u, r0, r1, t0, t1);
+    uint32_t r0, r1, y;
+    unit_of(g, u, r0, r1, y);
     Hdr h{};
     if (!g.direct) h = *g.h;
     uint64_t n = 0;
@@ -893,12 +970,12 @@ __global__ __launch_bounds__(kJoinBlk) void region_count_k(Join g, uint64_t* __r
         const bool valid = i < r1;
         uint32_t lo = 0, hi = 0;
         interval(g, h, g.Ra[valid ? i : r1 - 1], valid, win[wv], lo, hi);
-        if (valid && t0 == 0) {
+        if (valid && y == 0) {
             g.lo[i] = lo;
             g.hi[i] = hi;
         }
         const int32_t xc = OPC != JOIN_OP_NONE && valid ? g.Rc[i] : 0;
-        each_interval(g, lo, hi, t0, t1, valid,
+        each_interval(g, lo, hi, y, valid,
                       [&](uint32_t a, uint32_t b) { n += count_in<OPC>(g, xc, a, b); });
     }
     const uint64_t wt = wave_sum64(n);
@@ -957,8 +1034,8 @@ __global__ __launch_bounds__(kJoinBlk) void region_write_k(Join g, const uint64_
     if (*total > cap || *g.stamp_at != g.stamp) return;
     const int wv = uniform((int32_t)(threadIdx.x / kWave));
     const uint32_t u = blockIdx.x / parts, part = blockIdx.x - u * parts;
-    uint32_t r0, r1, t0, t1;
-    unit_of(g, u, r0, r1, t0, t1);
+    uint32_t r0, r1, y;
+    unit_of(g, u, r0, r1, y);
     uint64_t at = uniform(g.counts[u] + g.wave_off[(uint64_t)u * kJoinWaves + wv]);
 #if JL_DEBUG
     const uint64_t at0 = at;
@@ -969,7 +1046,7 @@ __global__ __launch_bounds__(kJoinBlk) void region_write_k(Join g, const uint64_
         const uint32_t lo = valid ? g.lo[i] : 0u, hi = valid ? g.hi[i] : 0u;
         const int32_t xc = OPC != JOIN_OP_NONE && valid ? g.Rc[i] : 0;
         const int32_t rr = valid ? g.Rr[i] : 0;
-        each_interval(g, lo, hi, t0, t1, valid,
+        each_interval(g, lo, hi, y, valid,
                       [&](uint32_t a, uint32_t b) { write_in<OPC>(g, xc, rr, a, b, at, out, part, parts); });
     }
 #if JL_DEBUG
@@ -1030,11 +1107,14 @@ RegionPlan region_plan(int64_t nR, int64_t nS, int op_a, int op_c, int num_cus, 
     pl.rows = ceil_div(ceil_div(nR > 0 ? nR : 1, kMaxBlocks), kJoinBlk) * kJoinBlk;
     const int64_t blocks = nR > 0 && nS > 0 ? ceil_div(nR, pl.rows) : 0;
     // A condition on c inside intervals of a large share of S is the one thing that costs more
-    // than the sort: it is cut into S tiles until there are waves for every SIMD.
-    const bool wide = op_a != JOIN_OP_EQ && op_a != JOIN_OP_BAND;
+    // than the sort: it is cut into S tiles until there are waves for every SIMD.  The intervals of a
+    // band or of equal values may be long as well (w, frequent values), and the R blocks few: cut into
+    // parts until there is a unit for every CU (1K x 1M, w = 100,000: count 7460 us whole,
+    // 114 in 64 parts).
+    pl.tiled = op_a != JOIN_OP_EQ && op_a != JOIN_OP_BAND;
     pl.Y = 1;
-    if (has_c && wide)
-        while (pl.Y < 64 && blocks * pl.Y < (int64_t)num_cus * 8 && nS / (2 * pl.Y) >= 256) pl.Y *= 2;
+    if (has_c)
+        while (pl.Y < 64 && blocks * pl.Y < (int64_t)num_cus * (pl.tiled ? 8 : 1) && nS / (2 * pl.Y) >= 256) pl.Y *= 2;
     pl.U = blocks * pl.Y;
     size_t off = 256;
     auto take = [&](size_t bytes) {
@@ -1099,7 +1179,8 @@ static Join join_of(const RegionPlan& pl, const join_rel_t& R, const join_rel_t&
     g.w = p.op_a == JOIN_OP_BAND ? (int64_t)p.w : 0;
     g.rows = (uint32_t)pl.rows;
     g.U = (uint32_t)pl.U;
-    g.Y = pl.Y;
+    g.log_y = __builtin_ctz((unsigned)pl.Y);
+    g.tiled = pl.tiled;
     g.direct = pl.direct;
     g.h = reinterpret_cast<const Hdr*>(ws);
     g.lut = reinterpret_cast<const uint16_t*>(ws + pl.off_lut);

@@ -11,7 +11,7 @@ struct RegionPlan {
     int64_t samples;             // rows sampled per side for the bins
     int64_t rows;                // R rows per unit
     int64_t U;                   // units: R blocks x Y
-    int Y;                       // S tiles per R block
+    int Y, tiled;                // shares of an R block's work, a power of two; 1: they are S tiles
     size_t off_zero, zero_words; // cleared first: bucket sizes, arrivals, counters
     size_t off_base, off_cur, off_extra, off_lut, off_sample, off_id;
     size_t off_pR, off_pS;       // bucketed rows
