@@ -13,7 +13,7 @@ struct RegionPlan {
     int64_t U;                   // units: R blocks x Y
     int Y, tiled;                // shares of an R block's work, a power of two; 1: they are S tiles
     size_t off_zero, zero_words; // cleared first: bucket sizes, arrivals, counters
-    size_t off_base, off_cur, off_extra, off_lut, off_sample, off_id;
+    size_t off_base, off_cur, off_extra, off_lut, off_split, off_sample, off_id;
     size_t off_pR, off_pS;       // bucketed rows
     size_t off_Ra, off_Rc, off_Rr, off_Sa, off_Sc, off_Sr;  // sorted columns
     size_t off_lo, off_hi;       // each R row's interval of sorted S rows
