@@ -830,8 +830,8 @@ __device__ __forceinline__ uint32_t plan_part(const PartPlan& q, int p, PartInfo
 constexpr int kRecBitsShift = 24;
 constexpr int kRecShared = 28;
 constexpr int kRecOrder = 29;
-// Set by the count pass for a unit whose table was crowded: write_crowded_k writes its pairs, and
-// the write pass takes it as empty.
+// Set by the count pass for a crowded unit (its table walked far, or long runs of matches):
+// write_crowded_k writes its pairs, and the write pass takes it as empty.
 constexpr int kRecCrowded = 30;
 __host__ __device__ __forceinline__ uint4 unit_rec(const PartInfo& pi, uint32_t local, uint32_t cap)
 {
@@ -1154,6 +1154,10 @@ constexpr int kSlots = 4;
 #endif
 constexpr int kProbe = JL_HASH_PROBE;  // keys probed together per thread
 constexpr int kEmitSort = 8;  // a probe with at most this many matches orders them in registers
+// A probe with more matches than this has the unit written from its sorted entries: ordering and emitting
+// them by walks takes longer than the sort (joins of 9000 rows with one hot key, probed in every unit:
+// 60 copies 263 us by walks, 333 sorted; 90 copies 402 and 344, 200 copies 1113 and 428).
+constexpr uint32_t kEmitTable = 72;
 
 __host__ __device__ constexpr uint32_t table_buckets(uint32_t rN)
 {
@@ -1184,6 +1188,10 @@ constexpr uint32_t kOverflow = 1u << 30;
 // The dynamic LDS of the count and write passes (the table), at file scope for the functions that
 // are not inlined.
 extern __shared__ uint4 join_lds[];
+
+// Count pass: whether a probe of the unit had more than kEmitTable matches.  Such a probe walks, so this is
+// written where walks are, and the probe loop keeps no register for it.
+__shared__ uint32_t long_runs;
 
 struct Table {
     const uint4* keys;    // [nb]: the 4 keys of each bucket
@@ -1292,13 +1300,36 @@ __device__ __forceinline__ uint32_t marker_hash(const JoinGeom& g, const Unit& u
     return HASHED && un.bits >= 2 ? (uint32_t)g.rt[un.rBeg].x : 0u;
 }
 
-// crowded (count pass): a word of LDS, zero on entry; set when an entry found no slot within
-// kWalkMax buckets of its own, because a key has hundreds of entries in the chunk: the walk of
-// every entry and probe that meets its buckets would pass them all (67 ms for a build of 0.8M Zipf
-// keys).  Such a unit is joined by its sorted entries instead (see below), in both passes.  The
-// write pass, which never builds the table of a unit found crowded, walks without a limit: its
-// table may come out a little more crowded than the count pass's, as the inserts race.
-constexpr uint32_t kWalkMax = 64;
+// Keys with many entries in a chunk make the table's walks long, of every entry and probe that meets
+// their buckets; past a point the unit is joined by its sorted entries instead (see below), in both
+// passes (a build of 0.8M Zipf keys against 3.9M rows: 67 ms by walks, 0.8 sorted).  The count pass
+// decides it, by what an entry knows before it walks: the claims of its two buckets, about the number
+// of its key's entries so far, and how many entries of the unit walked before it.  Once
+// claims / Crowd::claims + walkers / Crowd::walkers exceeds 1 the unit is crowded, and entries that
+// come then do not walk.  (Counting steps in the walk itself made walks 15% slower; letting the
+// walkers wait until the others are placed, 10 to 50%.)  crowded: two words of LDS, zero on entry; [0] is
+// set for a crowded unit, [1] counts the walkers.  The write pass, which never builds the table of a unit
+// found crowded, walks without a limit.
+//
+// The line is fitted to builds of 9K and 1M rows with 1 to 46 keys of 60 to 4400 copies in a table: one
+// key of 560 copies reaches it where the unit has one round of B probes, of 360 with 16 rounds; many
+// keys with 9500 and 2000 entries together.  Sorting 9K entries takes 100 to 120 us a pass, and each round
+// of probes 5 us.  (With the line at a walk of 64 buckets for all units and a sort of 145 us, builds
+// with keys of 80 to 400 copies took up to 3.5 times the time of their walks: 9000 rows against 10K, one
+// key of 160, 96 us by walks, 335 sorted; 400 copies, 246 and 350.)
+struct Crowd {
+    uint32_t claims, walkers;
+
+    __device__ __forceinline__ bool reached(uint32_t c, uint32_t w) const { return c * walkers + w * claims > claims * walkers; }
+};
+
+template <int B>
+__device__ __forceinline__ Crowd crowd_line(const Unit& un)
+{
+    const uint32_t lg = 31u - (uint32_t)__builtin_clz((un.sN + B - 1) / B | 1u);  // of the rounds
+    const uint32_t c = lg < 8 ? 600 - 53 * lg : 200, w = (lg & 1 ? 5955u : 8440u) >> lg / 2;
+    return Crowd{c * (un.rN + 6144) >> 14, (w * un.rN >> 13) + 1};
+}
 
 template <bool RIDS, bool HASHED, int B, bool CLEARED = false>
 __device__ __forceinline__ Table insert_chunk(const JoinGeom& g, const Unit& un, const Chunk<RIDS>& c,
@@ -1326,18 +1357,19 @@ __device__ __forceinline__ Table insert_chunk(const JoinGeom& g, const Unit& un,
             uint32_t b = second ? b2 : b1;
             uint32_t old = atomicAdd(&cnt[b], 1u);
             if (old >= (uint32_t)kSlots) {
+                const uint32_t first = old;
                 b = second ? b1 : b2;
                 old = atomicAdd(&cnt[b], 1u);
                 if (old >= (uint32_t)kSlots) {
-                    b = b2;
-                    uint32_t steps = 0;
-                    do {  // ends: 4 * nb slots > rN entries
-                        b = next_bucket(b, nb);
-                        old = atomicAdd(&cnt[b], 1u);
-                    } while (old >= (uint32_t)kSlots && (RIDS || ++steps < kWalkMax));
-                    if (!RIDS && old >= (uint32_t)kSlots) {  // goes anywhere: the table is not used
-                        *crowded = 1;
+                    if (!RIDS && crowd_line<B>(un).reached(min(first, old), atomicAdd(&crowded[1], 1u))) {
+                        crowded[0] = 1;  // goes anywhere: the table is not used
                         old = 0;
+                    } else {
+                        b = b2;
+                        do {  // ends: 4 * nb slots > rN entries
+                            b = next_bucket(b, nb);
+                            old = atomicAdd(&cnt[b], 1u);
+                        } while (old >= (uint32_t)kSlots);
                     }
                 }
             }
@@ -1455,8 +1487,10 @@ __device__ __forceinline__ uint32_t probe_count(const Table& t, int bits, const 
     if (ballot(any)) {
 #pragma unroll
         for (int i = 0; i < N; ++i)
-            if (walk[i])
+            if (walk[i]) {
                 walk_on<MARKED>(t, x[i], b1[i], b2[i], [&](uint32_t, uint32_t hm) { h[i] += __builtin_popcount(hm); });
+                if (h[i] > kEmitTable) long_runs = 1;
+            }
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -1953,9 +1987,10 @@ __device__ __forceinline__ void load_keys(const JoinGeom& g, const Unit& un, uin
 
 // ------------------------------------------------------------------------ crowded units --
 // A chunk with keys of hundreds of entries is sorted in LDS instead of hashed: the matches of a
-// probe are then one run, found by two binary searches whatever its length.  Sorting takes about
-// 15 us for 9K entries and a probe 28 LDS reads, so only units whose table would be walked take
-// this path; the code is kept out of the kernels' loops.
+// probe are then one run, found by two binary searches whatever its length.  Sorting takes 100 to
+// 120 us for 9K entries and a probe 28 LDS reads, so only units whose table would be walked far
+// (crowd_line), and in the write pass units with long runs of matches (kEmitTable), take this path; the
+// code is kept out of the kernels' loops.
 constexpr uint32_t kWaveRun = 64;  // longer runs are written by the whole wave
 
 // What the functions below need of their unit, in LDS: they are not inlined, and arguments by
@@ -1977,20 +2012,53 @@ __device__ __forceinline__ void set_crowded(const JoinGeom& g, const Unit& un)
     __syncthreads();
 }
 
-// Sorts v[0, N), N a power of two, by a bitonic network over B threads.
-template <int B, typename T>
+// Steps j, j / 2, .. of stage k of a bitonic network over v[0, N), S of them, in registers between one
+// read and one write of v.
+template <int S, int B, typename T>
+__device__ __forceinline__ void bitonic_steps(T* v, uint32_t N, uint32_t k, uint32_t j)
+{
+    constexpr int M = 1 << S;  // values j >> (S - 1) apart, which those steps compare with each other
+    const uint32_t d = (uint32_t)__builtin_ctz(j) - (S - 1);
+    __syncthreads();
+    for (uint32_t g = threadIdx.x; g < N / M; g += B) {
+        const uint32_t e = ((g >> d) << (d + S)) | (g & ((1u << d) - 1));
+        const T flip = (e & k) == 0 ? (T)0 : ~(T)0;  // descending: ascending of the complements
+        T x[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) x[m] = v[e + ((uint32_t)m << d)] ^ flip;
+#pragma unroll
+        for (int h = M / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+                if (!(m & h)) {
+                    const T a = x[m], b = x[m | h];
+                    x[m] = min(a, b);
+                    x[m | h] = max(a, b);
+                }
+#pragma unroll
+        for (int m = 0; m < M; ++m) v[e + ((uint32_t)m << d)] = x[m] ^ flip;
+    }
+}
+
+// Sorts v[0, N), N a power of two, by a bitonic network over B threads, up to S steps at a time: 40
+// passes over 16K values with 3, 105 one by one.  S is what the count kernels' registers bear: a
+// called function's are not the caller's to keep, and every unit pays for what it then moves
+// aside.  (3 steps cost the unpartitioned count 0.6 of 28 us, 2 nothing; all values of a thread in
+// registers, and most steps between lanes, sorted in 60% of the time, but cost all counts 6%.)
+template <int B, int S, typename T>
 __device__ void bitonic(T* v, uint32_t N)
 {
     for (uint32_t k = 2; k <= N; k *= 2)
-        for (uint32_t j = k / 2; j > 0; j /= 2) {
-            __syncthreads();
-            for (uint32_t i = threadIdx.x; i < N / 2; i += B) {
-                const uint32_t x = 2 * j * (i / j) + i % j, y = x + j;
-                const T a = v[x], b = v[y];
-                if ((a > b) == ((x & k) == 0)) {
-                    v[x] = b;
-                    v[y] = a;
-                }
+        for (uint32_t j = k / 2; j > 0;) {
+            if (S >= 3 && j >= 4) {
+                bitonic_steps<3, B>(v, N, k, j);
+                j >>= 3;
+            } else if (j >= 2) {
+                bitonic_steps<2, B>(v, N, k, j);
+                j >>= 2;
+            } else {
+                bitonic_steps<1, B>(v, N, k, j);
+                j >>= 1;
             }
         }
     __syncthreads();
@@ -2026,8 +2094,8 @@ __device__ __forceinline__ void sort_chunk()
         else
             reinterpret_cast<uint32_t*>(join_lds)[e] = e < rN ? k : ~0u;
     }
-    if constexpr (RIDS) bitonic<B>(reinterpret_cast<uint64_t*>(join_lds), N);
-    else bitonic<B>(reinterpret_cast<uint32_t*>(join_lds), N);
+    if constexpr (RIDS) bitonic<B, 3>(reinterpret_cast<uint64_t*>(join_lds), N);
+    else bitonic<B, AOS ? 3 : 2>(reinterpret_cast<uint32_t*>(join_lds), N);
 }
 
 // The run of key x among the n sorted entries.
@@ -2179,7 +2247,7 @@ __device__ __attribute__((noinline)) UnitCount count_crowded()
 // unit and wave, where the wave's pairs start inside the unit's output range, so the write pass
 // needs no shared cursor and every pair lands at a position that depends on the input and the
 // plan alone.  Entry 0 of a unit (wave 0 starts at 0) instead holds 1 when some probe of the
-// unit has more than kEmitSort entries in its table, plus 2 when the table was crowded.  Inside a
+// unit has more than kEmitSort entries in its table, plus 2 for a crowded unit.  Inside a
 // wave's range the pairs of probes with at most two matches come first, in (batch, tuple, lane)
 // order, then those of probes with more, in the order the wave queued them; the second half of the
 // unit's record holds, per wave, where that second block starts inside the wave's range.
@@ -2205,7 +2273,7 @@ template <int B, typename Between>
 __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_many, bool multi,
                                             uint32_t semi_rows, uint32_t u, uint64_t* __restrict__ counts,
                                             uint64_t* __restrict__ wave_off, uint64_t* sh, uint32_t* rec_word,
-                                            bool crowded, uint64_t* unit_pub, Between between)
+                                            bool crowded, uint64_t* unit_pub, uint64_t* pub, Between between)
 {
     const uint64_t wt = wave_sum64(lane_total);
     const uint64_t wmany = wave_sum64(lane_many);
@@ -2216,20 +2284,23 @@ __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_m
         wave_off[(size_t)u * kWaveRec + kWaveHalf + wv] = (wt - wmany) | ((uint64_t)semi_rows << 32);
     }
     __syncthreads();
-    if (threadIdx.x < (B / kWave)) {
-        uint64_t before = 0, sum = 0, any = 0;
-#pragma unroll
-        for (int w = 0; w < (B / kWave); ++w) {
-            const uint64_t v = sh[w];
-            const uint64_t c = v & ~(1ull << 63);
-            before += w < (int)threadIdx.x ? c : 0ull;
-            sum += c;
-            any |= v >> 63;
-        }
-        wave_off[(size_t)u * kWaveRec + threadIdx.x] = threadIdx.x == 0 ? any | (crowded ? 2u : 0u) : before;
-        if (threadIdx.x == 0) {
-            store_shared(&counts[u], sum);
-            if (unit_pub) __hip_atomic_store(&unit_pub[u], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x < kWave) {
+        constexpr uint32_t W = B / kWave;
+        const uint32_t w = threadIdx.x;
+        const uint64_t v = sh[w < W ? w : 0u];
+        const uint64_t c = w < W ? v & ~(1ull << 63) : 0ull;
+        const uint64_t inc = wave_incl_scan64(c);
+        const bool any = ballot(w < W && v >> 63) != 0;
+        crowded = crowded || long_runs;
+        if (w < W)
+            wave_off[(size_t)u * kWaveRec + w] = w == 0 ? (any ? 1u : 0u) | (crowded ? 2u : 0u) : inc - c;
+        if (w == W - 1) {
+            if (pub && crowded) {  // told to the host before the unit's count: it is read with the total
+                __hip_atomic_store(pub + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                drain();
+            }
+            store_shared(&counts[u], inc);
+            if (unit_pub) __hip_atomic_store(&unit_pub[u], inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             const uint32_t flags = (any ? 1u << kRecOrder : 0u) | (crowded ? 1u << kRecCrowded : 0u);
             if (flags && rec_word) atomicOr(rec_word, flags);
         }
@@ -2295,8 +2366,9 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
     const uint32_t U = unit_total(g);
     if (g.stamp_at && blockIdx.x == 0 && threadIdx.x == 0) *g.stamp_at = g.unit_pub ? ~g.stamp : g.stamp;
     __shared__ uint32_t slot[2];
-    __shared__ uint32_t crowded;
-    if (threadIdx.x == 0) crowded = 0;
+    __shared__ uint32_t crowded[2];
+    if (threadIdx.x < 2) crowded[threadIdx.x] = 0;
+    if (threadIdx.x == 0) long_runs = 0;
     Sched sc = make_sched(U, false, g.sched);
     uint32_t u, nxi;
     sched_start(sc, u, nxi, slot);
@@ -2316,7 +2388,7 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
         Chunk<false> ch;
         load_chunk<AOS, false, B>(g, un, ch);
         uint32_t pos[kBuildItems];
-        const Table t = insert_chunk<false, AOS, B, true>(g, un, ch, tab, pos, &crowded);
+        const Table t = insert_chunk<false, AOS, B, true>(g, un, ch, tab, pos, crowded);
         __builtin_amdgcn_s_waitcnt(0);  // nothing in flight enters the batch loop
         const bool more = nxi < U;
         const Unit nx = more ? decode_unit<AOS>(g, nxi) : Unit{};
@@ -2336,13 +2408,9 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
                 many += (uint64_t)ma + mb;
             }
         };
-        const bool by_sort = uniform(crowded) != 0;
-        if (by_sort) {
+        const bool by_sort = uniform(crowded[0]) != 0;
+        if (__builtin_expect(by_sort, 0)) {
             set_crowded(g, un);
-            // told to the host at once: it is read with the total, which is published later
-            if (pub && threadIdx.x == 0)
-                __hip_atomic_store(pub + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            drain();  // before this unit's count is
             const UnitCount c = count_crowded<AOS, SEMI, B>();
             cnt = c.cnt;
             many = c.many;
@@ -2363,9 +2431,10 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
         // of a partition has the partition's top bits (a unit without probe keys never reads
         // its table, so its marker does not matter).
         unit_totals<B>(cnt, many, multi, sm.k, u, counts, wave_off, wsum, rec_word, by_sort,
-                       AOS ? nullptr : g.unit_pub, [&] {
+                       AOS ? nullptr : g.unit_pub, pub, [&] {
             if (more) clear_table<false, AOS, B>(nx, xa[0], tab);
-            if (threadIdx.x == 0) crowded = 0;
+            if (threadIdx.x < 2) crowded[threadIdx.x] = 0;
+            if (threadIdx.x == 0) long_runs = 0;
         });  // ends with a barrier
         const uint32_t nn = sched_after(sc, need, nxi, slot);
         u = nxi;
@@ -2374,7 +2443,7 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
         un = nx;
     }
     if (done) {
-        // Thread 0 wrote every count of this workgroup.  Only the last to arrive acquires (an
+        // The first wave wrote every count of this workgroup.  Only the last to arrive acquires (an
         // acquire also drops the L2 lines that workgroups still running on this XCD are reading).
         __shared__ uint32_t last;
         if (threadIdx.x == 0) {
@@ -3322,7 +3391,7 @@ hipError_t hash_write(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
     else if (pl.semi) join_write_k<true, true, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
     else join_write_k<true, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
     if (crowded) {
-        // one unit per workgroup while there are few: a unit takes some 50 us
+        // one unit per workgroup while there are few: a unit takes some 120 us
         const unsigned cg = (unsigned)(pl.Umax < pl.gridWrite ? pl.Umax : pl.gridWrite);
         const size_t cl = sorted_lds((uint32_t)pl.cap);
         if (pl.single) write_crowded_k<false, kJoinBlock><<<cg, kJoinBlock, cl, st>>>(g, offsets, wave_off, total, out, cap);

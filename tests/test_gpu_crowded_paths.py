@@ -55,3 +55,52 @@ def test_semi_join_of_a_hot_build_key(hot, copies):
     got = canon_gpu(hash_join(dR, dS, prefilter=True))
     assert np.array_equal(got, ref)
     assert np.array_equal(canon_gpu(hash_join(dR, dS)), ref)
+
+
+@gpu
+@pytest.mark.parametrize("nS", [3000, 200_000, 4_000_000])
+@pytest.mark.parametrize("keys,copies", [(1, 70), (1, 300), (1, 700), (3, 550), (10, 250), (40, 60), (40, 150)])
+def test_around_the_line_between_walks_and_sorts(keys, copies, nS):
+    """Tables with keys of about as many copies as make a unit crowded, unpartitioned and in
+    partitions of one chunk, with one round of probes and many."""
+    need_gpu()
+    from paper_1904_11201_amd import _native
+    from paper_1904_11201_amd.join import hash_join
+    R, S = _hot_join(list(range(keys)), 9000 - keys * copies, nS, copies, domain=30_000)
+    ref = _expect(R, S)
+    dR, dS = dev_rel(R), dev_rel(S)
+    for bits in (0, 1):
+        _native.tune_set("hash.bits", bits, local=True)
+        try:
+            log(f"crowd line, {keys} keys of {copies}, {nS} probes, bits {bits}")
+            assert np.array_equal(canon_gpu(hash_join(dR, dS)), ref)
+        finally:
+            _native.tune_set("hash.bits", None, local=True)
+
+
+@gpu
+def test_moderately_hot_keys_are_walked():
+    """9000 x 10,000 with one key of 160 copies that no row asks for: at most 4 times the join without
+    it (sorting its tables took 8 times, their walks 2)."""
+    need_gpu()
+    import time
+
+    import torch
+
+    from paper_1904_11201_amd.join import hash_join
+    took = {}
+    for copies in (1, 160):
+        R, S = _hot_join([7], 9000 - copies, 10_000, copies, domain=1_000_000)
+        S.key[S.key == 7] = 8
+        R, S = dev_rel(R), dev_rel(S)
+        log(f"one key of {copies} copies")
+        runs = []
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            hash_join(R, S)
+            torch.cuda.synchronize()
+            runs.append(time.perf_counter() - t0)
+        took[copies] = min(runs)
+    log(f"us: {[(k, round(v * 1e6)) for k, v in took.items()]}")
+    assert took[160] < 4 * took[1]
