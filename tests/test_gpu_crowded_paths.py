@@ -104,3 +104,87 @@ def test_moderately_hot_keys_are_walked():
         took[copies] = min(runs)
     log(f"us: {[(k, round(v * 1e6)) for k, v in took.items()]}")
     assert took[160] < 4 * took[1]
+
+
+def _noalloc(R, S, cap):
+    import ctypes
+
+    import torch
+
+    from paper_1904_11201_amd import _native
+    pairs = torch.empty((cap, 2), dtype=torch.int32, device="cuda")
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    rr, sr = R.c(), S.c()
+    rc = _native.lib.join_hash_noalloc(ctypes.byref(rr), ctypes.byref(sr), ctypes.c_void_p(pairs.data_ptr()), cap,
+                                       ctypes.c_void_p(count.data_ptr()), None)
+    assert rc == _native.JOIN_OK, _native.last_error()
+    assert int(count.item()) == cap
+    return pairs
+
+
+def _written_by_another_thread(R, S, n):
+    """The count pass on this thread, the write pass on one that knows nothing of it."""
+    import threading
+
+    import torch
+
+    from paper_1904_11201_amd import join as J
+    ws = J.workspace(J.JOIN_KIND_HASH, R.n, S.n)
+    assert J.join_count(J.JOIN_KIND_HASH, R, S, None, ws) == n
+    pairs, errors = torch.empty((n, 2), dtype=torch.int32, device="cuda"), []
+
+    def write():
+        try:
+            J.join_materialize(J.JOIN_KIND_HASH, R, S, None, ws, pairs)
+            torch.cuda.synchronize()
+        except Exception as e:  # shown by the assertion below
+            errors.append(e)
+
+    t = threading.Thread(target=write)
+    t.start()
+    t.join()
+    assert not errors, errors
+    return pairs
+
+
+@gpu
+@pytest.mark.parametrize("nR,copies", [(3000, 1000), (7000, 1000), (7000, 100), (200_000, 1000)])
+def test_every_entry_of_a_hot_build_key(nR, copies):
+    """Unpartitioned and partitioned, for tables crowded by the build and units sorted for a probe's
+    long run."""
+    need_gpu()
+    from paper_1904_11201_amd import join as J
+    R, S = _hot_join(HOT, nR, 50_000, copies, domain=60_000)
+    ref = _expect(R, S)
+    dR, dS = dev_rel(R), dev_rel(S)
+    for name, run in (("resident build", lambda: J.ResidentBuild(dR).probe(dS)),
+                      ("noalloc", lambda: _noalloc(dR, dS, len(ref))),
+                      ("written by another thread", lambda: _written_by_another_thread(dR, dS, len(ref))),
+                      ("pre-filtered", lambda: J.hash_join(dR, dS, prefilter=True))):
+        log(f"hot build keys, {nR} rows and {copies} copies: {name}")
+        assert np.array_equal(canon_gpu(run()), ref), name
+
+
+@gpu
+@pytest.mark.parametrize("copies", [100, 1000])
+def test_batch_with_hot_build_keys(copies):
+    """Fan-outs of 0 and 1 bits (raw and unmarked tables) and more, hot jobs among others; written
+    twice from one count."""
+    need_gpu()
+    import torch
+
+    from paper_1904_11201_amd import join as J
+    jobs, refs = [], []
+    for i, (bits, hot) in enumerate([(0, HOT[:2]), (1, HOT), (-1, []), (2, HOT), (5, HOT), (-1, HOT), (0, [])]):
+        R, S = _hot_join(hot, 2000 if bits == 0 else 9000, 6000 + i, copies, seed=i, domain=20_000)
+        refs.append(_expect(R, S))
+        jobs.append(J.Job(dev_rel(R), dev_rel(S), bits))
+    log(f"batch with hot build keys, {copies} copies")
+    batch = J.Batch(jobs)
+    offs = batch.count().cpu().tolist()
+    pairs = torch.empty((offs[-1], 2), dtype=torch.int32, device="cuda")
+    for _ in range(2):
+        pairs.fill_(-1)
+        batch.materialize(pairs)
+        for j, ref in enumerate(refs):
+            assert np.array_equal(canon_gpu(pairs[offs[j]:offs[j + 1]]), ref), j
