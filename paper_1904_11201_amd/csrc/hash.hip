@@ -2885,14 +2885,18 @@ static int default_slice(int64_t nS, int num_cus)
 }
 
 // Whether a join of up to single_max build rows is joined without partitioning.  The
-// unpartitioned path probes every S row once per R chunk, so it repeats (chunks - 1) * nS
-// probes; partitioning reads and writes both sides once more in three more launches (about 25 us)
-// and probes once.  Measured (us a join, unpartitioned / partitioned): 18K x 4M 91 / 131,
-// x 16M 214 / 223; 36K x 1M 69 / 84, x 4M 142 / 122; 73K x 256K 60 / 70, x 1M 89 / 81;
-// 147K x 256K 69 / 70, x 1M 139 / 81, x 16M 1292 / 195.  The line lies at about 6M repeats.
+// unpartitioned path probes every S row once per R chunk; partitioning reads and writes both sides
+// once more in three more launches, and probes once.  Both grow with |S|: a second probe of every row
+// costs less than partitioning at any size, a third costs as much at about 1M rows.  Measured (us
+// a join, unpartitioned / partitioned): two chunks, 10K x 1M 46 / 70, x 8M 125 / 160, x 64M 664 / 726,
+// 18K x 8M 124 / 156, x 64M 635 / 746; three, 27K x 1M 74 / 66, x 4M 129 / 97, x 16M 364 / 212; four,
+// 36K x 1M 59 / 63, x 2M 76 / 78, x 4M 125 / 95; eight, 73K x 1M 76 / 62; sixteen, 147K x 1M 124 / 64,
+// x 16M 1185 / 183.  So: two chunks never, from three on where (chunks - 1) * nS exceeds 6M repeats (a few
+// us to either side of the line for three and eight chunks).  The semi-join's write pass leaves out
+// most rows, and partitioned it wins from two chunks on: 10K x 4M, 1% matching 74 / 86, x 16M 189 / 148.
 constexpr int64_t kSingleRepeats = (int64_t)6 << 20;
-// Fewer partitions than this make the histogram's and the scatter's LDS atomics collide
-// (18K x 16M: 270 us with 4 partitions, 223 with 16).
+// Fewer partitions than this leave too few units, and LDS atomics that collide (100K x 16M: 306 us
+// with 8 partitions, 186 with 16, 184 with 32, 194 with 64; 36K x 16M: 208, 185, 203, 254).
 constexpr int kMinBits = 5;
 
 HashPlan hash_plan(int64_t nR, int64_t nS, int num_cus, int prebuilt_bits, bool semi, bool keep_single)
@@ -2911,8 +2915,9 @@ HashPlan hash_plan(int64_t nR, int64_t nS, int num_cus, int prebuilt_bits, bool 
     const int forced_bits = pl.prebuilt ? prebuilt_bits : (int)tune_get(TUNE_HASH_BITS, -1);
     // a join under single_max chunks set by the caller, or asked to stay unpartitioned
     // (keep_single), is not moved by the rule above
-    const bool repeats_ok = single_knob >= 0 || keep_single ||
-                            (ceil_div(nR, cap) - 1) * nS <= kSingleRepeats;
+    const int64_t chunks = ceil_div(nR, cap);
+    const bool repeats_ok = single_knob >= 0 || keep_single || (chunks <= 2 && !semi) ||
+                            (chunks - 1) * nS <= kSingleRepeats;
     pl.single = !pl.prebuilt &&
                 (forced_bits == 0 || (forced_bits < 0 && nR <= single_max && repeats_ok));
     if (semi && !pl.single) {
