@@ -22,7 +22,7 @@
  *     current HIP device.  join_rel_t / join_pred_t structs themselves and `count` are HOST
  *     pointers (except join_hash_noalloc's `count`, a device pointer).  The caller owns every
  *     buffer; the library never allocates device memory and keeps no pointer after a call
- *     returns.  The one piece of device memory the library holds is the static 64 MiB array that
+ *     returns.  The one piece of device memory the library holds is the static array (64 MiB and 128 KiB) that
  *     join_hash_noalloc works in, which exists once per GPU from the loading of the library's
  *     GPU code until the process ends.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).  All device work is
@@ -146,8 +146,8 @@ int join_theta(const join_rel_t* R, const join_rel_t* S, const join_pred_t* pred
 /* ---- the hash join without a workspace argument -------------------------------------------
  * For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid allocation): join_hash with its workspace taken from a static
- * device array of 64 MiB that the library holds on every GPU it runs on until the process ends,
- * instead of a caller buffer.  The call allocates nothing (no hipMalloc, hipFree or allocating
+ * device array of 64 MiB and 128 KiB that the library holds on every GPU it runs on until the
+ * process ends, instead of a caller buffer.  The call allocates nothing (no hipMalloc, hipFree or allocating
  * library routine) and does not synchronise: the exact count is written to `count`, a DEVICE
  * pointer to one uint64, and the pairs are written to `pairs` (device, `capacity` pairs) only if
  * the count fits (device-side snprintf semantics: count always set, pairs written only when
@@ -155,8 +155,11 @@ int join_theta(const join_rel_t* R, const join_rel_t* S, const join_pred_t* pred
  * Every call on one GPU uses that GPU's array, which keeps the last call's contents; each call
  * clears what it accumulates into before use.  Calls that overlap in time on one GPU (other
  * streams, other host threads) race on the array and must be serialised by the caller.
- * Errors: JOIN_E_INVAL, JOIN_E_UNSUPPORTED, JOIN_E_WORKSPACE (the join's workspace, the size
- * join_workspace_bytes(JOIN_KIND_HASH, ...) reports, exceeds 64 MiB), JOIN_E_HIP. */
+ * A join whose workspace, the size join_workspace_bytes(JOIN_KIND_HASH, ...) reports, exceeds the
+ * array is joined unpartitioned if its build is small enough for that (see
+ * "hash.single_max_chunks"), whatever the number of probe rows.
+ * Errors: JOIN_E_INVAL, JOIN_E_UNSUPPORTED, JOIN_E_WORKSPACE (the join fits the array neither way),
+ * JOIN_E_HIP. */
 int join_hash_noalloc(const join_rel_t* R, const join_rel_t* S, int32_t* pairs, uint64_t capacity,
                       uint64_t* count, void* stream);
 
