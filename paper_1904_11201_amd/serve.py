@@ -57,6 +57,20 @@ class BudgetError(RuntimeError):
     pass
 
 
+SINGLE_MAX = 16  # tables of a build that can be joined unpartitioned (the library's own limit)
+
+
+class _Unpartitioned:
+    """Joins of this thread take the unpartitioned path where they can: a workspace of under a
+    megabyte instead of both sides' tuples, in more time (each table probed by every row)."""
+
+    def __enter__(self):
+        J._native.tune_set("hash.single_max_chunks", SINGLE_MAX, local=True)
+
+    def __exit__(self, *exc):
+        J._native.tune_set("hash.single_max_chunks", None, local=True)
+
+
 class _Retry(Exception):
     """Raised inside a slot whose request must give its workspace back and start over."""
 
@@ -78,9 +92,9 @@ class Engine:
         self.active = 0
         self._waiting: set = set()
         self._cv = threading.Condition()
-        # Builds large enough to be partitioned are kept partitioned; small ones are joined
-        # directly (the library reads a small build without partitioning it at all).
-        single_max = J._native.tune_get("hash.single_max_chunks", 16) * J._native.tune_get("hash.cap", 9216)
+        # Builds too large for the unpartitioned path are kept partitioned; small ones are joined
+        # directly (the library partitions those only for many probe rows).
+        single_max = J._native.tune_get("hash.single_max_chunks", SINGLE_MAX) * J._native.tune_get("hash.cap", 9216)
         self.builds = builds
         self.resident = [J.ResidentBuild(R) if resident and R.n > single_max else None for R in builds]
         torch.cuda.synchronize()
@@ -134,6 +148,18 @@ class Engine:
 
     # ---- one request on one stream ----------------------------------------------------------
     def _run(self, req: Request, stream) -> tuple[torch.Tensor, int]:
+        try:
+            return self._run_once(req, stream)
+        except BudgetError:
+            # a small build against many rows is partitioned for speed; where that does not fit the
+            # budget, it is joined the other way
+            rb = self.resident[req.build_id] if req.R is None and req.kind == "hash" else None
+            if req.kind != "hash" or rb is not None or J._native.tune_get("hash.single_max_chunks", -1) >= 0:
+                raise
+            with _Unpartitioned():
+                return self._run_once(req, stream)
+
+    def _run_once(self, req: Request, stream) -> tuple[torch.Tensor, int]:
         dev = self.device
         key = (req.arrival_s, req.rid)
         rb = None
