@@ -1217,6 +1217,12 @@ __host__ __device__ constexpr size_t sorted_lds(uint32_t cap)
     return N * 8;
 }
 
+// Dynamic LDS of a batch's write pass: a table, or in its place the sorted entries of a crowded unit.
+__host__ __device__ constexpr size_t batch_write_lds(uint32_t cap)
+{
+    return table_lds(cap, true) > sorted_lds(cap) ? table_lds(cap, true) : sorted_lds(cap);
+}
+
 // One R chunk held in registers between its load and its insertion.
 template <bool RIDS>
 struct Chunk {
@@ -2256,10 +2262,10 @@ constexpr int kWaveRec = 2 * kJoinWaves;  // uint64 entries per unit in the wave
 constexpr int kWaveHalf = kJoinWaves;     // its second half (a 512-thread workgroup uses 8 + 8)
 // the write pass's queues of probes with many matches, beside its dynamic table
 constexpr size_t kWriteStaticLds = (size_t)kJoinWaves * kManyQ * 16;
-constexpr size_t kBatchStaticLds = (size_t)(kBatchBlock / kWave) * kManyQ * 16;
+constexpr size_t kBatchStaticLds = (size_t)(kBatchBlock / kWave) * kManyQ * 16 + (kBatchBlock + 1) * 4 + 512;
 static_assert(table_lds(kMaxCap, true) + kWriteStaticLds <= 160 * 1024, "write pass LDS");
 static_assert(sorted_lds(kMaxCap) + kJoinBlock * 4 + 256 <= 160 * 1024, "crowded units' LDS");
-static_assert(2 * (table_lds(kBatchCap, true) + kBatchStaticLds + 256) <= 160 * 1024,
+static_assert(2 * (batch_write_lds(kBatchCap) + kBatchStaticLds + 256) <= 160 * 1024,
               "two batch write workgroups per CU");
 
 // End of a unit in the count pass: lane totals -> wave totals -> the unit's total in counts[u],
@@ -2273,7 +2279,8 @@ template <int B, typename Between>
 __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_many, bool multi,
                                             uint32_t semi_rows, uint32_t u, uint64_t* __restrict__ counts,
                                             uint64_t* __restrict__ wave_off, uint64_t* sh, uint32_t* rec_word,
-                                            bool crowded, uint64_t* unit_pub, uint64_t* pub, Between between)
+                                            bool crowded, uint64_t* unit_pub, uint64_t* pub, uint32_t* sched,
+                                            Between between)
 {
     const uint64_t wt = wave_sum64(lane_total);
     const uint64_t wmany = wave_sum64(lane_many);
@@ -2302,7 +2309,10 @@ __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_m
             store_shared(&counts[u], inc);
             if (unit_pub) __hip_atomic_store(&unit_pub[u], inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             const uint32_t flags = (any ? 1u << kRecOrder : 0u) | (crowded ? 1u << kRecCrowded : 0u);
-            if (flags && rec_word) atomicOr(rec_word, flags);
+            if (flags && rec_word) {
+                atomicOr(rec_word, flags);
+                if (B == kBatchBlock && crowded) sched[kSchedCrowded] = 1;
+            }
         }
     }
     between();  // every wave has finished the unit's probes
@@ -2431,7 +2441,7 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
         // of a partition has the partition's top bits (a unit without probe keys never reads
         // its table, so its marker does not matter).
         unit_totals<B>(cnt, many, multi, sm.k, u, counts, wave_off, wsum, rec_word, by_sort,
-                       AOS ? nullptr : g.unit_pub, pub, [&] {
+                       AOS ? nullptr : g.unit_pub, pub, g.sched, [&] {
             if (more) clear_table<false, AOS, B>(nx, xa[0], tab);
             if (threadIdx.x < 2) crowded[threadIdx.x] = 0;
             if (threadIdx.x == 0) long_runs = 0;
@@ -2578,21 +2588,16 @@ __device__ __forceinline__ uint64_t write_crowded(uint64_t cursor, uint64_t cman
     return cursor + cmany - at0;
 }
 
-// The write pass of the crowded units, which join_write_k leaves out (inside it this code's
-// registers cost every other unit 5 to 10%).  Launched when the count pass said there are any, or
-// when its word about it is not at hand.  Workgroup b looks through units b, b + grid, ..., B at a
+// The write pass of the crowded units, which join_write_k leaves out of its loop (inside it this code's
+// registers cost every other unit 5 to 10%).  Workgroup b looks through units b, b + grid, ..., B at a
 // time, and writes those that are flagged (crowded units lie next to each other, so neighbouring
 // units go to different workgroups).
 template <bool AOS, int B>
-__global__ JL_WRITE_ATTR(B) void write_crowded_k(JoinGeom g, const uint64_t* __restrict__ offsets,
-                                                 const uint64_t* __restrict__ wave_off,
-                                                 const uint64_t* __restrict__ total,
-                                                 int2* __restrict__ out, uint64_t cap)
+__device__ __forceinline__ void write_crowded_units(const JoinGeom& g, uint32_t U, const uint64_t* offsets,
+                                                    const uint64_t* wave_off, const RawCounts& raw, int2* out,
+                                                    uint64_t cap)
 {
     __shared__ uint32_t found[B], nfound;
-    const uint32_t U = unit_total(g);
-    const RawCounts raw = raw_counts<AOS>(g, offsets, U);
-    if ((raw.on ? raw.total : *total) > cap || (g.stamp_at && !raw.on && *g.stamp_at != g.stamp)) return;
     const int wv = uniform((int32_t)(threadIdx.x / kWave));
     const cptr<uint64_t> offs = as_const(offsets);
     const cptr<uint64_t> wo = as_const(wave_off);
@@ -2620,6 +2625,45 @@ __global__ JL_WRITE_ATTR(B) void write_crowded_k(JoinGeom g, const uint64_t* __r
             __syncthreads();
         }
     }
+}
+
+// One join: a kernel of their own, launched when the count pass said there are any, or when its word
+// about it is not at hand.
+template <bool AOS>
+__global__ JL_WRITE_ATTR(kJoinBlock) void write_crowded_k(JoinGeom g, const uint64_t* __restrict__ offsets,
+                                                          const uint64_t* __restrict__ wave_off,
+                                                          const uint64_t* __restrict__ total,
+                                                          int2* __restrict__ out, uint64_t cap)
+{
+    const uint32_t U = unit_total(g);
+    const RawCounts raw = raw_counts<AOS>(g, offsets, U);
+    if ((raw.on ? raw.total : *total) > cap || (g.stamp_at && !raw.on && *g.stamp_at != g.stamp)) return;
+    write_crowded_units<AOS, kJoinBlock>(g, U, offsets, wave_off, raw, out, cap);
+}
+
+// A batch, whose count pass tells the host nothing: by the workgroups of join_write_k when their other
+// units are done, if there are any (g.sched); a launch that mostly finds none cost 4 us a batch.
+// What the function needs is in LDS, as it is not inlined.
+struct CrowdedPass {
+    const int2 *rt, *st;
+    const uint4* urec;
+    uint64_t* dbg;
+    const uint64_t *offsets, *wave_off;
+    int2* out;
+    uint64_t cap;
+    uint32_t U;
+};
+__shared__ CrowdedPass crowded_pass;
+
+__device__ __attribute__((noinline)) void write_crowded_rest()
+{
+    const CrowdedPass& p = crowded_pass;
+    JoinGeom g{};
+    g.rt = p.rt;
+    g.st = p.st;
+    g.urec = p.urec;
+    g.dbg = p.dbg;
+    write_crowded_units<true, kBatchBlock>(g, uniform(p.U), p.offsets, p.wave_off, RawCounts{}, p.out, p.cap);
 }
 
 // Write pass.  Units are walked in a Sched sequence (for one join a contiguous run per
@@ -2812,6 +2856,23 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
         ++sc.pos;
         un = nxt;
     }
+    if constexpr (B == kBatchBlock)
+        if (g.sched && uniform(g.sched[kSchedCrowded])) {
+            if (threadIdx.x == 0) {
+                CrowdedPass& p = crowded_pass;  // field by field: as a whole it would be made in scratch memory
+                p.rt = g.rt;
+                p.st = g.st;
+                p.urec = g.urec;
+                p.dbg = g.dbg;
+                p.offsets = offsets;
+                p.wave_off = wave_off;
+                p.out = out;
+                p.cap = cap;
+                p.U = U;
+            }
+            __syncthreads();
+            write_crowded_rest();
+        }
     // The last workgroup to finish resets the ticket counter for the next write from this
     // workspace (every workgroup took its last ticket before it arrives here).
     if (sc.ticket && threadIdx.x == 0 && atomicAdd(g.sched + 2, 1u) == gridDim.x - 1) {
@@ -3041,8 +3102,8 @@ static hipError_t set_attrs()
         if (e != hipSuccess) return e;
     }
     for (const void* f : {(const void*)join_write_k<true, false, kJoinBlock>, (const void*)join_write_k<false, false, kJoinBlock>,
-                          (const void*)join_write_k<true, true, kJoinBlock>, (const void*)write_crowded_k<true, kJoinBlock>,
-                          (const void*)write_crowded_k<false, kJoinBlock>, (const void*)write_crowded_k<true, kBatchBlock>}) {
+                          (const void*)join_write_k<true, true, kJoinBlock>, (const void*)write_crowded_k<true>,
+                          (const void*)write_crowded_k<false>}) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, write_max);
         if (e != hipSuccess) return e;
     }
@@ -3399,8 +3460,8 @@ hipError_t hash_write(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
         // one unit per workgroup while there are few: a unit takes some 120 us
         const unsigned cg = (unsigned)(pl.Umax < pl.gridWrite ? pl.Umax : pl.gridWrite);
         const size_t cl = sorted_lds((uint32_t)pl.cap);
-        if (pl.single) write_crowded_k<false, kJoinBlock><<<cg, kJoinBlock, cl, st>>>(g, offsets, wave_off, total, out, cap);
-        else write_crowded_k<true, kJoinBlock><<<cg, kJoinBlock, cl, st>>>(g, offsets, wave_off, total, out, cap);
+        if (pl.single) write_crowded_k<false><<<cg, kJoinBlock, cl, st>>>(g, offsets, wave_off, total, out, cap);
+        else write_crowded_k<true><<<cg, kJoinBlock, cl, st>>>(g, offsets, wave_off, total, out, cap);
     }
     return hipGetLastError();
 }
@@ -3539,7 +3600,7 @@ int hash_batch_plan(int njobs, const join_job_t* jobs, int num_cus, BatchPlan* o
     bp.off_itemsS = take(off, (size_t)bp.nItemsS * sizeof(SideItem));
     // totR, totS, then the group shares of R and S: cleared together
     // sizes, group shares, then the count and write passes' unit tickets (Sched), cleared together
-    bp.off_tot = take(off, ((size_t)(2 + 2 * kGroups) * bp.nParts + 4) * 4);
+    bp.off_tot = take(off, ((size_t)(2 + 2 * kGroups) * bp.nParts + kSchedWords) * 4);
     bp.off_baseR = take(off, (size_t)(bp.nParts + 1) * 4);
     bp.off_baseS = take(off, (size_t)(bp.nParts + 1) * 4);
     bp.off_tupR = take(off, (size_t)bp.sumR * 8);
@@ -3561,7 +3622,7 @@ int hash_batch_plan(int njobs, const join_job_t* jobs, int num_cus, BatchPlan* o
     // 512-thread workgroups: four count workgroups (64 VGPRs) or two write workgroups (128
     // VGPRs, and their static queues) fit a CU when their tables do
     auto grid_for = [&](bool rids) {
-        const size_t lds = table_lds((uint32_t)bp.cap, rids) + (rids ? kBatchStaticLds : 0) + 256;
+        const size_t lds = (rids ? batch_write_lds((uint32_t)bp.cap) + kBatchStaticLds : table_lds((uint32_t)bp.cap, false)) + 256;
         int per_cu = (int)((160 * 1024) / lds);
         if (per_cu < 1) per_cu = 1;
         if (per_cu > (rids ? 2 : 4)) per_cu = rids ? 2 : 4;
@@ -3683,7 +3744,7 @@ hipError_t hash_batch_count(const BatchPlan& bp, char* ws, uint64_t* offsets, hi
     const SideItem none{};
     if (bp.nParts > 0) {
         prof::Scope pz(st, "hash.plan");
-        const int64_t nz = (2 + 2 * kGroups) * bp.nParts + 4;
+        const int64_t nz = (2 + 2 * kGroups) * bp.nParts + kSchedWords;
         zero_u32_k<<<(unsigned)ceil_div(nz, 256), 256, 0, st>>>(totR, nz);
     }
     e = hipGetLastError();
@@ -3745,9 +3806,7 @@ hipError_t hash_batch_write(const BatchPlan& bp, char* ws, int32_t* pairs, uint6
     const uint64_t* wave_off = reinterpret_cast<const uint64_t*>(ws + bp.off_wave);
     const uint64_t* total = reinterpret_cast<const uint64_t*>(ws);
     int2* out = reinterpret_cast<int2*>(pairs);
-    join_write_k<true, false, kBatchBlock><<<(unsigned)bp.gridWrite, kBatchBlock, table_lds((uint32_t)bp.cap, true), st>>>(
-        g, offsets, wave_off, total, out, cap);
-    write_crowded_k<true, kBatchBlock><<<(unsigned)bp.gridWrite, kBatchBlock, sorted_lds((uint32_t)bp.cap), st>>>(
+    join_write_k<true, false, kBatchBlock><<<(unsigned)bp.gridWrite, kBatchBlock, batch_write_lds((uint32_t)bp.cap), st>>>(
         g, offsets, wave_off, total, out, cap);
     return hipGetLastError();
 }

@@ -22,6 +22,11 @@ struct SideItem {
                          // counts starts at element cnt0 + t * 2^bits of the side's count array
 };
 
+// Words of JoinGeom::sched.  The flag lies on a line of its own: all workgroups read it when they run out
+// of units, behind each other's tickets if they shared a line (64 joins of 64K: write 69 us, 77).
+constexpr int kSchedCrowded = 64;
+constexpr int kSchedWords = 96;
+
 // Everything the count and write kernels need to walk the work units.
 struct JoinGeom {
     const int32_t* rk;  // single: the input build keys
@@ -50,7 +55,8 @@ struct JoinGeom {
     uint64_t* dbg;       // checking build: pairs written per unit (NULL: not counted)
     uint32_t* semi;      // the probe rows with matches, per unit and wave (NULL: not recorded)
     int stream;          // the probe tuples are read non-temporally (kStreamBytes)
-    uint32_t* sched;     // [3]: count ticket, write ticket, write arrivals (NULL: static shares)
+    uint32_t* sched;     // [kSchedWords] of a batch: count ticket, write ticket, write arrivals, and at
+                         // kSchedCrowded whether some unit is crowded (NULL: static shares)
 };
 
 struct HashPlan {
