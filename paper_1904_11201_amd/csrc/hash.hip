@@ -1911,11 +1911,19 @@ constexpr int64_t kStreamBytes = 320ll << 20;
 int stream_rows(int64_t rows) { return rows * (int64_t)sizeof(int2) > kStreamBytes; }
 
 // load(std::true_type) when the join streams its tuples, else load(std::false_type).  The empty
-// statements keep the compiler from merging the two sides' loads into ordinary ones.
-template <bool AOS, typename Load>
+// statements keep the compiler from merging the two sides' loads into ordinary ones.  A batch's kernels
+// are compiled for each (16 joins of 1M: count 244 us with the branch, 238 without); one join's
+// choose here, as the branch costs them nothing.
+enum Stream : int { kPlain, kStreamed, kEither };
+
+template <bool AOS, int ST, typename Load>
 __device__ __forceinline__ void by_stream(const JoinGeom& g, Load load)
 {
-    if (AOS && g.stream) {  // uniform
+    if constexpr (!AOS || ST == kPlain) {
+        load(std::false_type{});
+    } else if constexpr (ST == kStreamed) {
+        load(std::true_type{});
+    } else if (g.stream) {  // uniform
         asm volatile("");
         load(std::true_type{});
         asm volatile("");
@@ -1924,7 +1932,7 @@ __device__ __forceinline__ void by_stream(const JoinGeom& g, Load load)
     }
 }
 
-template <bool AOS, int B>
+template <bool AOS, int B, int ST>
 __device__ __forceinline__ void load_tuples(const JoinGeom& g, const Unit& un, uint32_t e0,
                                             uint32_t (&x)[kWriteLoadOf<B>], int32_t (&r)[kWriteLoadOf<B>])
 {
@@ -1955,17 +1963,17 @@ __device__ __forceinline__ void load_tuples(const JoinGeom& g, const Unit& un, u
             }
         }
     };
-    by_stream<AOS>(g, load);
+    by_stream<AOS, ST>(g, load);
 }
 
 // A batch of S keys of a unit with un.sN > 0.  Out-of-range lanes read the unit's first tuple and
 // drop it (the probe masks them), so the loads carry no branch.
-template <bool AOS, int B>
+template <bool AOS, int B, int ST>
 __device__ __forceinline__ void load_keys_of(const JoinGeom& g, const Unit& un, uint32_t e0,
                                              uint32_t (&xs)[kCountBatch])
 {
     const bool full = e0 + (uint32_t)(kCountBatch * B) <= un.sN;  // uniform
-    by_stream<AOS>(g, [&](auto once) {
+    by_stream<AOS, ST>(g, [&](auto once) {
 #pragma unroll
         for (int i = 0; i < kCountBatch; ++i) {
             const uint32_t e = e0 + i * B + threadIdx.x;
@@ -1979,7 +1987,7 @@ __device__ __forceinline__ void load_keys_of(const JoinGeom& g, const Unit& un, 
 }
 
 // The same for any unit: a unit without probes loads nothing.
-template <bool AOS, int B>
+template <bool AOS, int B, int ST>
 __device__ __forceinline__ void load_keys(const JoinGeom& g, const Unit& un, uint32_t e0,
                                           uint32_t (&xs)[kCountBatch])
 {
@@ -1988,7 +1996,7 @@ __device__ __forceinline__ void load_keys(const JoinGeom& g, const Unit& un, uin
         for (int i = 0; i < kCountBatch; ++i) xs[i] = 0u;
         return;
     }
-    load_keys_of<AOS, B>(g, un, e0, xs);
+    load_keys_of<AOS, B, ST>(g, un, e0, xs);
 }
 
 // ------------------------------------------------------------------------ crowded units --
@@ -2364,7 +2372,7 @@ __device__ void scan_counts_block(uint64_t* counts, uint32_t U, int64_t Umax, ui
 // done: NULL, or a zeroed arrival set; then the last workgroup to arrive scans the counts
 // (Umax <= kFuseScanMax) and writes the sum to *total and, when pub is not NULL, to that pinned
 // host slot.
-template <bool AOS, bool SEMI, int B>
+template <bool AOS, bool SEMI, int B, int ST>
 __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__ counts,
                                            uint64_t* __restrict__ wave_off,
                                            uint32_t* __restrict__ done, uint64_t* __restrict__ total,
@@ -2386,7 +2394,7 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
     Unit un{};
     if (u < U) {
         un = decode_unit<AOS>(g, u);
-        load_keys<AOS, B>(g, un, 0, xa);
+        load_keys<AOS, B, ST>(g, un, 0, xa);
         // each unit's table is cleared in the previous unit's closing step; the first one here
         clear_table<false, AOS, B>(un, marker_hash<AOS>(g, un), tab);
         __syncthreads();
@@ -2410,10 +2418,10 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
             for (uint32_t e0 = 0; e0 < un.sN; e0 += 2 * kB) {
                 const uint32_t e1 = e0 + kB, e2 = e1 + kB;
                 uint32_t ma = 0, mb = 0;
-                load_keys_of<AOS, B>(g, un, e1 < un.sN ? e1 : e0, xb);
+                load_keys_of<AOS, B, ST>(g, un, e1 < un.sN ? e1 : e0, xb);
                 cnt += count_batch<AOS, M, SEMI, B>(t, un, e0, xa, multi, ma, sm);
                 const bool here = e2 < un.sN, there = !here && more && nx.sN > 0;
-                load_keys_of<AOS, B>(g, there ? nx : un, here ? e2 : (there ? 0u : e0), xa);
+                load_keys_of<AOS, B, ST>(g, there ? nx : un, here ? e2 : (there ? 0u : e0), xa);
                 cnt += count_batch<AOS, M, SEMI, B>(t, un, e1, xb, multi, mb, sm);  // every lane masked past the unit
                 many += (uint64_t)ma + mb;
             }
@@ -2426,11 +2434,11 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
             many = c.many;
             multi = c.multi;
             sm.k = c.semi;
-            if (more) load_keys<AOS, B>(g, nx, 0, xa);
+            if (more) load_keys<AOS, B, ST>(g, nx, 0, xa);
         } else {
             if (AOS && t.marked) batches(std::true_type{});
             else batches(std::false_type{});
-            if (un.sN == 0 && more) load_keys<AOS, B>(g, nx, 0, xa);
+            if (un.sN == 0 && more) load_keys<AOS, B, ST>(g, nx, 0, xa);
         }
         sched_put(sc, need, tk, slot);
         // a partitioned join's record is read only by this workgroup in this pass (it decoded it
@@ -2671,7 +2679,7 @@ __device__ __attribute__((noinline)) void write_crowded_rest()
 // tuples from the start the count pass recorded for it, in (batch, tuple, lane) order, with one
 // wave-wide scan per round and no shared cursor: the output depends on the input and the plan
 // only, not on which workgroup takes a unit.
-template <bool AOS, bool SEMI, int B>
+template <bool AOS, bool SEMI, int B, int ST>
 __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __restrict__ offsets,
                                            const uint64_t* __restrict__ wave_off,
                                            const uint64_t* __restrict__ total,
@@ -2711,7 +2719,7 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
     if (u < U) {
         un = decode_written<AOS>(g, wave_off, u);
         load_chunk<AOS, true, B>(g, un, ch);
-        if constexpr (!SEMI) load_tuples<AOS, B>(g, un, 0, nx, nr);
+        if constexpr (!SEMI) load_tuples<AOS, B, ST>(g, un, 0, nx, nr);
     }
     Unit tu{};  // the unit whose chunk is in the table (rN == 0: none yet)
     const cptr<uint64_t> offs = as_const(offsets);
@@ -2816,7 +2824,7 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
                     round(cx, cr, [&](int j) { return k0 + j * kWave + lane_id() < semi_rows; });
                 }
             } else {
-                if (SEMI) load_tuples<AOS, B>(g, un, 0, nx, nr);  // not loaded ahead in this mode
+                if (SEMI) load_tuples<AOS, B, ST>(g, un, 0, nx, nr);  // not loaded ahead in this mode
                 for (uint32_t e0 = 0; e0 < un.sN; e0 += B * kWriteLoad) {
                     if constexpr (B == kJoinBlock) take_turn(e0 / (B * kWriteLoad));
                     uint32_t cx[kWriteLoad];
@@ -2827,9 +2835,9 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
                         cr[i] = nr[i];
                     }
                     if (e0 + B * kWriteLoad < un.sN)
-                        load_tuples<AOS, B>(g, un, e0 + B * kWriteLoad, nx, nr);
+                        load_tuples<AOS, B, ST>(g, un, e0 + B * kWriteLoad, nx, nr);
                     else if (more)
-                        load_tuples<AOS, B>(g, nxt, 0, nx, nr);
+                        load_tuples<AOS, B, ST>(g, nxt, 0, nx, nr);
                     round(cx, cr, [&](int j) { return e0 + j * B + threadIdx.x < un.sN; });
                 }
             }
@@ -2847,7 +2855,7 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
             atomicAdd(reinterpret_cast<unsigned long long*>(&g.dbg[u]), (unsigned long long)wrote);
 #endif
         if constexpr (!SEMI)
-            if (un.sN == 0 && more) load_tuples<AOS, B>(g, nxt, 0, nx, nr);
+            if (un.sN == 0 && more) load_tuples<AOS, B, ST>(g, nxt, 0, nx, nr);
         sched_put(sc, need, tk, slot);
         __syncthreads();
         const uint32_t nn = sched_after(sc, need, nxi, slot);
@@ -3094,22 +3102,23 @@ static hipError_t set_attrs()
         (const void*)scatter_k<true, false>, (const void*)scatter_k<false, false>,
         (const void*)scatter_k<true, false, kSmallIt>, (const void*)scatter_k<false, false, kSmallIt>,
         (const void*)scatter_k<true, true>, (const void*)scatter_k<false, true>, (const void*)hist_k,
-        (const void*)join_count_k<true, false, kJoinBlock>, (const void*)join_count_k<false, false, kJoinBlock>,
-        (const void*)join_count_k<true, true, kJoinBlock>, (const void*)join_count_k<true, false, kBatchBlock>,
+        (const void*)join_count_k<true, false, kJoinBlock, kEither>, (const void*)join_count_k<false, false, kJoinBlock, kEither>,
+        (const void*)join_count_k<true, true, kJoinBlock, kEither>, (const void*)join_count_k<true, false, kBatchBlock, kPlain>,
+        (const void*)join_count_k<true, false, kBatchBlock, kStreamed>,
     };
     for (const void* f : fns) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, big);
         if (e != hipSuccess) return e;
     }
-    for (const void* f : {(const void*)join_write_k<true, false, kJoinBlock>, (const void*)join_write_k<false, false, kJoinBlock>,
-                          (const void*)join_write_k<true, true, kJoinBlock>, (const void*)write_crowded_k<true>,
+    for (const void* f : {(const void*)join_write_k<true, false, kJoinBlock, kEither>, (const void*)join_write_k<false, false, kJoinBlock, kEither>,
+                          (const void*)join_write_k<true, true, kJoinBlock, kEither>, (const void*)write_crowded_k<true>,
                           (const void*)write_crowded_k<false>}) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, write_max);
         if (e != hipSuccess) return e;
     }
-    {
-        const hipError_t e = hipFuncSetAttribute((const void*)join_write_k<true, false, kBatchBlock>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, write_max_b);
+    for (const void* f : {(const void*)join_write_k<true, false, kBatchBlock, kPlain>,
+                          (const void*)join_write_k<true, false, kBatchBlock, kStreamed>}) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, write_max_b);
         if (e != hipSuccess) return e;
     }
     g_attr_done = true;
@@ -3428,9 +3437,9 @@ hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
                              ? reinterpret_cast<uint32_t*>(ws + pl.off_done) : nullptr;
         uint64_t* wave_off = reinterpret_cast<uint64_t*>(ws + pl.off_wave);
         prof::Scope pc(st, "hash.count");
-        if (pl.single) join_count_k<false, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, nullptr, total, pub);
-        else if (pl.semi) join_count_k<true, true, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, done, total, pub);
-        else join_count_k<true, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, done, total, pub);
+        if (pl.single) join_count_k<false, false, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, nullptr, total, pub);
+        else if (pl.semi) join_count_k<true, true, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, done, total, pub);
+        else join_count_k<true, false, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, counts, wave_off, done, total, pub);
         e = hipGetLastError();
         if (e != hipSuccess || done || unit_pub) return e;
     }
@@ -3453,9 +3462,9 @@ hipError_t hash_write(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
     const size_t lds = table_lds((uint32_t)pl.cap, true);
     int2* out = reinterpret_cast<int2*>(pairs);
     prof::Scope pw(st, "hash.write");
-    if (pl.single) join_write_k<false, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
-    else if (pl.semi) join_write_k<true, true, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
-    else join_write_k<true, false, kJoinBlock><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
+    if (pl.single) join_write_k<false, false, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
+    else if (pl.semi) join_write_k<true, true, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
+    else join_write_k<true, false, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
     if (crowded) {
         // one unit per workgroup while there are few: a unit takes some 120 us
         const unsigned cg = (unsigned)(pl.Umax < pl.gridWrite ? pl.Umax : pl.gridWrite);
@@ -3779,7 +3788,9 @@ hipError_t hash_batch_count(const BatchPlan& bp, char* ws, uint64_t* offsets, hi
     if (bp.Umax > 0) {
         const JoinGeom g = batch_geom(bp, ws);
         prof::Scope pc(st, "hash.count");
-        join_count_k<true, false, kBatchBlock><<<(unsigned)bp.gridCount, kBatchBlock, table_lds((uint32_t)bp.cap, false), st>>>(
+        const auto count_k = g.stream ? join_count_k<true, false, kBatchBlock, kStreamed>
+                                      : join_count_k<true, false, kBatchBlock, kPlain>;
+        count_k<<<(unsigned)bp.gridCount, kBatchBlock, table_lds((uint32_t)bp.cap, false), st>>>(
             g, counts, reinterpret_cast<uint64_t*>(ws + bp.off_wave), nullptr, nullptr, nullptr);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -3806,7 +3817,9 @@ hipError_t hash_batch_write(const BatchPlan& bp, char* ws, int32_t* pairs, uint6
     const uint64_t* wave_off = reinterpret_cast<const uint64_t*>(ws + bp.off_wave);
     const uint64_t* total = reinterpret_cast<const uint64_t*>(ws);
     int2* out = reinterpret_cast<int2*>(pairs);
-    join_write_k<true, false, kBatchBlock><<<(unsigned)bp.gridWrite, kBatchBlock, batch_write_lds((uint32_t)bp.cap), st>>>(
+    const auto write_k = g.stream ? join_write_k<true, false, kBatchBlock, kStreamed>
+                                  : join_write_k<true, false, kBatchBlock, kPlain>;
+    write_k<<<(unsigned)bp.gridWrite, kBatchBlock, batch_write_lds((uint32_t)bp.cap), st>>>(
         g, offsets, wave_off, total, out, cap);
     return hipGetLastError();
 }
