@@ -22,6 +22,8 @@
 #include "hash.hpp"
 #include "debug.hpp"
 
+#include <atomic>
+#include <chrono>
 #include <type_traits>
 #include <vector>
 
@@ -833,6 +835,9 @@ constexpr int kRecOrder = 29;
 // Set by the count pass for a crowded unit (its table walked far, or long runs of matches):
 // write_crowded_k writes its pairs, and the write pass takes it as empty.
 constexpr int kRecCrowded = 30;
+// Set by the count pass when kEmitLanes threads met runs of more than kEmitSort matches: written from sorted
+// entries in a batch, and in one join where most units are so (sort_all).
+constexpr int kRecRuns = 31;
 __host__ __device__ __forceinline__ uint4 unit_rec(const PartInfo& pi, uint32_t local, uint32_t cap)
 {
     const uint32_t rc = local / pi.nSs;
@@ -1158,6 +1163,12 @@ constexpr int kEmitSort = 8;  // a probe with at most this many matches orders t
 // them by walks takes longer than the sort (joins of 9000 rows with one hot key, probed in every unit:
 // 60 copies 263 us by walks, 333 sorted; 90 copies 402 and 344, 200 copies 1113 and 428).
 constexpr uint32_t kEmitTable = 72;
+// Nor are shorter runs of matches written by walks when many threads (of a workgroup) met some of more than
+// kEmitSort: they take 25 to 65 ns a pair, and 16 threads with them about as long as the sort.  In one join
+// the sorted units have a kernel of their own, so all units are sorted when three in four are at
+// kEmitLanes, and otherwise those at kEmitOwn: with the line at kEmitLanes alone a join whose units
+// lie on both sides of it pays for both (2M rows of 0.7M keys, each asked for once: 223 us by walks, 349).
+constexpr uint32_t kEmitLanes = 16, kEmitOwn = 128;
 
 __host__ __device__ constexpr uint32_t table_buckets(uint32_t rN)
 {
@@ -1189,8 +1200,9 @@ constexpr uint32_t kOverflow = 1u << 30;
 // are not inlined.
 extern __shared__ uint4 join_lds[];
 
-// Count pass: whether a probe of the unit had more than kEmitTable matches.  Such a probe walks, so this is
-// written where walks are, and the probe loop keeps no register for it.
+// Count pass: threads that met runs of more than kEmitSort matches in the unit, or kEmitOwn and more once a
+// probe had more than kEmitTable.  Such a probe walks, so that is written where walks are, and the probe
+// loop keeps no register for it; the threads are added when the unit ends.
 __shared__ uint32_t long_runs;
 
 struct Table {
@@ -1495,7 +1507,7 @@ __device__ __forceinline__ uint32_t probe_count(const Table& t, int bits, const 
         for (int i = 0; i < N; ++i)
             if (walk[i]) {
                 walk_on<MARKED>(t, x[i], b1[i], b2[i], [&](uint32_t, uint32_t hm) { h[i] += __builtin_popcount(hm); });
-                if (h[i] > kEmitTable) long_runs = 1;
+                if (h[i] > kEmitTable) long_runs = kEmitOwn;
             }
     }
 #pragma unroll
@@ -2261,8 +2273,8 @@ __device__ __attribute__((noinline)) UnitCount count_crowded()
 // unit and wave, where the wave's pairs start inside the unit's output range, so the write pass
 // needs no shared cursor and every pair lands at a position that depends on the input and the
 // plan alone.  Entry 0 of a unit (wave 0 starts at 0) instead holds 1 when some probe of the
-// unit has more than kEmitSort entries in its table, plus 2 for a crowded unit.  Inside a
-// wave's range the pairs of probes with at most two matches come first, in (batch, tuple, lane)
+// unit has more than kEmitSort entries in its table, plus 2 for a crowded unit, plus 4 for one in which
+// kEmitLanes threads or more met such probes.  Inside a wave's range the pairs of probes with at most two matches come first, in (batch, tuple, lane)
 // order, then those of probes with more, in the order the wave queued them; the second half of the
 // unit's record holds, per wave, where that second block starts inside the wave's range.
 constexpr int kJoinWaves = kJoinBlock / kWave;
@@ -2281,21 +2293,22 @@ static_assert(2 * (batch_write_lds(kBatchCap) + kBatchStaticLds + 256) <= 160 * 
 // wave's count of pairs before its block of many-match pairs (low 32 bits: at most two pairs per
 // probe row of the wave) and its count of probe rows with matches when the semi-join is recorded
 // (high 32 bits, else 0); sh: kJoinWaves + 1 words of LDS.  rec_word (partitioned joins): the
-// second word of the unit's record, which receives the canonical-order flag as well.  between:
+// second word of the unit's record, which receives the same three flags.  between:
 // run by every thread after all waves have finished the unit, before the closing barrier.
 template <int B, typename Between>
 __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_many, bool multi,
                                             uint32_t semi_rows, uint32_t u, uint64_t* __restrict__ counts,
                                             uint64_t* __restrict__ wave_off, uint64_t* sh, uint32_t* rec_word,
-                                            bool crowded, uint64_t* unit_pub, uint64_t* pub, uint32_t* sched,
+                                            bool crowded, uint64_t* unit_pub, uint64_t* pub, Told told, uint32_t* sched,
                                             Between between)
 {
     const uint64_t wt = wave_sum64(lane_total);
     const uint64_t wmany = wave_sum64(lane_many);
-    const bool wm = ballot(multi) != 0;
+    const uint64_t wm = ballot(multi);
     const int wv = threadIdx.x / kWave;
     if (lane_id() == 0) {
         sh[wv] = wt | (wm ? (1ull << 63) : 0ull);
+        if (wm) atomicAdd(&long_runs, (uint32_t)__builtin_popcountll(wm));
         wave_off[(size_t)u * kWaveRec + kWaveHalf + wv] = (wt - wmany) | ((uint64_t)semi_rows << 32);
     }
     __syncthreads();
@@ -2306,20 +2319,24 @@ __device__ __forceinline__ void unit_totals(uint64_t lane_total, uint64_t lane_m
         const uint64_t c = w < W ? v & ~(1ull << 63) : 0ull;
         const uint64_t inc = wave_incl_scan64(c);
         const bool any = ballot(w < W && v >> 63) != 0;
-        crowded = crowded || long_runs;
+        const uint32_t flags = (any ? 1u : 0u) | (long_runs >= kEmitLanes ? 4u : 0u) |
+                               (crowded || long_runs >= (B == kBatchBlock ? kEmitLanes : kEmitOwn) ? 2u : 0u);
         if (w < W)
-            wave_off[(size_t)u * kWaveRec + w] = w == 0 ? (any ? 1u : 0u) | (crowded ? 2u : 0u) : inc - c;
+            wave_off[(size_t)u * kWaveRec + w] = w == 0 ? flags : inc - c;
         if (w == W - 1) {
-            if (pub && crowded) {  // told to the host before the unit's count: it is read with the total
-                __hip_atomic_store(pub + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                drain();
+            if (pub && flags > 1) {
+                // told to the host, which reads it with the total: before the unit's count where the host adds
+                // those up, else before this workgroup arrives or its kernel ends, and once a join (768
+                // units' stores to host memory took 70 us)
+                if (unit_pub || atomicExch(told.at, told.id) != told.id)
+                    __hip_atomic_store(pub + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                if (unit_pub) drain();
             }
             store_shared(&counts[u], inc);
             if (unit_pub) __hip_atomic_store(&unit_pub[u], inc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            const uint32_t flags = (any ? 1u << kRecOrder : 0u) | (crowded ? 1u << kRecCrowded : 0u);
             if (flags && rec_word) {
-                atomicOr(rec_word, flags);
-                if (B == kBatchBlock && crowded) sched[kSchedCrowded] = 1;
+                atomicOr(rec_word, flags << kRecOrder);
+                if (B == kBatchBlock && (flags & 2)) sched[kSchedCrowded] = 1;
             }
         }
     }
@@ -2449,7 +2466,7 @@ __global__ JL_COUNT_ATTR(B) void join_count_k(JoinGeom g, uint64_t* __restrict__
         // of a partition has the partition's top bits (a unit without probe keys never reads
         // its table, so its marker does not matter).
         unit_totals<B>(cnt, many, multi, sm.k, u, counts, wave_off, wsum, rec_word, by_sort,
-                       AOS ? nullptr : g.unit_pub, pub, g.sched, [&] {
+                       AOS ? nullptr : g.unit_pub, pub, g.told, g.sched, [&] {
             if (more) clear_table<false, AOS, B>(nx, xa[0], tab);
             if (threadIdx.x < 2) crowded[threadIdx.x] = 0;
             if (threadIdx.x == 0) long_runs = 0;
@@ -2596,14 +2613,14 @@ __device__ __forceinline__ uint64_t write_crowded(uint64_t cursor, uint64_t cman
     return cursor + cmany - at0;
 }
 
-// The write pass of the crowded units, which join_write_k leaves out of its loop (inside it this code's
-// registers cost every other unit 5 to 10%).  Workgroup b looks through units b, b + grid, ..., B at a
+// The write pass of the crowded units (all: of every unit), which join_write_k leaves out of its loop
+// (inside it this code's registers cost every other unit 5 to 10%).  Workgroup b looks through units b, b + grid, ..., B at a
 // time, and writes those that are flagged (crowded units lie next to each other, so neighbouring
 // units go to different workgroups).
 template <bool AOS, int B>
 __device__ __forceinline__ void write_crowded_units(const JoinGeom& g, uint32_t U, const uint64_t* offsets,
                                                     const uint64_t* wave_off, const RawCounts& raw, int2* out,
-                                                    uint64_t cap)
+                                                    uint64_t cap, bool all = false)
 {
     __shared__ uint32_t found[B], nfound;
     const int wv = uniform((int32_t)(threadIdx.x / kWave));
@@ -2614,13 +2631,15 @@ __device__ __forceinline__ void write_crowded_units(const JoinGeom& g, uint32_t 
         __syncthreads();
         const uint64_t mine64 = u0 + (uint64_t)threadIdx.x * gridDim.x;
         const uint32_t mine = mine64 < U ? (uint32_t)mine64 : U;
-        if (mine < U && (AOS ? unit_of(g.urec[mine]).crowded : (wave_off[(size_t)mine * kWaveRec] & 2) != 0))
+        if (mine < U && (all || (AOS ? unit_of(g.urec[mine]).crowded : (wave_off[(size_t)mine * kWaveRec] & 2) != 0)))
             found[atomicAdd(&nfound, 1u)] = mine;
         __syncthreads();
         const uint32_t n = uniform(nfound);
         for (uint32_t k = 0; k < n; ++k) {
             const uint32_t u = uniform(found[k]);
-            set_crowded(g, decode_unit<AOS>(g, u));
+            const Unit un = decode_unit<AOS>(g, u);
+            if (un.rN == 0 || un.sN == 0) continue;  // uniform; not of a flagged unit
+            set_crowded(g, un);
             const uint64_t at = (raw.on ? raw.before(u) : uniform(offs[u])) + (wv ? uniform(wo[(size_t)u * kWaveRec + wv]) : 0ull);
             const uint64_t few = (uint32_t)uniform(wo[(size_t)u * kWaveRec + kWaveHalf + wv]);
             const uint64_t wrote = write_crowded<AOS, B>(at, at + few, out, cap);
@@ -2635,7 +2654,36 @@ __device__ __forceinline__ void write_crowded_units(const JoinGeom& g, uint32_t 
     }
 }
 
-// One join: a kernel of their own, launched when the count pass said there are any, or when its word
+// Whether write_crowded_k writes every unit: three in four have long runs of matches or are crowded, or the
+// crowded ones alone take as many rounds of its workgroups as all of them (join_write_k then adds only
+// its own time; 1M rows, half of them in 8K keys of 64 copies that no row asks for: 314 us, 436 with
+// the crowded ones alone sorted).  By up to
+// kJoinBlock units (partitions are by hash, so any are a sample).
+template <bool AOS>
+__device__ __forceinline__ bool sort_all(const JoinGeom& g, uint32_t U, const uint64_t* wave_off)
+{
+    __shared__ uint32_t have[2];
+    if (threadIdx.x < 2) have[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t n = U < (uint32_t)kJoinBlock ? U : (uint32_t)kJoinBlock;
+    uint32_t flags = 0;  // 1: crowded, 2: with long runs
+    if (threadIdx.x < n) {
+        const uint32_t u = (uint32_t)((uint64_t)threadIdx.x * U / n);
+        flags = AOS ? g.urec[u].y >> kRecCrowded : (uint32_t)wave_off[(size_t)u * kWaveRec] >> 1;
+    }
+    const uint32_t own = (uint32_t)__builtin_popcountll(ballot((flags & 1) != 0));
+    const uint32_t any = (uint32_t)__builtin_popcountll(ballot((flags & 3) != 0));
+    if (lane_id() == 0 && any) {
+        atomicAdd(&have[0], own);
+        atomicAdd(&have[1], any);
+    }
+    __syncthreads();
+    const uint32_t owns = uniform(have[0]), G = gridDim.x;
+    const uint32_t some = n ? (uint32_t)(((uint64_t)owns * U + n - 1) / n) : 0u;
+    return (owns && (some + G - 1) / G == (U + G - 1) / G) || (n && uniform(have[1]) * 4 >= n * 3);
+}
+
+// One join: a kernel of their own before join_write_k, launched when the count pass said there are any, or when its word
 // about it is not at hand.
 template <bool AOS>
 __global__ JL_WRITE_ATTR(kJoinBlock) void write_crowded_k(JoinGeom g, const uint64_t* __restrict__ offsets,
@@ -2646,7 +2694,9 @@ __global__ JL_WRITE_ATTR(kJoinBlock) void write_crowded_k(JoinGeom g, const uint
     const uint32_t U = unit_total(g);
     const RawCounts raw = raw_counts<AOS>(g, offsets, U);
     if ((raw.on ? raw.total : *total) > cap || (g.stamp_at && !raw.on && *g.stamp_at != g.stamp)) return;
-    write_crowded_units<AOS, kJoinBlock>(g, U, offsets, wave_off, raw, out, cap);
+    const bool all = sort_all<AOS>(g, U, wave_off);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *g.all_at = all ? 1u : 0u;
+    write_crowded_units<AOS, kJoinBlock>(g, U, offsets, wave_off, raw, out, cap, all);
 }
 
 // A batch, whose count pass tells the host nothing: by the workgroups of join_write_k when their other
@@ -2694,6 +2744,7 @@ __global__ JL_WRITE_ATTR(B) void join_write_k(JoinGeom g, const uint64_t* __rest
     {
         const RawCounts raw = raw_counts<AOS>(g, offsets, U);
         if ((raw.on ? raw.total : *total) > cap || (g.stamp_at && !raw.on && *g.stamp_at != g.stamp)) return;
+        if (B == kJoinBlock && g.crowded_apart && uniform(*g.all_at)) return;  // written by write_crowded_k
         raw_on = raw.on;
         if (raw_on) raw_before = uniform(raw.before(blockIdx.x));
     }
@@ -3319,6 +3370,7 @@ static JoinGeom make_geom(const HashPlan& pl, const join_rel_t& R, const join_re
     g.cap = (uint32_t)pl.cap;
     g.Umax = pl.Umax;
     g.stamp_at = reinterpret_cast<uint64_t*>(ws + kStampOffset);
+    g.all_at = reinterpret_cast<uint32_t*>(ws + kAllSortedOffset);
     g.stamp = pl.stamp;
     g.dbg = JL_DEBUG ? reinterpret_cast<uint64_t*>(ws + pl.off_dbg) : nullptr;
     g.semi = pl.semi ? reinterpret_cast<uint32_t*>(ws + pl.off_semi) : nullptr;
@@ -3357,6 +3409,14 @@ static JoinGeom make_geom(const HashPlan& pl, const join_rel_t& R, const join_re
 int hash_direct_units(const HashPlan& pl)
 {
     return pl.single && pl.Umax <= kDirectUnits && !JL_DEBUG ? (int)pl.Umax : 0;
+}
+
+// A value that no earlier count pass left in a workspace.
+static unsigned long long next_told_id()
+{
+    static std::atomic<unsigned long long> next{
+        (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count()};
+    return next.fetch_add(1, std::memory_order_relaxed);
 }
 
 hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t& S, char* ws,
@@ -3430,6 +3490,7 @@ hipError_t hash_count(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
     if (pl.Umax > 0) {
         JoinGeom g = make_geom(pl, R, S, ws, pre);
         g.unit_pub = unit_pub;
+        g.told = Told{reinterpret_cast<unsigned long long*>(ws + kToldOffset), next_told_id()};
         const unsigned grid = (unsigned)(pl.single ? pl.Umax : pl.gridCount);
         const size_t lds = table_lds((uint32_t)pl.cap, false);
         // the partitioned path cleared the arrival counter with the partition sizes
@@ -3462,9 +3523,6 @@ hipError_t hash_write(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
     const size_t lds = table_lds((uint32_t)pl.cap, true);
     int2* out = reinterpret_cast<int2*>(pairs);
     prof::Scope pw(st, "hash.write");
-    if (pl.single) join_write_k<false, false, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
-    else if (pl.semi) join_write_k<true, true, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
-    else join_write_k<true, false, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
     if (crowded) {
         // one unit per workgroup while there are few: a unit takes some 120 us
         const unsigned cg = (unsigned)(pl.Umax < pl.gridWrite ? pl.Umax : pl.gridWrite);
@@ -3472,6 +3530,9 @@ hipError_t hash_write(const HashPlan& pl, const join_rel_t& R, const join_rel_t&
         if (pl.single) write_crowded_k<false><<<cg, kJoinBlock, cl, st>>>(g, offsets, wave_off, total, out, cap);
         else write_crowded_k<true><<<cg, kJoinBlock, cl, st>>>(g, offsets, wave_off, total, out, cap);
     }
+    if (pl.single) join_write_k<false, false, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
+    else if (pl.semi) join_write_k<true, true, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
+    else join_write_k<true, false, kJoinBlock, kEither><<<grid, kJoinBlock, lds, st>>>(g, offsets, wave_off, total, out, cap);
     return hipGetLastError();
 }
 

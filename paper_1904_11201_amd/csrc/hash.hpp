@@ -27,6 +27,18 @@ struct SideItem {
 constexpr int kSchedCrowded = 64;
 constexpr int kSchedWords = 96;
 
+// Workspace header: whether the write pass sorts every unit (see kEmitOwn).
+constexpr size_t kAllSortedOffset = 192;
+
+// Workspace header: where a count pass leaves its own value when it has told the host of units to be
+// sorted (a value, as no launch clears the word).
+constexpr size_t kToldOffset = 200;
+struct Told {
+    unsigned long long* at;
+    unsigned long long id;
+};
+
+
 // Everything the count and write kernels need to walk the work units.
 struct JoinGeom {
     const int32_t* rk;  // single: the input build keys
@@ -46,12 +58,14 @@ struct JoinGeom {
     int bits;                   // partition bits; the table position uses the bits below them
     int P;
     int single;
-    int crowded_apart;  // write pass: a kernel of their own writes the crowded units
+    int crowded_apart;  // write pass: units marked crowded are left to write_crowded_units
     int contig;  // write pass: contiguous runs of units per workgroup (else round robin)
     uint64_t* stamp_at;  // plan stamp in the workspace header (NULL for batches: no re-planning)
     uint64_t stamp;      // this plan's stamp: the count pass records it, the write pass checks it;
                          // its complement where the unit counts were left unscanned
+    uint32_t* all_at;    // write pass: whether write_crowded_k wrote every unit (read if crowded_apart)
     uint64_t* unit_pub;  // count pass: pinned words of the units' counts (NULL: they are scanned)
+    Told told;           // count pass, with pub
     uint64_t* dbg;       // checking build: pairs written per unit (NULL: not counted)
     uint32_t* semi;      // the probe rows with matches, per unit and wave (NULL: not recorded)
     int stream;          // the probe tuples are read non-temporally (kStreamBytes)

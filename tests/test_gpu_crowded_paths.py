@@ -188,3 +188,98 @@ def test_batch_with_hot_build_keys(copies):
         batch.materialize(pairs)
         for j, ref in enumerate(refs):
             assert np.array_equal(canon_gpu(pairs[offs[j]:offs[j + 1]]), ref), j
+
+
+@gpu
+@pytest.mark.parametrize("rows", [15, 16, 17, 127, 128, 129])
+@pytest.mark.parametrize("copies", [9, 30])
+def test_around_the_line_for_runs_of_matches(copies, rows):
+    """`rows` probe rows, one to a thread, that match more than eight build rows each: below and above the
+    counts from which a unit, or every unit of a join, is written from sorted entries."""
+    need_gpu()
+    from paper_1904_11201_amd import _native
+    from paper_1904_11201_amd import join as J
+    R, S = _hot_join([1, 2, 3], 5000, 900, copies, domain=30_000)
+    S.key[:] = np.arange(len(S.key)) + 100_000
+    S.key[:rows] = 1 + np.arange(rows) % 3
+    ref = _expect(R, S)
+    assert len(ref) >= rows * copies
+    dR, dS = dev_rel(R), dev_rel(S)
+    for bits in (0, 1, 3):
+        _native.tune_set("hash.bits", bits, local=True)
+        try:
+            log(f"{rows} rows with runs of {copies}, bits {bits}")
+            assert np.array_equal(canon_gpu(J.hash_join(dR, dS)), ref)
+            assert np.array_equal(canon_gpu(_written_by_another_thread(dR, dS, len(ref))), ref)
+            assert np.array_equal(canon_gpu(_batch(dR, dS, bits)), ref)
+        finally:
+            _native.tune_set("hash.bits", None, local=True)
+
+
+def _batch(R, S, bits):
+    import torch
+
+    from paper_1904_11201_amd import join as J
+    batch = J.Batch([J.Job(R, S, bits)])
+    offs = batch.count().cpu().tolist()
+    pairs = torch.empty((offs[-1], 2), dtype=torch.int32, device="cuda")
+    batch.materialize(pairs)
+    return pairs
+
+
+def _repeated(nR, d, nS, seed=5):
+    g = datagen.rng_for(seed)
+    k = nR // d
+    R = datagen.Rel(key=datagen.uniform_keys(g, nR, 0, k), rid=g.permutation(nR).astype(np.int32))
+    return R, datagen.Rel(key=datagen.uniform_keys(g, nS, 0, 2 * k), rid=g.permutation(nS).astype(np.int32))
+
+
+@gpu
+@pytest.mark.parametrize("nR,nS,d", [(nR, nS, d) for d in (3, 4, 6, 12, 40)
+                                     for nR, nS in ((700, 700), (9001, 2000), (30_000, 5000), (300_001, 40_000),
+                                                    (2_500_000, 50_000))] +
+                                    [(150_000, 2_200_000, d) for d in (3, 4, 6)])
+def test_builds_of_evenly_repeated_keys(nR, nS, d):
+    """Every key has about d copies: units on both sides of the lines, of one and of several rounds of
+    workgroups, and joins all of whose units are sorted."""
+    need_gpu()
+    from paper_1904_11201_amd import join as J
+    R, S = _repeated(nR, d, nS)
+    ref = _expect(R, S)
+    dR, dS = dev_rel(R), dev_rel(S)
+    for name, run in (("join", lambda: J.hash_join(dR, dS)),
+                      ("resident build", lambda: J.ResidentBuild(dR).probe(dS)),
+                      ("written by another thread", lambda: _written_by_another_thread(dR, dS, len(ref))),
+                      ("pre-filtered", lambda: J.hash_join(dR, dS, prefilter=True)),
+                      ("batch", lambda: _batch(dR, dS, -1))):
+        log(f"{nR} rows of keys with {d} copies x {nS}: {name}")
+        assert np.array_equal(canon_gpu(run()), ref), name
+
+
+@gpu
+@pytest.mark.parametrize("nR", [9000, 400_000])
+def test_evenly_repeated_keys_are_not_walked(nR):
+    """Keys of 32 copies, each asked for once: at most 4 times the join of as many rows in keys of 2 (their
+    walks took 10 times)."""
+    need_gpu()
+    import time
+
+    import torch
+
+    from paper_1904_11201_amd.join import hash_join
+    took = {}
+    for d in (2, 32):
+        R, _ = _repeated(nR, d, 1)
+        S = datagen.Rel(key=np.arange(nR // d, dtype=np.int32), rid=np.arange(nR // d, dtype=np.int32))
+        R, S = dev_rel(R), dev_rel(S)
+        log(f"{nR} rows of keys with {d} copies")
+        runs = []
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            hash_join(R, S)
+            torch.cuda.synchronize()
+            runs.append(time.perf_counter() - t0)
+        took[d] = min(runs)
+    log(f"us: {[(k, round(v * 1e6)) for k, v in took.items()]}")
+    assert took[32] < 4 * took[2]
