@@ -2274,9 +2274,10 @@ __device__ __attribute__((noinline)) UnitCount count_crowded()
 // needs no shared cursor and every pair lands at a position that depends on the input and the
 // plan alone.  Entry 0 of a unit (wave 0 starts at 0) instead holds 1 when some probe of the
 // unit has more than kEmitSort entries in its table, plus 2 for a crowded unit, plus 4 for one in which
-// kEmitLanes threads or more met such probes.  Inside a wave's range the pairs of probes with at most two matches come first, in (batch, tuple, lane)
-// order, then those of probes with more, in the order the wave queued them; the second half of the
-// unit's record holds, per wave, where that second block starts inside the wave's range.
+// kEmitLanes threads or more met such probes.  Inside a wave's range the pairs of probes with at most
+// two matches come first, in (batch, tuple, lane) order, then those of probes with more, in the order the
+// wave queued them; the second half of the unit's record holds, per wave, where that second block starts
+// inside the wave's range.
 constexpr int kJoinWaves = kJoinBlock / kWave;
 constexpr int kWaveRec = 2 * kJoinWaves;  // uint64 entries per unit in the wave record
 constexpr int kWaveHalf = kJoinWaves;     // its second half (a 512-thread workgroup uses 8 + 8)
@@ -3011,9 +3012,13 @@ static int default_slice(int64_t nS, int num_cus)
 // a join, unpartitioned / partitioned): two chunks, 10K x 1M 46 / 70, x 8M 125 / 160, x 64M 664 / 726,
 // 18K x 8M 124 / 156, x 64M 635 / 746; three, 27K x 1M 74 / 66, x 4M 129 / 97, x 16M 364 / 212; four,
 // 36K x 1M 59 / 63, x 2M 76 / 78, x 4M 125 / 95; eight, 73K x 1M 76 / 62; sixteen, 147K x 1M 124 / 64,
-// x 16M 1185 / 183.  So: two chunks never, from three on where (chunks - 1) * nS exceeds 6M repeats (a few
-// us to either side of the line for three and eight chunks).  The semi-join's write pass leaves out
-// most rows, and partitioned it wins from two chunks on: 10K x 4M, 1% matching 74 / 86, x 16M 189 / 148.
+// x 16M 1185 / 183.  (Of three chunks or four counted alone, without the write pass, partitioning costs
+// 20 to 25 us at 4M to 8M rows, where the join gains 10 to 60: 27K x 8M 85 / 102 counted, 209 / 145
+// joined.  The plan is made before it is known whether the pairs are wanted.)  So: two chunks never, from
+// three on where (chunks - 1) * nS exceeds 6M repeats (a few us to either side of the line for three and
+// eight chunks).  The same line serves the semi-join, whose write pass leaves out the rows that match
+// nothing: two chunks, 15K x 14M, 1% matching 164 / 148, half 167 / 206, all 168 / 267; four, 30K x 14M
+// 286 / 142, 292 / 190, 295 / 230.
 constexpr int64_t kSingleRepeats = (int64_t)6 << 20;
 // Fewer partitions than this leave too few units, and LDS atomics that collide (100K x 16M: 306 us
 // with 8 partitions, 186 with 16, 184 with 32, 194 with 64; 36K x 16M: 208, 185, 203, 254).
@@ -3036,7 +3041,7 @@ HashPlan hash_plan(int64_t nR, int64_t nS, int num_cus, int prebuilt_bits, bool 
     // a join under single_max chunks set by the caller, or asked to stay unpartitioned
     // (keep_single), is not moved by the rule above
     const int64_t chunks = ceil_div(nR, cap);
-    const bool repeats_ok = single_knob >= 0 || keep_single || (chunks <= 2 && !semi) ||
+    const bool repeats_ok = single_knob >= 0 || keep_single || chunks <= 2 ||
                             (chunks - 1) * nS <= kSingleRepeats;
     pl.single = !pl.prebuilt &&
                 (forced_bits == 0 || (forced_bits < 0 && nR <= single_max && repeats_ok));
@@ -3229,7 +3234,7 @@ static hipError_t cursors_side(uint32_t* grp, const uint32_t* base, int64_t stri
 
 // Partition starts and group starts of both sides (a NULL totR or totS skips that side), and
 // the run offsets of the sides' tiles given by bR and bS (cnt NULL: none): one launch up to
-// kFuseParts partitions, else a scan and a cursor kernel per side (then no run offsets: batches
+// kFuseStarts partitions, else a scan and a cursor kernel per side (then no run offsets: batches
 // compute theirs with band_batch_k).
 static hipError_t starts_sides(uint32_t* totR, uint32_t* baseR, uint32_t* grpR,
                                uint32_t* totS, uint32_t* baseS, uint32_t* grpS, int64_t n,

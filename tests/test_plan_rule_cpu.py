@@ -27,6 +27,8 @@ def test_more_tables_are_partitioned_past_the_repeats():
     assert _partitioned(16 * CAP + 1, 1000)
 
 
-def test_the_semi_join_is_partitioned_from_two_tables_on():
-    assert not _partitioned(2 * CAP, 6 * M, n.JOIN_KIND_HASH_PREFILTER)
-    assert _partitioned(2 * CAP, 6 * M + 1, n.JOIN_KIND_HASH_PREFILTER)
+def test_the_semi_join_follows_the_same_rule():
+    for nS in (6 * M, 6 * M + 1, 64 * M):
+        assert not _partitioned(2 * CAP, nS, n.JOIN_KIND_HASH_PREFILTER)
+    assert not _partitioned(3 * CAP, 3 * M, n.JOIN_KIND_HASH_PREFILTER)
+    assert _partitioned(3 * CAP, 3 * M + 1, n.JOIN_KIND_HASH_PREFILTER)
