@@ -22,9 +22,9 @@
  *     current HIP device.  join_rel_t / join_pred_t structs themselves and `count` are HOST
  *     pointers (except join_hash_noalloc's `count`, a device pointer).  The caller owns every
  *     buffer; the library never allocates device memory and keeps no pointer after a call
- *     returns.  The one piece of device memory the library holds is the static array (64 MiB and 128 KiB) that
- *     join_hash_noalloc works in, which exists once per GPU from the loading of the library's
- *     GPU code until the process ends.
+ *     returns.  The one piece of device memory the library holds is the static array (64 MiB and
+ *     128 KiB) that join_hash_noalloc works in, which exists once per GPU from the loading of
+ *     the library's GPU code until the process ends.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).  All device work is
  *     enqueued on it in order.  The only host synchronisation is the wait for the exact count
  *     in join_count, join_hash, join_theta and join_probe_count: the kernel that produces it
@@ -58,11 +58,11 @@ extern "C" {
 #define JOIN_KIND_HASH 1  /* equi join R.key = S.key (Section 3.3.2, hash join)                */
 #define JOIN_KIND_THETA 2 /* theta join, nested-loop evaluation (Sections 3.3.1 and 4.2)       */
 #define JOIN_KIND_THETA_REGION 3 /* theta join with the improved algorithm's region pruning
-                                  * (Section 4.2, Algorithm 3): key ranges cut into buckets shared
-                                  * by both tables; white regions skipped, green regions counted
-                                  * and cross-joined without evaluation, red regions evaluated by
-                                  * the nested loop.  Same predicates and results as
-                                  * JOIN_KIND_THETA. */
+                                  * (Section 4.2, Algorithm 3): both tables sorted by column a
+                                  * through buckets they share, so the S rows that satisfy op_a
+                                  * with an R row are one interval, a green region, and all
+                                  * others white; only a condition on c is evaluated, inside the
+                                  * interval.  Same predicates and results as JOIN_KIND_THETA. */
 #define JOIN_KIND_HASH_PREFILTER 4 /* equi join preceded by the pre-filter of Algorithm 1
                                     * (Section 3.1): a relation of at most 2^21 rows gets a bit
                                     * filter of its keys (16 bits per row, at most 2^24 bits) and
@@ -111,7 +111,10 @@ typedef struct {
 /* Workspace size in bytes needed by join_count / join_materialize / join_hash / join_theta for
  * this kind and these sizes.  Depends only on (kind, nR, nS, pred) and the library's tuning
  * environment (JOIN_HASH_BITS, ...), so the same value serves a count and its later
- * materialize.  Returns 0 for invalid arguments (kind unknown, n < 0). */
+ * materialize.  Returns 0 for invalid arguments (kind unknown, n < 0).
+ * A hash join of a build of more than two LDS tables (18,432 rows) is partitioned when it repeats
+ * too many probes otherwise, and then needs 8 bytes for every row of both sides (100K x 16M rows:
+ * 135 MB; unpartitioned, as with "hash.single_max_chunks" set to 16, 136 KB). */
 size_t join_workspace_bytes(int kind, int64_t nR, int64_t nS, const join_pred_t* pred);
 
 /* Exact result size (Section 3.3.3, done exactly).  Runs the count pass and the device scan of
@@ -147,11 +150,11 @@ int join_theta(const join_rel_t* R, const join_rel_t* S, const join_pred_t* pred
  * For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid allocation): join_hash with its workspace taken from a static
  * device array of 64 MiB and 128 KiB that the library holds on every GPU it runs on until the
- * process ends, instead of a caller buffer.  The call allocates nothing (no hipMalloc, hipFree or allocating
- * library routine) and does not synchronise: the exact count is written to `count`, a DEVICE
- * pointer to one uint64, and the pairs are written to `pairs` (device, `capacity` pairs) only if
- * the count fits (device-side snprintf semantics: count always set, pairs written only when
- * count <= capacity).  Same inputs and result as join_hash.
+ * process ends, instead of a caller buffer.  The call allocates nothing (no hipMalloc, hipFree or
+ * allocating library routine) and does not synchronise: the exact count is written to `count`, a
+ * DEVICE pointer to one uint64, and the pairs are written to `pairs` (device, `capacity` pairs)
+ * only if the count fits (device-side snprintf semantics: count always set, pairs written only
+ * when count <= capacity).  Same inputs and result as join_hash.
  * Every call on one GPU uses that GPU's array, which keeps the last call's contents; each call
  * clears what it accumulates into before use.  Calls that overlap in time on one GPU (other
  * streams, other host threads) race on the array and must be serialised by the caller.

@@ -70,7 +70,7 @@ struct JoinGeom {
     uint32_t* semi;      // the probe rows with matches, per unit and wave (NULL: not recorded)
     int stream;          // the probe tuples are read non-temporally (kStreamBytes)
     uint32_t* sched;     // [kSchedWords] of a batch: count ticket, write ticket, write arrivals, and at
-                         // kSchedCrowded whether some unit is crowded (NULL: static shares)
+                         // kSchedCrowded whether some unit is to be sorted (NULL: static shares)
 };
 
 struct HashPlan {

@@ -11,11 +11,13 @@
 //
 //   1. setup:    value bins over a sample of both sides (gathered by one launch, binned by the
 //                next), buckets (quantiles of the sample) made of whole bins, so both sides share
-//                boundaries and bucket ids rise with the value;
+//                boundaries and bucket ids rise with the value; where a few bins hold most of the
+//                sample, buckets between quantiles of the sorted sample instead;
 //   2. sizes:    rows of each bucket; the last workgroup turns them into starts;
 //   3. scatter:  rows (a, [c,] rid) into their buckets, tile by tile through LDS;
 //   4. sort:     each bucket sorted by a in LDS, written as columns: both sides are sorted;
-//   5. count:    each R row's interval and its matches; the last workgroup scans the counts;
+//   5. count:    each R row's interval and its matches, long intervals walked by the wave and wide
+//                ones cut into shares; the last workgroup scans the counts;
 //   6. write:    the pairs of each wave from the offset the count pass gave it.
 // Sides that fit one workgroup's LDS skip 1 to 3.
 //

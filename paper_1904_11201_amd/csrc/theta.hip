@@ -45,7 +45,6 @@ struct ThetaGeom {
     int64_t U;    // units = R blocks * S tiles
     int2* stash;  // [U][K] matches kept by the count pass (selective predicates), or NULL
     int64_t K;
-    int64_t nOff;          // entries of the offsets array the write pass reads
     uint64_t* stamp_at;    // plan stamp in the workspace header: recorded by the count pass,
     uint64_t stamp;        // checked by the write pass
     uint64_t* dbg;         // checking build: pairs written per unit (NULL: not counted)
@@ -315,7 +314,7 @@ __global__ __launch_bounds__(kThetaBlock) void theta_write_k(ThetaGeom g,
     if (u >= g.U) return;
     {
         const uint64_t off = uniform(offsets[u]);
-        const uint64_t cnt = (u + 1 < g.nOff ? uniform(offsets[u + 1]) : tot) - off;
+        const uint64_t cnt = (u + 1 < g.U ? uniform(offsets[u + 1]) : tot) - off;
         if (cnt == 0) return;
         if (g.stash && cnt <= (uint64_t)g.K) {  // the count pass kept every match of this unit
             const int2* st = g.stash + u * g.K;
@@ -434,7 +433,6 @@ ThetaGeom geom(const ThetaPlan& pl, const join_rel_t& R, const join_rel_t& S, co
     g.TS = pl.TS;
     g.nSt = pl.nSt;
     g.U = pl.U;
-    g.nOff = pl.U;
     g.stamp_at = reinterpret_cast<uint64_t*>(ws + kStampOffset);
     g.stamp = pl.stamp;
     g.dbg = JL_DEBUG ? reinterpret_cast<uint64_t*>(ws + pl.off_dbg) : nullptr;
